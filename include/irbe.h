@@ -145,18 +145,17 @@ typedef struct {
                               (2^(1/6) for the soft spheres of the paper's
                               primitive-model electrolytes, Sec. 4)              */
     int32_t shell_entries; /* storage of the shell lists S(i) (split lists only):
-                              IRBE_ENTRIES_AUTO: 16-bit codes, the member's
-                              stencil row and its position in that row's
-                              candidate range, where the build of dense cells
-                              (>= 4 atoms per cell on average) runs, the shell
-                              stencil has at most 64 rows and every row's
-                              candidate range fits the code (otherwise, and once
-                              a build finds a range too long, 32-bit indices);
-                              IRBE_ENTRIES_32: 32-bit sorted indices always.
-                              Lists, batches and results are the same either way:
-                              the codes halve the shell rows' device memory (2
-                              bytes per entry of capacity) and the bytes the list
-                              build writes and the pair kernel reads.            */
+                              IRBE_ENTRIES_AUTO: compact, one bit per candidate of
+                              the atom's block of up to 32 atoms, where the build
+                              of dense cells (>= 4 atoms per cell on average)
+                              runs, the shell stencil has at most 128 rows, a
+                              block at most 8,192 candidates and a stencil row at
+                              most 1,024 (otherwise, and once a build finds more,
+                              32-bit indices); IRBE_ENTRIES_32: 32-bit sorted
+                              indices always. Lists, batches and results are the
+                              same either way: the masks take a fifth of the
+                              device memory of the indices, and of the bytes the
+                              list build writes and the pair kernel reads.       */
 } irbe_config;
 
 /* Create a handle for one system size and parameter set; work is queued on
@@ -305,11 +304,11 @@ irbe_status irbe_get_timing(irbe_handle h, double* ms_host, int64_t capacity, in
  *   IRBE_DBG_ADJ_BATCH   int64 [1]          1 when the last compute_forces_backward
  *                                           read the batch atoms written by the
  *                                           forward, 0 when it read the ranks and
- *                                           the shell rows (with 16-bit shell
- *                                           entries: decoded them first into
+ *                                           the shell rows (with compact shell
+ *                                           lists: decoded them first into
  *                                           batch atoms)
  *   IRBE_DBG_SHELL_BITS  int64 [1]          storage of the current shell lists:
- *                                           16 (codes) or 32 (sorted indices) */
+ *                                           16 (compact) or 32 (sorted indices) */
 enum {
     IRBE_DBG_CELL_START = 1,
     IRBE_DBG_CELL_ATOMS = 2,

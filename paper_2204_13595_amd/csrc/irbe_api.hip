@@ -232,8 +232,9 @@ int32_t ktable(double beta, double L, std::vector<uint64_t>& U, double& H, doubl
 
 int32_t round_up32(double v) { return (int32_t)((std::ceil(v) + 31.0) / 32.0) * 32; }
 
-// Rows of cap_core and cap_shell entries per atom; shell entries of 2 bytes
-// (16-bit codes) while the handle can use them, else 4.
+// Rows of cap_core entries and, per atom, cap_shell sorted indices or (while the
+// handle stores its shell lists as masks) cap_words mask words; cap_shell then
+// only bounds the list lengths.
 hipError_t alloc_lists(irbe_ctx* h, int32_t cap_core, int32_t cap_shell)
 {
     const size_t n = (size_t)h->cfg.n_atoms;
@@ -242,37 +243,58 @@ hipError_t alloc_lists(irbe_ctx* h, int32_t cap_core, int32_t cap_shell)
     h->core = h->shell = nullptr;
     hipError_t e = dalloc(h, &h->core, n * (size_t)cap_core);
     if (e != hipSuccess) return e;
-    const int32_t eb = h->shell16_ok && h->sgroup != nullptr && irbe::shell16_possible(h) ? 2 : 4;
-    e = dalloc(h, &h->shell, (n * (size_t)cap_shell * eb + 3) / 4);
+    const int want = h->masks_ok ? irbe::mask_words_wanted(h) : 0;
+    h->masks = want > 0;
+    if (h->masks) {
+        const size_t slots = (size_t)list_block_slots(h->geo, h->stencil, h->cfg.n_atoms);
+        h->cap_words = std::max(h->cap_words, want);
+        dfree(h, h->blk_words);
+        h->blk_words = nullptr;
+        e = dalloc(h, &h->blk_words, 2 * slots * (size_t)h->cap_words);
+        if (e == hipSuccess && !h->blk_nw) e = dalloc(h, &h->blk_nw, slots);
+        if (e == hipSuccess && !h->slot_of) e = dalloc(h, &h->slot_of, n);
+        if (e != hipSuccess) return e;
+    }
+    e = dalloc(h, &h->shell, n * (size_t)(h->masks ? h->cap_words : cap_shell));
     if (e != hipSuccess) return e;
-    h->shell_bytes = eb;
     h->cap_core = cap_core;
     h->cap_shell = cap_shell;
     return hipSuccess;
 }
 
-// Shell rows of 4-byte entries once the 16-bit codes have been given up
-// (after the queued work that may still read the old rows).
+// Shell rows of 32-bit indices once the masks have been given up (after the
+// queued work that may still read the old rows).
 hipError_t ensure_shell_rows_32(irbe_ctx* h)
 {
-    if (h->shell_bytes == 4 || h->shell16_ok) return hipSuccess;
+    if (!h->masks || h->masks_ok) return hipSuccess;
     const hipError_t e = hipStreamSynchronize(h->stream);
     if (e != hipSuccess) return e;
     h->have_lists = false;
     return alloc_lists(h, h->cap_core, h->cap_shell);
 }
 
+// Longer mask rows for blocks of max_words words: true when the rows must be
+// allocated again (beyond kMaskMaxWords the masks are given up).
+bool grow_mask_rows(irbe_ctx* h, int32_t max_words)
+{
+    if (!h->masks || max_words <= h->cap_words) return false;
+    if (max_words > kMaskMaxWords) h->masks_ok = false;
+    else h->cap_words = std::min(kMaskMaxWords, (max_words + max_words / 8 + 3) / 4 * 4);
+    return true;
+}
+
 // Rows for lists of the given longest lengths, grown by at least 30% so that a
 // few rounds converge (waits: the old rows may still be read by queued work).
-hipError_t grow_lists(irbe_ctx* h, int32_t max_core, int32_t max_shell)
+hipError_t grow_lists(irbe_ctx* h, int32_t max_core, int32_t max_shell, int32_t max_words)
 {
+    const bool words = grow_mask_rows(h, max_words);
     const int32_t nc = max_core > h->cap_core
                            ? std::max(round_up32(1.15 * max_core + 32.0), round_up32(1.3 * h->cap_core))
                            : h->cap_core;
     const int32_t ns = !h->stencil && max_shell > h->cap_shell
                            ? std::max(round_up32(1.15 * max_shell + 32.0), round_up32(1.3 * h->cap_shell))
                            : h->cap_shell;
-    if (nc == h->cap_core && ns == h->cap_shell) return hipSuccess;
+    if (nc == h->cap_core && ns == h->cap_shell && !words) return hipSuccess;
     if (ns > 65535) return hipErrorInvalidValue;
     const hipError_t e = hipStreamSynchronize(h->stream);
     if (e != hipSuccess) return e;
@@ -280,49 +302,38 @@ hipError_t grow_lists(irbe_ctx* h, int32_t max_core, int32_t max_shell)
     return alloc_lists(h, nc, ns);
 }
 
-// Sorted index of the 16-bit shell entry e of an atom of list-build group grp,
-// decoded on the host (cs: the cell starts of the build); the layout of the
-// codes is that of ListCode. Clamped to [0, N) as on the device.
-int32_t decode_shell_entry(const ListCode& lc, const std::vector<int32_t>& cs, int32_t grp, uint32_t e)
+// The first len members (sorted indices) of a shell row stored as a mask: the
+// set bits of its nw words, half q of word w holding the candidates base[2 w + q] ...
+void expand_mask_row(const uint32_t* mask, const int32_t* base, int nw, int64_t len, std::vector<int32_t>& row)
 {
-    if (grp < 0 || grp >= lc.gpr * lc.n_c * lc.n_c) return 0;
-    auto wrap = [&](int c) { return c < 0 ? c + lc.n_c : (c >= lc.n_c ? c - lc.n_c : c); };
-    const int rid = (int)(e >> lc.pb), p = (int)(e & ((1u << lc.pb) - 1));
-    if (rid >= lc.span * lc.span) return 0;
-    const int rowid = grp / lc.gpr;
-    const int cz = rowid / lc.n_c, cy = rowid % lc.n_c;
-    const int x0 = (grp % lc.gpr) * lc.G;
-    const int span_u = std::min(lc.G, lc.n_c - x0) - 1 + lc.span;
-    const int xu0 = wrap(x0 + lc.lo);
-    const int lenA = std::min(span_u, lc.n_c - xu0);
-    const int z = wrap(cz + rid / lc.span + lc.lo), y = wrap(cy + rid % lc.span + lc.lo);
-    const int64_t row = ((int64_t)z * lc.n_c + y) * lc.n_c;
-    const int32_t a = cs[row + xu0], na = cs[row + xu0 + lenA] - a;
-    const int64_t j = p < na ? (int64_t)a + p : (int64_t)cs[row] + (p - na);
-    return (int32_t)std::min<int64_t>(std::max<int64_t>(j, 0), cs.back() - 1);
+    row.clear();
+    for (int w = 0; w < nw; ++w)
+        for (uint32_t m = mask[w]; m != 0 && (int64_t)row.size() < len; m &= m - 1)
+            row.push_back(base[2 * w + (__builtin_ctz(m) >> 4)] + (__builtin_ctz(m) & 15));
+    row.resize((size_t)len, 0);
 }
 
 irbe_status check_device_error(irbe_ctx* h)
 {
     uint32_t err = 0;
-    int32_t mx[2] = {0, 0};
+    int32_t mx[3] = {0, 0, 0};
     IRBE_TRY(h, hipMemcpyAsync(&err, h->err, sizeof(err), hipMemcpyDeviceToHost, h->stream), "read error word");
     IRBE_TRY(h, hipMemcpyAsync(mx, h->maxcnt, sizeof(mx), hipMemcpyDeviceToHost, h->stream), "read list sizes");
     IRBE_TRY(h, hipStreamSynchronize(h->stream), "synchronize");
     if (err) {
         IRBE_TRY(h, launch_fill_i32(h->stream, (int32_t*)h->err, 0, 1), "clear error word");
         if (err & ERR_NONFINITE) return fail(h, IRBE_ENONFINITE, "non-finite position");
-        // a stencil row's candidates beyond the 16-bit entry codes: 32-bit entries
-        // from the next build on
-        if (err & ERR_SHELL_CODE) h->shell16_ok = false;
+        // a stencil row's candidates too many for the masks: 32-bit entries from the
+        // next build on
+        if (err & ERR_SHELL_ROW) h->masks_ok = false;
         // the rows of some build since the last check were too short: the forces
         // computed from those lists miss entries; grow the rows for the next build
-        const hipError_t e = grow_lists(h, std::max(mx[0], h->max_core), std::max(mx[1], h->max_shell));
+        const hipError_t e = grow_lists(h, std::max(mx[0], h->max_core), std::max(mx[1], h->max_shell), mx[2]);
         if (e == hipErrorInvalidValue) return fail(h, IRBE_ECAPACITY, "more than 65535 list entries per atom");
         if (e != hipSuccess) return hip_fail(h, e, "grow lists");
-        if (err & ERR_SHELL_CODE)
+        if (err & ERR_SHELL_ROW)
             return fail(h, IRBE_ECAPACITY,
-                        "a shell stencil row's candidates exceeded the 16-bit entry codes in a build since the last "
+                        "a shell stencil row's candidates exceeded the shell masks in a build since the last "
                         "check: forces computed from those lists are wrong; 32-bit entries from now on, build the "
                         "lists again");
         return fail(h, IRBE_ECAPACITY,
@@ -345,10 +356,10 @@ irbe_status poll_list_check(irbe_ctx* h)
     const uint32_t err = (uint32_t)h->chk_host[0];
     h->max_core = h->chk_host[1];
     h->max_shell = h->chk_host[2];
-    // (an overflowing code: 32-bit entries from the next build on)
-    if (err & ERR_SHELL_CODE) h->shell16_ok = false;
+    // (a row range too long for the masks: 32-bit entries from the next build on)
+    if (err & ERR_SHELL_ROW) h->masks_ok = false;
     if (err & (ERR_CORE_CAP | ERR_SHELL_CAP)) {
-        const hipError_t e = grow_lists(h, h->max_core, h->max_shell);
+        const hipError_t e = grow_lists(h, h->max_core, h->max_shell, h->chk_host[3]);
         if (e == hipErrorInvalidValue) return fail(h, IRBE_ECAPACITY, "more than 65535 list entries per atom");
         if (e != hipSuccess) return hip_fail(h, e, "grow lists");
     }
@@ -486,7 +497,7 @@ irbe_status irbe_create(const irbe_config* cfg, void* hip_stream, irbe_handle* o
     h->real_size = h->fp64 ? 8 : 4;
     h->full_list = c.p_shell <= 0;
     h->stencil = c.shell_source == IRBE_SHELL_STENCIL;
-    h->shell16_ok = c.shell_entries == IRBE_ENTRIES_AUTO;
+    h->masks_ok = c.shell_entries == IRBE_ENTRIES_AUTO;
     geometry(c, h->geo);
     if (h->geo.n_c < 3) {
         delete h;
@@ -526,7 +537,7 @@ irbe_status irbe_create(const irbe_config* cfg, void* hip_stream, irbe_handle* o
 #define ALLOC(expr)                      \
     if (e == hipSuccess) e = (expr);
     ALLOC(dalloc(h, &h->err, 1));
-    ALLOC(dalloc(h, &h->maxcnt, 2));
+    ALLOC(dalloc(h, &h->maxcnt, 3));
     ALLOC(dalloc(h, &h->adj_atomics, 1));
     ALLOC(dalloc(h, &h->ktab, U.size()));
     ALLOC(dalloc_bytes(h, &h->q_orig, n * rs));
@@ -552,6 +563,7 @@ irbe_status irbe_create(const irbe_config* cfg, void* hip_stream, irbe_handle* o
         ALLOC(dalloc(h, &lv, 2));
         h->scan_levels.push_back(lv);
     }
+    ALLOC(dalloc(h, &h->blk_start, (size_t)list_block_slots(h->geo, h->stencil, c.n_atoms)));
     ALLOC(dalloc(h, &h->perm, n));
     ALLOC(dalloc(h, &h->rank, n));
     ALLOC(dalloc(h, &h->spos, n));
@@ -565,7 +577,6 @@ irbe_status irbe_create(const irbe_config* cfg, void* hip_stream, irbe_handle* o
     h->p_stride = c.p_shell > 0 ? (c.p_shell + 3) / 4 * 4 : 0;
     if (h->p_stride > 0) ALLOC(dalloc(h, &h->ranks, n * (size_t)h->p_stride));
     if (h->stencil) ALLOC(dalloc(h, &h->scell, n));
-    if (!h->full_list && !h->stencil && h->shell16_ok) ALLOC(dalloc(h, &h->sgroup, n));
     ALLOC(dalloc(h, &h->nshell, n));
     ALLOC(dalloc_bytes(h, &h->fsr, 3 * n * rs));
     ALLOC(dalloc(h, &h->pair_part, (size_t)nb64 * kPairPartials));
@@ -737,10 +748,10 @@ irbe_status irbe_build_lists(irbe_handle h, const void* pos, uint64_t step)
         if (st != IRBE_OK) return st;
         IRBE_TRY(h, ensure_shell_rows_32(h), "reallocate the shell rows");
         IRBE_STAGE(h, IRBE_STAGE_BIN, launch_bin(h, pos), "binning");
-        IRBE_TRY(h, launch_fill_i32(h->stream, h->maxcnt, 0, 2), "list build");
+        IRBE_TRY(h, launch_fill_i32(h->stream, h->maxcnt, 0, 3), "list build");
         IRBE_STAGE(h, IRBE_STAGE_LISTS, launch_build_lists(h), "list build");
         IRBE_TRY(h, hipMemcpyAsync(h->chk_host, h->err, 4, hipMemcpyDeviceToHost, h->stream), "list check");
-        IRBE_TRY(h, hipMemcpyAsync(h->chk_host + 1, h->maxcnt, 8, hipMemcpyDeviceToHost, h->stream), "list check");
+        IRBE_TRY(h, hipMemcpyAsync(h->chk_host + 1, h->maxcnt, 12, hipMemcpyDeviceToHost, h->stream), "list check");
         IRBE_TRY(h, hipEventRecord(h->chk_event, h->stream), "list check");
         h->chk_pending = true;
         h->have_lists = true;
@@ -751,9 +762,9 @@ irbe_status irbe_build_lists(irbe_handle h, const void* pos, uint64_t step)
     IRBE_STAGE(h, IRBE_STAGE_BIN, launch_bin(h, pos), "binning");
     for (int attempt = 0; attempt < 4; ++attempt) {
         IRBE_TRY(h, ensure_shell_rows_32(h), "reallocate the shell rows");
-        IRBE_TRY(h, launch_fill_i32(h->stream, h->maxcnt, 0, 2), "list build");
+        IRBE_TRY(h, launch_fill_i32(h->stream, h->maxcnt, 0, 3), "list build");
         IRBE_STAGE(h, IRBE_STAGE_LISTS, launch_build_lists(h), "list build");
-        int32_t mx[2] = {0, 0};
+        int32_t mx[3] = {0, 0, 0};
         uint32_t err = 0;
         IRBE_TRY(h, hipMemcpyAsync(mx, h->maxcnt, sizeof(mx), hipMemcpyDeviceToHost, h->stream), "read list sizes");
         IRBE_TRY(h, hipMemcpyAsync(&err, h->err, sizeof(err), hipMemcpyDeviceToHost, h->stream), "read error word");
@@ -762,16 +773,17 @@ irbe_status irbe_build_lists(irbe_handle h, const void* pos, uint64_t step)
             IRBE_TRY(h, launch_fill_i32(h->stream, (int32_t*)h->err, 0, 1), "clear error word");
             if (err & ERR_NONFINITE) return fail(h, IRBE_ENONFINITE, "non-finite position");
             // capacity bits of this build: the rows grow below and the lists are built again
-            if (err & ERR_SHELL_CODE) {
-                // a stencil row's candidate range too long for the 16-bit codes:
-                // 32-bit entries from now on, and the lists built again
-                h->shell16_ok = false;
+            if (err & ERR_SHELL_ROW) {
+                // a stencil row's candidate range too long for the masks: 32-bit
+                // entries from now on, and the lists built again
+                h->masks_ok = false;
                 continue;
             }
         }
         if (h->stencil && mx[1] > 65535)
             return fail(h, IRBE_EUNSUPPORTED, "more than 65535 atoms in a shell stencil");
-        if (mx[0] <= h->cap_core && (h->stencil || mx[1] <= h->cap_shell)) {
+        const bool words = grow_mask_rows(h, mx[2]);
+        if (!words && mx[0] <= h->cap_core && (h->stencil || mx[1] <= h->cap_shell)) {
             h->max_core = mx[0];
             h->max_shell = mx[1];
             h->have_lists = true;
@@ -994,18 +1006,22 @@ irbe_status irbe_get_debug(irbe_handle h, int32_t what, void* dst_host, int64_t 
                 rk.resize((size_t)n * h->p_stride);
                 IRBE_TRY(h, d2h(rk.data(), h->ranks, rk.size() * 2), "debug");
             }
-        } else if (!is_core && h->shell16) {
-            // 16-bit entries, decoded here
-            std::vector<uint16_t> r16((size_t)n * stride);
-            std::vector<int32_t> cs((size_t)h->geo.n_cells + 1), grp((size_t)n);
-            IRBE_TRY(h, d2h(r16.data(), h->shell, r16.size() * 2), "debug");
-            IRBE_TRY(h, d2h(cs.data(), h->cell_start, cs.size() * 4), "debug");
-            IRBE_TRY(h, d2h(grp.data(), h->sgroup, grp.size() * 4), "debug");
+        } else if (!is_core && h->masks) {
+            // masks, expanded here
+            const size_t cw = (size_t)h->cap_words;
+            const size_t slots = (size_t)list_block_slots(h->geo, h->stencil, n);
+            std::vector<uint32_t> mk((size_t)n * cw);
+            std::vector<int32_t> base(2 * slots * cw), nw(slots), slot((size_t)n), row;
+            IRBE_TRY(h, d2h(mk.data(), h->shell, mk.size() * 4), "debug");
+            IRBE_TRY(h, d2h(base.data(), h->blk_words, base.size() * 4), "debug");
+            IRBE_TRY(h, d2h(nw.data(), h->blk_nw, slots * 4), "debug");
+            IRBE_TRY(h, d2h(slot.data(), h->slot_of, (size_t)n * 4), "debug");
             rows.assign((size_t)n * stride, 0);
-            for (int64_t k = 0; k < n; ++k)
-                for (int32_t t = 0; t < cnt[k]; ++t)
-                    rows[(size_t)k * stride + t] =
-                        decode_shell_entry(h->lcode, cs, grp[k], r16[(size_t)k * stride + t]);
+            for (int64_t k = 0; k < n; ++k) {
+                const size_t b = (size_t)slot[k];
+                expand_mask_row(&mk[(size_t)k * cw], &base[2 * b * cw], nw[b], cnt[k], row);
+                std::copy(row.begin(), row.end(), rows.begin() + k * (int64_t)stride);
+            }
         } else {
             rows.resize((size_t)n * stride);
             IRBE_TRY(h, d2h(rows.data(), is_core ? h->core : h->shell, rows.size() * 4), "debug");
@@ -1077,7 +1093,7 @@ irbe_status irbe_get_debug(irbe_handle h, int32_t what, void* dst_host, int64_t 
     }
     case IRBE_DBG_SHELL_BITS: {
         if (!h->have_lists) return fail(h, IRBE_ESTATE, "no lists built");
-        const int64_t v = h->shell16 ? 16 : 32;
+        const int64_t v = h->masks ? 16 : 32;
         copy_out(&v, 8, 1);
         return IRBE_OK;
     }
@@ -1127,23 +1143,21 @@ irbe_status irbe_get_debug_rows(irbe_handle h, int32_t what, const int64_t* rows
     std::vector<int64_t> off((size_t)n_rows + 1, 0);
     std::vector<int32_t> idx;
     // the first len entries of sorted atom k's shell row as sorted indices
-    std::vector<int32_t> cs16;  // cell starts of the build, for 16-bit entries
     auto read_shell_row = [&](int32_t k, int64_t len, std::vector<int32_t>& row) -> hipError_t {
         row.resize((size_t)len);
-        if (!h->shell16)
+        if (!h->masks)
             return hipMemcpy(row.data(), h->shell + (int64_t)k * h->cap_shell, (size_t)len * 4, hipMemcpyDeviceToHost);
-        std::vector<uint16_t> r16((size_t)len);
-        int32_t grp = 0;
-        hipError_t e = hipMemcpy(r16.data(), reinterpret_cast<const uint16_t*>(h->shell) + (int64_t)k * h->cap_shell,
-                                 (size_t)len * 2, hipMemcpyDeviceToHost);
-        if (e == hipSuccess) e = hipMemcpy(&grp, h->sgroup + k, 4, hipMemcpyDeviceToHost);
-        if (e == hipSuccess && cs16.empty()) {
-            cs16.resize((size_t)h->geo.n_cells + 1);
-            e = hipMemcpy(cs16.data(), h->cell_start, cs16.size() * 4, hipMemcpyDeviceToHost);
-        }
-        if (e != hipSuccess) return e;
-        for (int64_t t = 0; t < len; ++t) row[(size_t)t] = decode_shell_entry(h->lcode, cs16, grp, r16[(size_t)t]);
-        return hipSuccess;
+        const size_t cw = (size_t)h->cap_words;
+        std::vector<uint32_t> mk(cw);
+        std::vector<int32_t> base(2 * cw);
+        int32_t slot = 0, nw = 0;
+        hipError_t e = hipMemcpy(mk.data(), h->shell + (size_t)k * cw, cw * 4, hipMemcpyDeviceToHost);
+        if (e == hipSuccess) e = hipMemcpy(&slot, h->slot_of + k, 4, hipMemcpyDeviceToHost);
+        if (e == hipSuccess) e = hipMemcpy(&nw, h->blk_nw + slot, 4, hipMemcpyDeviceToHost);
+        if (e == hipSuccess)
+            e = hipMemcpy(base.data(), h->blk_words + 2 * (size_t)slot * cw, 2 * cw * 4, hipMemcpyDeviceToHost);
+        if (e == hipSuccess) expand_mask_row(mk.data(), base.data(), nw, len, row);
+        return e;
     };
     for (int64_t r = 0; r < n_rows; ++r) {
         int32_t k = 0, cnt = 0;

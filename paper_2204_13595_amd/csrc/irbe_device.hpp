@@ -109,6 +109,21 @@ __device__ __forceinline__ double bcast(double v, int t)
     return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
+// Position of the (k + 1)-th set bit of m (which has more than k), by the counts
+// of halves of 16, 8, 4, 2 and 1 bits.
+__device__ __forceinline__ int nth_set_bit(uint32_t m, uint32_t k)
+{
+    int b = 0;
+#pragma unroll
+    for (int s = 16; s >= 1; s >>= 1) {
+        const uint32_t c = __popc(__builtin_amdgcn_ubfe(m, b, s));
+        const bool up = k >= c;
+        k -= up ? c : 0u;
+        b += up ? s : 0;
+    }
+    return b;
+}
+
 // ---------------------------------------------------------------------------
 // Reductions (fixed order: deterministic for a fixed launch shape).
 // ---------------------------------------------------------------------------

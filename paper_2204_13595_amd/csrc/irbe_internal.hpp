@@ -13,22 +13,23 @@
 namespace irbe {
 
 // Error-word bits set by kernels and read back at the next waiting call.
-enum : uint32_t { ERR_NONFINITE = 1u, ERR_CORE_CAP = 2u, ERR_SHELL_CAP = 4u, ERR_SHELL_CODE = 8u };
+enum : uint32_t { ERR_NONFINITE = 1u, ERR_CORE_CAP = 2u, ERR_SHELL_CAP = 4u, ERR_SHELL_ROW = 8u };
 
-// 16-bit shell entries. The list build treats the cells of a cell row in groups
-// of G consecutive cells (the last group of a row may be shorter); for stencil
-// row (dz, dy) a group's candidates are the atoms of the union of its cells'
-// x ranges in that row, at most two index ranges of the sorted atoms (the
-// second after the periodic wrap). An entry stores the row's id
-// (dz - lo) * span + (dy - lo) in its high bits and the member's position in
-// that candidate range in its low pb bits; the member is then
-// a + p for p < na, else b + (p - na), with a, na the first atom and length of
-// the first range and b the first atom of the second.
-struct ListCode {
-    const int32_t* cell_start;  // [n_c^3 + 1] of the build
-    const int32_t* sgroup;      // [N] list-build group of each sorted atom
-    int n_c, lo, span, G, gpr, pb;  // gpr: groups per cell row
+// Shell lists as masks. The list build takes blocks of up to 32 consecutive
+// atoms of one cell row (slot_of: an atom's block); a block's candidates, in
+// canonical order, fill words of 32 in half words of 16 (words[2 (slot * cap + w)
+// + q]: the sorted index of the first candidate of half q of word w, the others
+// follow it; nw[slot] words), and S(i) is
+// one bit per candidate (mask[i * cap + w], zero up to the next multiple of four
+// words): member r is the (r + 1)-th set bit.
+struct ShellMasks {
+    const uint32_t* mask;
+    const int32_t* words;
+    const int32_t* nw;
+    const int32_t* slot_of;
+    int cap;  // words per row, a multiple of 4, at most kMaskMaxWords
 };
+constexpr int kMaskMaxWords = 256;
 
 constexpr int kBlock = 256;          // threads per block of the per-atom kernels
 constexpr int kReduceBlock = 256;    // threads of the deterministic final reductions
@@ -39,7 +40,7 @@ constexpr int kMaxTypesGrad = 4;     // LJ parameter gradients: n_types <= 4
 // kernel with list-drawn batches, and the forward kernel with stencil sampling
 constexpr int kAtomsPerWave = 8;
 constexpr int kAtomsPerWaveList = 4;   // full lists
-constexpr int kAtomsPerWaveSplit = 8;  // split lists (the optimum with 16-bit shell entries; the same with
+constexpr int kAtomsPerWaveSplit = 8;  // split lists (the optimum with compact shell lists; the same with
                                        // 32-bit ones, so that the per-block sums and results do not change)
 constexpr int kAtomsPerWaveStencil = 16;
 // Shell-adjoint transpose: scatter records staged per block in LDS, then
@@ -91,6 +92,43 @@ struct Geometry {
     int64_t n_cells = 0;
 };
 
+// What a list build produces: split core and shell lists, one full list, the
+// core list alone (the shell batch of stencil sampling is drawn from the
+// stencil's cells), or split lists with a skin, where S(i) starts at its own
+// threshold below C(i)'s end (the two lists overlap).
+enum { kListsSplit = 0, kListsFull = 1, kListsCoreOnly = 2, kListsSplitSkin = 3 };
+
+// Arguments of k_list_blocks.
+struct ListBlockArgs {
+    int n_c, lo, span, G, cap_core, cap_shell;
+    uint64_t t_out, t_in, t_lo;      // squared radii (quanta): outer list, C(i), inner end of S(i) with a skin
+    float tu_out, tu_in, tu_lo;      // the same in the units of the test
+    float unit;                      // units per quantum
+    float inv_span;                  // 1 / span
+    float r_in;                      // C(i)'s radius in units, with a margin
+    float tf_hi;                     // t_out with the margin of the row pruning
+    float band_valu;                 // error bound of the vector-unit distances
+    const uint4* spos;
+    const int32_t* cell_start;
+    const uint32_t* bound;
+    const int32_t* blk_start;        // first atom + 1 of every block slot (0: unused)
+    const int2* sxr;
+    const int32_t* sxidx;
+    int32_t *core, *ncore, *shell, *nshell, *maxcnt;
+    uint32_t* err;
+    // shell lists as masks (ShellMasks)
+    uint32_t* mask;
+    int32_t *words, *nw, *slot_of;
+    int cap_words;
+};
+
+// Stencil and segments of the block list build: segments of G cells of a cell
+// row, gpr per row; narrow: the stencil does not wrap the box.
+struct ListBlockShape {
+    int reach, lo, span, G, gpr;
+    bool narrow;
+};
+
 }  // namespace irbe
 
 struct irbe_ctx {
@@ -119,7 +157,7 @@ struct irbe_ctx {
     // shell_bound()
     int32_t max_core = 0, max_shell = 0;
     bool lists_sized = false;         // a waiting build has sized the list rows
-    int32_t* chk_host = nullptr;      // pinned [3]: error word, max core, max shell of the last build
+    int32_t* chk_host = nullptr;      // pinned [4]: error word, max core, max shell, max mask words of the last build
     hipEvent_t chk_event = nullptr;   // recorded after the copy into chk_host
     bool chk_pending = false;         // chk_host awaits a completed copy
     // Upper bound on every atom's shell (or full, or stencil) list length.
@@ -130,7 +168,7 @@ struct irbe_ctx {
 
     // device memory, all owned by the handle
     uint32_t* err = nullptr;          // error word
-    int32_t* maxcnt = nullptr;        // [2] max core / shell count of the last build
+    int32_t* maxcnt = nullptr;        // [3] max core / shell count and mask words of the last build
     uint64_t* ktab = nullptr;         // [2M+1]
     void* q_orig = nullptr;           // real[N]
     int32_t* type_orig = nullptr;     // [N]
@@ -151,6 +189,7 @@ struct irbe_ctx {
     uint32_t* cell_bound = nullptr;   // [n_c + 1] first fixed-point coordinate of each cell row/column
     std::vector<int32_t*> scan_levels;
     std::vector<int64_t> scan_sizes;
+    int32_t* blk_start = nullptr;     // [list_block_slots] first atom + 1 of the blocks of the list build
     int32_t* perm = nullptr;          // [N] sorted -> caller id
     int32_t* rank = nullptr;          // [N] caller id -> sorted
     uint4* spos = nullptr;            // [N] sorted {sx, sy, sz, type}
@@ -163,13 +202,14 @@ struct irbe_ctx {
 
     int32_t* core = nullptr;          // [N * cap_core]
     int32_t* ncore = nullptr;         // [N]
-    int32_t* shell = nullptr;         // [N * cap_shell] 32-bit sorted indices, or (shell16) 16-bit codes in
-                                      //     the first half of the allocation, rows of cap_shell entries
-    bool shell16 = false;             // the current shell lists hold 16-bit codes (ListCode)
-    int32_t shell_bytes = 4;          // bytes per entry of the shell rows' allocation (2: codes)
-    bool shell16_ok = true;           // cleared for good once a build found a row range too long for the codes
-    irbe::ListCode lcode{};           // decoding of the current lists' codes
-    int32_t* sgroup = nullptr;        // [N] list-build group of each sorted atom (16-bit shell entries)
+    int32_t* shell = nullptr;         // [N * cap_shell] sorted indices, or (masks) [N * cap_words] mask words
+    bool masks = false;               // the shell rows are allocated as masks (ShellMasks)
+    bool masks_ok = true;             // cleared for good once a build found a row range too long for them
+    int32_t cap_words = 0;            // words per mask row
+    int32_t* blk_words = nullptr;     // [2 * list_block_slots * cap_words] first candidate of the blocks' half words
+    int32_t* blk_nw = nullptr;        // [list_block_slots] words of the blocks
+    int32_t* slot_of = nullptr;       // [N] block of each sorted atom
+    irbe::ShellMasks shell_masks() const { return {(const uint32_t*)shell, blk_words, blk_nw, slot_of, cap_words}; }
     int32_t* nshell = nullptr;        // [N]
 
     void* fsr = nullptr;              // real[3N] sorted short-range (+ excluded-pair) force
@@ -208,7 +248,7 @@ struct irbe_ctx {
     int32_t* batch_j = nullptr;       // [N * p_stride] the drawn atoms (sorted index) of the current ranks (with
                                       // stencil sampling -1: i or i's molecule), for the adjoint and read-back:
                                       // written by the forward for the backward that follows it, or decoded
-                                      // (stencil ranks, 16-bit shell entries); allocated on first use
+                                      // (stencil ranks, compact shell lists); allocated on first use
     bool batch_j_valid = false;       // batch_j holds the decode of the current ranks
     bool batch_j_fwd = false;         // ... written by a forward (not by a decode for the backward)
     bool keep_batch = false;          // the next forward writes batch_j (the last forward had a backward)
@@ -246,6 +286,14 @@ hipError_t launch_fill_bytes0(hipStream_t s, void* p, size_t bytes);
 hipError_t launch_bin(irbe_ctx* h, const void* pos);
 hipError_t launch_requantize(irbe_ctx* h, const void* pos);
 hipError_t launch_build_lists(irbe_ctx* h);
+// Mean atoms per cell below which the list build takes one lane per atom.
+constexpr double kLaneMaxPerCell = 4.0;
+// True when it does (k_build_lists_lanes); else the blocks below.
+bool lists_by_lanes(const irbe_ctx* h);
+// The block form of the list build (k_list_blocks) and the block slots it takes.
+hipError_t launch_list_blocks(irbe_ctx* h);
+ListBlockShape list_block_shape(const Geometry& geo, bool core_only);
+int64_t list_block_slots(const Geometry& geo, bool core_only, int64_t n);
 hipError_t launch_ksample(irbe_ctx* h, uint64_t step);
 hipError_t launch_rho(irbe_ctx* h, const void* grad, bool with_adjoint);
 hipError_t launch_pair_forces(irbe_ctx* h, uint64_t step, bool ev);
@@ -262,9 +310,9 @@ hipError_t launch_pair_adjoint(irbe_ctx* h, uint64_t step, bool want_q, bool wan
 hipError_t ensure_buckets(irbe_ctx* h, int64_t records);
 // Stencil sampling: allocate the read-back array of the decoded batch, and fill it.
 hipError_t ensure_batch_atoms(irbe_ctx* h);
-// Whether this handle's shell lists can take 16-bit codes (ListCode): split lists
-// built by the tiled kernel over a narrow stencil of at most 64 rows.
-bool shell16_possible(const irbe_ctx* h);
+// Words per mask row that this handle's shell lists take (an estimate with a
+// margin), 0 when they are stored as 32-bit indices.
+int mask_words_wanted(const irbe_ctx* h);
 // Device-memory Floyd bitmaps of at least `words` 32-bit words.
 hipError_t ensure_draw_bits(irbe_ctx* h, size_t words);
 hipError_t launch_stencil_decode(irbe_ctx* h);

@@ -362,40 +362,61 @@ __device__ __forceinline__ int stencil_rows_atom(const StencilRows<ROWS>& T, int
     return o < la ? T.a[lo_k] + o : T.b[lo_k] + (o - la);
 }
 
-// 16-bit shell entries (ListCode): the stencil rows of one list-build group,
-// one row per lane: first atom and length of the row's first index range, and
-// the first atom of its second range minus that length (zeros past the last
-// row, so that any code reads a defined entry).
-__device__ void group_rows_build(int4* T, int grp, const ListCode& lc, int lane)
+// Shell lists as masks: a wavefront keeps one atom's mask row in LDS, with the
+// members before every word and the words' first candidates (those of the
+// atom's block), and finds a member by its rank: the word by binary search over
+// the members before it, the bit by halving the word.
+struct MaskTable {
+    uint32_t pre[kMaskMaxWords];   // members before word w
+    uint32_t word[kMaskMaxWords];
+    int32_t base[2 * kMaskMaxWords];  // sorted index of the first candidate of half q of word w at 2 w + q
+};
+
+// This lane's four words of atom a's row (nw words).
+__device__ __forceinline__ uint4 mask_load(const ShellMasks& sm, int64_t a, int nw, int lane)
 {
-    T[lane] = make_int4(0, 0, 0, 0);
-    if (lane < lc.span * lc.span) {
-        const int rowid = grp / lc.gpr;
-        const int cz = rowid / lc.n_c, cy = rowid - cz * lc.n_c;
-        const int x0 = (grp - rowid * lc.gpr) * lc.G;
-        const int span_u = min(lc.G, lc.n_c - x0) - 1 + lc.span;  // cells of the union x range
-        const int xu0 = wrap_cell(x0 + lc.lo, lc.n_c);
-        const int lenA = min(span_u, lc.n_c - xu0);
-        const int dz = lane / lc.span;
-        const int z = wrap_cell(cz + dz + lc.lo, lc.n_c);
-        const int y = wrap_cell(cy + (lane - dz * lc.span) + lc.lo, lc.n_c);
-        const int row = (z * lc.n_c + y) * lc.n_c;
-        const int a = lc.cell_start[row + xu0];
-        const int na = lc.cell_start[row + xu0 + lenA] - a;
-        T[lane] = make_int4(a, na, lc.cell_start[row] - na, 0);
-    }
-    // (the wavefront's own table: its later reads follow these writes in order)
+    return 4 * lane < nw ? *(const uint4*)(sm.mask + a * (int64_t)sm.cap + 4 * lane) : make_uint4(0u, 0u, 0u, 0u);
+}
+
+// The first candidates of the words of block `slot`.
+__device__ __forceinline__ void mask_bases(MaskTable& T, const ShellMasks& sm, int slot, int nw, int lane)
+{
+    const int32_t* const b = sm.words + 2 * (int64_t)slot * sm.cap;
+#pragma unroll
+    for (int q = 0; q < 2 * kMaskMaxWords; q += 256)
+        if (q + 4 * lane < 2 * nw) *(int4*)&T.base[q + 4 * lane] = *(const int4*)(b + q + 4 * lane);
     __builtin_amdgcn_wave_barrier();
 }
 
-// Atom (sorted index) of shell entry e through the rows of its group in T,
-// clamped to the last atom: codes of a build that reported a too long row range
-// (forces from such lists are wrong, as the error says) still read in bounds.
-__device__ __forceinline__ int group_rows_atom(const int4* T, int pb, int e, int last)
+// The lanes' words and the members before each into the table (the wavefront's
+// own: its later reads follow these writes in order).
+__device__ __forceinline__ void mask_rows(MaskTable& T, uint4 m, int lane)
 {
-    const int4 r = T[e >> pb];
-    const int p = e & ((1 << pb) - 1);
-    return (int)min((uint32_t)(p < r.y ? r.x + p : r.z + p), (uint32_t)last);
+    const uint32_t c0 = __popc(m.x), c1 = c0 + __popc(m.y), c2 = c1 + __popc(m.z), c3 = c2 + __popc(m.w);
+    int x = (int)c3;
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);
+    const uint32_t p = (uint32_t)x - c3;
+    *(uint4*)&T.pre[4 * lane] = make_uint4(p, p + c0, p + c1, p + c2);
+    *(uint4*)&T.word[4 * lane] = m;
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Sorted index of member r (below the list's length) of a row of nw words
+// (clamped to the last atom: the rows of a build that reported too few words
+// per row still read in bounds).
+__device__ __forceinline__ int mask_member(const MaskTable& T, int nw, int r, int last)
+{
+    int w = 0;
+    if (nw > 128 && T.pre[128] <= (uint32_t)r) w = 128;
+#pragma unroll
+    for (int s = 64; s >= 1; s >>= 1) w += T.pre[w + s] <= (uint32_t)r ? s : 0;
+    const int b = nth_set_bit(T.word[w], (uint32_t)r - T.pre[w]);
+    return (int)min((uint32_t)(T.base[2 * w + (b >> 4)] + (b & 15)), (uint32_t)last);
 }
 
 // A drawn atom j of atom a (sorted indices) counts as a shell pair: not a
@@ -451,55 +472,35 @@ __global__ __launch_bounds__(kDecodeBlock) void k_stencil_decode(int64_t n, int 
     }
 }
 
-// 16-bit shell entries: the drawn atoms of the current batch (the list members
+// Shell lists as masks: the drawn atoms of the current batch (the list members
 // at the drawn ranks) into batch_j, for the adjoint when no forward at this
-// step wrote them. One wavefront per apw consecutive atoms, one group's rows
-// per wavefront in LDS.
-__global__ __launch_bounds__(kDecodeBlock) void k_list_decode(int64_t n, int apw, ListCode lc,
-                                                              const uint16_t* __restrict__ shell16, int cap_shell,
+// step wrote them. One wavefront per apw consecutive atoms.
+__global__ __launch_bounds__(kDecodeBlock) void k_list_decode(int64_t n, int apw, ShellMasks sm,
                                                               const int32_t* __restrict__ nshell, int p_shell,
                                                               int p_stride, const uint16_t* __restrict__ ranks,
                                                               int32_t* __restrict__ batch_j)
 {
-    __shared__ int4 gt[kDecodeBlock / 64][64];
+    __shared__ __align__(16) MaskTable tab[kDecodeBlock / 64];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int64_t a0 = ((int64_t)blockIdx.x * (kDecodeBlock / 64) + wave) * apw;
     const int64_t a1 = min(n, a0 + apw);
-    // an atom's first two slots: their ranks (or list positions), -1 past the batch
-    auto slots = [&](int64_t a, int& q0, int& q1) {
-        const int m = nshell[a];
-        const bool sample = m > p_shell;
-        const int cnt = sample ? p_shell : m;
-        const uint16_t* rrow = ranks + a * (int64_t)p_stride;
-        q0 = lane < cnt ? (sample ? (int)rrow[lane] : lane) : -1;
-        q1 = lane + 64 < cnt ? (sample ? (int)rrow[lane + 64] : lane + 64) : -1;
-    };
-    int cur = -1;
-    int n_q0 = -1, n_q1 = -1;
-    if (a0 < a1) slots(a0, n_q0, n_q1);
+    MaskTable& T = tab[wave];
+    int cur = -1, nw = 0;
     for (int64_t a = a0; a < a1; ++a) {
-        const int q0 = n_q0, q1 = n_q1;
-        const uint16_t* srow = shell16 + a * (int64_t)cap_shell;
-        // this atom's entries, then the next atom's ranks (in flight while these decode)
-        const int e0 = q0 >= 0 ? (int)srow[q0] : 0;
-        const int e1 = q1 >= 0 ? (int)srow[q1] : 0;
-        if (a + 1 < a1) slots(a + 1, n_q0, n_q1);
-        const int grp = lc.sgroup[a];
-        if (grp != cur) {
-            group_rows_build(gt[wave], grp, lc, lane);
-            cur = grp;
+        const int slot = sm.slot_of[a];
+        if (slot != cur) {
+            nw = sm.nw[slot];
+            mask_bases(T, sm, slot, nw, lane);
+            cur = slot;
         }
-        int32_t* out = batch_j + a * (int64_t)p_stride;
-        if (q0 >= 0) out[lane] = group_rows_atom(gt[wave], lc.pb, e0, (int)n - 1);
-        if (q1 >= 0) out[lane + 64] = group_rows_atom(gt[wave], lc.pb, e1, (int)n - 1);
-        // the rest (batches of more than 128)
         const int m = nshell[a];
         const bool sample = m > p_shell;
         const int cnt = sample ? p_shell : m;
         const uint16_t* rrow = ranks + a * (int64_t)p_stride;
-        for (int c = lane + 128; c < cnt; c += 64)
-            out[c] = group_rows_atom(gt[wave], lc.pb, srow[sample ? (int)rrow[c] : c], (int)n - 1);
+        mask_rows(T, mask_load(sm, a, nw, lane), lane);
+        for (int c = lane; c < cnt; c += 64)
+            batch_j[a * (int64_t)p_stride + c] = mask_member(T, nw, sample ? (int)rrow[c] : c, (int)n - 1);
     }
 }
 
@@ -566,19 +567,19 @@ __device__ __forceinline__ void add_excl(PairSum<real>& px, uint4 si, real qi, u
 }
 
 template <typename real, bool FULL, bool EV, bool STENCIL, bool SKIN, bool ENC>
-__global__ __launch_bounds__(kCoopBlock) void k_pair_coop(
+__global__ __launch_bounds__(kCoopBlock, ENC && !EV && sizeof(real) == 4 ? 5 : 1) void k_pair_coop(
     int64_t n, int apw, PairParams<real> pp, const uint4* __restrict__ spos, const real* __restrict__ sqr,
     const uint4* __restrict__ spq, const int2* __restrict__ sxr, const int32_t* __restrict__ sxidx,
     const int32_t* __restrict__ core, const int32_t* __restrict__ ncore, int cap_core,
     const int32_t* __restrict__ shell, const int32_t* __restrict__ nshell, int cap_shell,
     const LJ<real>* __restrict__ lj_g, int n_types, int p_shell, int p_stride, const uint16_t* __restrict__ ranks,
     StencilArgs sa, uint64_t t_core, uint64_t t_shell, real* __restrict__ fsr, double* __restrict__ part,
-    int32_t* __restrict__ bj_out, ListCode lc)
+    int32_t* __restrict__ bj_out, ShellMasks sm)
 {
     __shared__ LJ<real> lj[256];
     __shared__ double red[kPairPartials * (kCoopBlock / 64)];
     __shared__ StencilRows<STENCIL ? kDecodeRows : 1> srows[kCoopBlock / 64];  // stencil rows of one cell per wave
-    __shared__ int4 gtab[ENC ? kCoopBlock / 64 : 1][ENC ? 64 : 1];  // 16-bit entries: one group's rows per wave
+    __shared__ __align__(16) unsigned char mtab[ENC ? (kCoopBlock / 64) * sizeof(MaskTable) : 16];  // masks: one atom's row per wave
     const int nt2 = n_types * n_types;
     for (int t = threadIdx.x; t < nt2; t += kCoopBlock) lj[t] = lj_g[t];
     __syncthreads();
@@ -602,19 +603,22 @@ __global__ __launch_bounds__(kCoopBlock) void k_pair_coop(
     const int h_ns = nshell[ah];
     const int2 h_x = sxr[ah];
     const int h_mol = STENCIL ? sa.smol[ah] : 0;
-    const int h_grp = ENC ? lc.sgroup[ah] : 0;
+    const int h_slot = ENC ? sm.slot_of[ah] : 0;
+    const int h_nw = ENC ? sm.nw[h_slot] : 0;
+    MaskTable& T = reinterpret_cast<MaskTable*>(mtab)[ENC ? wave : 0];
     // shell weight N_S / p~ (1 when every member is taken), one division per lane
     const real h_w = (!FULL && h_ns > p_shell) ? (real)((double)h_ns / (double)p_shell) : (real)1;
     const int nrows = sa.span * sa.span;
     int tcell = -1;  // the cell whose stencil rows sit in srows[wave]
-    int tgrp = -1;   // the group whose rows sit in gtab[wave]
+    int tslot = -1;  // the block whose words' bases sit in T
     // first-level indices of one atom's first pass: the lane's first core entry,
     // its two batch ranks (or shell positions) and its first excluded partner
     // Without energies the excluded partners follow the core entries in one slot
     // (entries nc .. nc + nx - 1 of the combined list); with energies they keep
     // their own slot.
     constexpr bool kFold = !EV;
-    auto first_level = [&](int64_t a, int t, int& jc, int& r0, int& r1, int& jx) {
+    auto first_level = [&](int64_t a, int t, int& jc, int& r0, int& r1, int& jx, uint4& mk) {
+        if (ENC) mk = mask_load(sm, a, bcast(h_nw, t), lane);
         const int nc = bcast(h_nc, t);
         const int ns = bcast(h_ns, t);
         const int2 xr = make_int2(bcast(h_x.x, t), bcast(h_x.y, t));
@@ -640,16 +644,26 @@ __global__ __launch_bounds__(kCoopBlock) void k_pair_coop(
         }
         jx = (!kFold && lane < xr.y) ? sxidx[xr.x + lane] : -1;
     };
-    // second level of an atom's first pass: the shell entries at its two ranks as
-    // stored (16-bit codes or indices; the atoms themselves with stencil sampling)
-    auto second_level = [&](int64_t a, int r0, int r1, int& e0, int& e1) {
+    // atom a's mask row (its lanes' words mk) into the wavefront's table
+    auto mask_table = [&](int t, uint4 mk) {
+        const int slot = bcast(h_slot, t);
+        if (slot != tslot) {
+            mask_bases(T, sm, slot, bcast(h_nw, t), lane);
+            tslot = slot;
+        }
+        mask_rows(T, mk, lane);
+    };
+    // second level of an atom's first pass: the shell members at its two ranks (the
+    // atoms themselves with stencil sampling)
+    auto second_level = [&](int64_t a, int t, int r0, int r1, uint4 mk, int& e0, int& e1) {
         if (STENCIL) {
             e0 = r0;
             e1 = r1;
         } else if (ENC) {
-            const uint16_t* s16 = reinterpret_cast<const uint16_t*>(shell) + a * (int64_t)cap_shell;
-            e0 = r0 >= 0 ? (int)s16[r0] : -1;
-            e1 = r1 >= 0 ? (int)s16[r1] : -1;
+            mask_table(t, mk);
+            const int nw = bcast(h_nw, t);
+            e0 = r0 >= 0 ? mask_member(T, nw, r0, (int)n - 1) : -1;
+            e1 = r1 >= 0 ? mask_member(T, nw, r1, (int)n - 1) : -1;
         } else {
             const int32_t* s1 = shell + a * (int64_t)cap_shell;
             e0 = r0 >= 0 ? s1[r0] : -1;
@@ -662,22 +676,16 @@ __global__ __launch_bounds__(kCoopBlock) void k_pair_coop(
     // them: the vector memory counter is in order)
     int n_jc = -1, n_e0 = -1, n_e1 = -1, n_jx = -1;  // atom a: first level and shell entries
     int m_jc = -1, m_r0 = -1, m_r1 = -1, m_jx = -1;  // atom a + 1: first level
+    uint4 m_mk = make_uint4(0u, 0u, 0u, 0u);         // ... and its mask words
     if (a0 < a1) {
         int r0, r1;
-        first_level(a0, 0, n_jc, r0, r1, n_jx);
-        second_level(a0, r0, r1, n_e0, n_e1);
-        if (a0 + 1 < a1) first_level(a0 + 1, 1, m_jc, m_r0, m_r1, m_jx);
+        first_level(a0, 0, n_jc, r0, r1, n_jx, m_mk);
+        second_level(a0, 0, r0, r1, m_mk, n_e0, n_e1);
+        if (a0 + 1 < a1) first_level(a0 + 1, 1, m_jc, m_r0, m_r1, m_jx, m_mk);
     }
     for (int64_t a = a0; a < a1; ++a) {
         const int t = (int)(a - a0);
         const int jc = n_jc, e0 = n_e0, e1 = n_e1, jx = n_jx;
-        if (ENC) {
-            const int grp = bcast(h_grp, t);
-            if (grp != tgrp) {
-                group_rows_build(gtab[wave], grp, lc, lane);
-                tgrp = grp;
-            }
-        }
         const uint4 si = make_uint4(bcast(h_s.x, t), bcast(h_s.y, t), bcast(h_s.z, t),
                                     bcast(h_s.w, t));
         const real qi = bcast(h_q, t) * pp.ke;
@@ -689,18 +697,14 @@ __global__ __launch_bounds__(kCoopBlock) void k_pair_coop(
         const int2 xr = make_int2(bcast(h_x.x, t), bcast(h_x.y, t));
         const int32_t* crow = core + a * (int64_t)cap_core;
         const int32_t* srow = shell + a * (int64_t)cap_shell;
-        const uint16_t* srow16 = reinterpret_cast<const uint16_t*>(shell) + a * (int64_t)cap_shell;
-        // shell member at position q of the atom's list
-        auto member = [&](int q) -> int {
-            return ENC ? group_rows_atom(gtab[wave], lc.pb, srow16[q], (int)n - 1) : srow[q];
-        };
+        // shell member at position q of the atom's list (masks: the atom's row in T)
+        auto member = [&](int q) -> int { return ENC ? mask_member(T, bcast(h_nw, t), q, (int)n - 1) : srow[q]; };
         const uint16_t* rrow = ranks + a * (int64_t)p_stride;
         const bool sample = !FULL && ns > p_shell;
         const int cnt = sample ? p_shell : ns;
         const real w = bcast(h_w, t);
         PairSum<real> pc, ps, px;
-        const int js0 = ENC ? (e0 >= 0 ? group_rows_atom(gtab[wave], lc.pb, e0, (int)n - 1) : -1) : e0;
-        const int js1 = ENC ? (e1 >= 0 ? group_rows_atom(gtab[wave], lc.pb, e1, (int)n - 1) : -1) : e1;
+        const int js0 = e0, js1 = e1;
         const int mi = STENCIL ? bcast(h_mol, t) : 0;
         const int mj0 = STENCIL ? sa.smol[max(js0, 0)] : 0;
         const int mj1 = STENCIL ? sa.smol[max(js1, 0)] : 0;
@@ -727,8 +731,8 @@ __global__ __launch_bounds__(kCoopBlock) void k_pair_coop(
         if (a + 1 < a1) {
             n_jc = m_jc;
             n_jx = m_jx;
-            second_level(a + 1, m_r0, m_r1, n_e0, n_e1);
-            if (a + 2 < a1) first_level(a + 2, t + 2, m_jc, m_r0, m_r1, m_jx);
+            second_level(a + 1, t + 1, m_r0, m_r1, m_mk, n_e0, n_e1);
+            if (a + 2 < a1) first_level(a + 2, t + 2, m_jc, m_r0, m_r1, m_jx, m_mk);
         }
         // skin: a core entry counts inside r_core, a list shell entry inside the annulus
         // (the whole ball in full-list mode), at these positions
@@ -780,6 +784,8 @@ __global__ __launch_bounds__(kCoopBlock) void k_pair_coop(
                 tcell = cell;
             }
         }
+        // (the table holds the next atom's row by now)
+        if (ENC && cnt > 128) mask_table(t, mask_load(sm, a, bcast(h_nw, t), lane));
         for (int c = lane + 128; c < cnt; c += 64) {
             if (STENCIL) {
                 const int j = stencil_rows_atom(srows[wave], nrows, sample ? (int)rrow[c] : c);
@@ -1006,18 +1012,17 @@ hipError_t launch_stencil_decode(irbe_ctx* h)
     return hipGetLastError();
 }
 
-// 16-bit shell entries: the drawn atoms of the current ranks into h->batch_j.
+// Shell lists as masks: the drawn atoms of the current ranks into h->batch_j.
 static hipError_t launch_list_decode(irbe_ctx* h)
 {
-    if (!h->shell16) return hipErrorInvalidValue;
+    if (!h->masks) return hipErrorInvalidValue;
     const int64_t n = h->cfg.n_atoms;
     const hipError_t e = ensure_batch_atoms(h);
     if (e != hipSuccess) return e;
     const int apw = 16;
     const int64_t waves = blocks_for(n, apw);
     k_list_decode<<<(unsigned)blocks_for(waves, kDecodeBlock / 64), kDecodeBlock, 0, h->stream>>>(
-        n, apw, h->lcode, reinterpret_cast<const uint16_t*>(h->shell), h->cap_shell, h->nshell, h->cfg.p_shell,
-        h->p_stride, h->ranks, h->batch_j);
+        n, apw, h->shell_masks(), h->nshell, h->cfg.p_shell, h->p_stride, h->ranks, h->batch_j);
     return hipGetLastError();
 }
 
@@ -1101,7 +1106,7 @@ static hipError_t launch_coop_t(irbe_ctx* h, uint64_t step)
     k_pair_coop<real, FULL, EV, STENCIL, SKIN, ENC><<<nb, kCoopBlock, 0, h->stream>>>(
         n, apw, pp, h->spos, (const real*)h->sq_r, h->spq, h->sxr, h->sxidx, h->core, h->ncore, h->cap_core,
         h->shell, h->nshell, h->cap_shell, (const LJ<real>*)h->lj, h->cfg.n_types, h->cfg.p_shell, h->p_stride,
-        h->ranks, stencil_args(h), h->geo.t_core, h->geo.t_shell, (real*)h->fsr, h->pair_part, bj_out, h->lcode);
+        h->ranks, stencil_args(h), h->geo.t_core, h->geo.t_shell, (real*)h->fsr, h->pair_part, bj_out, h->shell_masks());
     h->pair_nb = nb;
     if (bj_out) h->batch_j_valid = h->batch_j_fwd = true;
     return hipGetLastError();
@@ -1141,7 +1146,7 @@ static hipError_t launch_coop_s(irbe_ctx* h, uint64_t step, bool ev)
     if (h->stencil)
         return ev ? launch_coop_t<real, false, true, true, SKIN>(h, step)
                   : launch_coop_t<real, false, false, true, SKIN>(h, step);
-    if (h->shell16)
+    if (h->masks)
         return ev ? launch_coop_t<real, false, true, false, SKIN, true>(h, step)
                   : launch_coop_t<real, false, false, false, SKIN, true>(h, step);
     return ev ? launch_coop_t<real, false, true, false, SKIN>(h, step)
@@ -1150,13 +1155,13 @@ static hipError_t launch_coop_s(irbe_ctx* h, uint64_t step, bool ev)
 
 // Split lists whose longest core list plus batch stays within this many entries
 // take the thread-per-atom kernel (32-bit shell entries only: the cooperative
-// kernel decodes the 16-bit ones).
+// kernel reads the masks).
 constexpr int kSparsePairs = 32;
 
 template <typename real>
 static hipError_t launch_coop_r(irbe_ctx* h, uint64_t step, bool ev)
 {
-    if (!h->full_list && !h->stencil && !h->shell16 &&
+    if (!h->full_list && !h->stencil && !h->masks &&
         h->max_core + std::min(h->max_shell, h->cfg.p_shell) <= kSparsePairs)
         return ev ? launch_thread_t<real, true>(h, step) : launch_thread_t<real, false>(h, step);
     return h->geo.skin ? launch_coop_s<real, true>(h, step, ev) : launch_coop_s<real, false>(h, step, ev);
@@ -1877,12 +1882,12 @@ static hipError_t launch_adj_r(irbe_ctx* h, uint64_t step, bool want_lj, int apw
         return e;
     }
     // the batch atoms the forward wrote, when they are those of this step's ranks
-    // (launch_draw keeps them unless it draws again); with 16-bit shell entries
+    // (launch_draw keeps them unless it draws again); with shell lists as masks
     // the atoms at the ranks decoded once otherwise
     hipError_t e = launch_draw(h, step);
     if (e != hipSuccess) return e;
     const bool from_fwd = h->batch_j_valid && h->batch_j_fwd;
-    if (h->shell16 && !h->batch_j_valid) {
+    if (h->masks && !h->batch_j_valid) {
         e = launch_list_decode(h);
         if (e != hipSuccess) return e;
         h->batch_j_valid = true;
