@@ -811,7 +811,7 @@ irbe_status irbe_compute_forces(irbe_handle h, const void* pos, uint64_t step, v
     IRBE_STAGE(h, IRBE_STAGE_KSAMPLE, launch_ksample(h, step), "k sampling");
     IRBE_STAGE(h, IRBE_STAGE_RHO, launch_rho(h, nullptr, false), "structure factor");
     IRBE_STAGE(h, IRBE_STAGE_PAIR, launch_pair_forces(h, step, ev), "pair forces");
-    IRBE_STAGE(h, IRBE_STAGE_PAIR_REDUCE, launch_pair_reduce(h), "pair reduction");
+    IRBE_STAGE(h, IRBE_STAGE_PAIR_REDUCE, launch_pair_reduce(h, ev), "pair reduction");
     IRBE_STAGE(h, IRBE_STAGE_KSPACE, launch_kspace_forces(h, force), "k-space forces");
     if (ev) IRBE_STAGE(h, IRBE_STAGE_ENERGY, launch_energy_finalize(h, energy_virial), "energy");
     h->last_force_step = step;
@@ -905,7 +905,7 @@ irbe_status irbe_compute_forces_noalloc(irbe_handle h, const void* pos, uint64_t
     IRBE_TRY(h, launch_ksample(h, step), "k sampling");
     IRBE_TRY(h, launch_rho(h, nullptr, false), "structure factor");
     IRBE_TRY(h, launch_pair_forces(h, step, ev), "pair forces");
-    IRBE_TRY(h, launch_pair_reduce(h), "pair reduction");
+    IRBE_TRY(h, launch_pair_reduce(h, ev), "pair reduction");
     IRBE_TRY(h, launch_kspace_forces(h, force), "k-space forces");
     if (ev) IRBE_TRY(h, launch_energy_finalize(h, energy_virial), "energy");
     return IRBE_OK;

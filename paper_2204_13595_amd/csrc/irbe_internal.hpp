@@ -75,7 +75,7 @@ struct KAdj {
 // energy is lowered by esh there (the shifted-truncated form).
 template <typename real>
 struct LJ {
-    real a12, b6, c12, c6, rc2, esh;
+    real a12, b6, rc2, esh, c12, c6;
 };
 
 struct Geometry {
@@ -300,7 +300,7 @@ hipError_t launch_pair_forces(irbe_ctx* h, uint64_t step, bool ev);
 // True when the shell batch draw of the current lists keeps its Floyd bitmaps in
 // LDS (lists of at most 16,384 entries); false when it needs device memory.
 bool draw_bitmaps_in_lds(const irbe_ctx* h);
-hipError_t launch_pair_reduce(irbe_ctx* h);
+hipError_t launch_pair_reduce(irbe_ctx* h, bool ev);
 hipError_t launch_kspace_forces(irbe_ctx* h, void* force);
 hipError_t launch_energy_finalize(irbe_ctx* h, double* ev);
 hipError_t launch_sum_q2(irbe_ctx* h);

@@ -26,10 +26,28 @@ namespace irbe {
 template <typename real>
 struct PairParams {
     real quantum;   // L / 2^32
+    real q2;        // quantum^2
     real beta;
+    real kbeta;     // 0.45 beta
+    real gexp;      // -beta^2 log2(e)
     real cgauss;    // 2 beta / sqrt(pi)
     real ke;
 };
+
+template <typename real>
+static PairParams<real> pair_params(const irbe_ctx* h)
+{
+    PairParams<real> pp;
+    const double beta = h->cfg.ewald_beta;
+    pp.quantum = (real)h->geo.quantum;
+    pp.q2 = (real)(h->geo.quantum * h->geo.quantum);
+    pp.beta = (real)beta;
+    pp.kbeta = (real)(0.45 * beta);
+    pp.gexp = (real)(-beta * beta * 1.4426950408889634);
+    pp.cgauss = (real)(2.0 * beta / 1.7724538509055160273);
+    pp.ke = (real)h->cfg.coulomb_k;
+    return pp;
+}
 
 // Position (type in .w) and charge of sorted atom j. FP32 evaluations read one
 // 16-byte record: the fixed-point coordinates and, in the fourth word, the
@@ -71,12 +89,68 @@ __device__ __forceinline__ bool in_annulus(uint4 a, uint4 b, uint64_t t_lo, uint
     return d2 > t_lo && d2 <= t_hi;
 }
 
+// The pair terms come in two forms. Full lists and lists kept with a skin (forces
+// only) and the gradients take the fused one: separations in quanta scaled once
+// per atom, erfc through exp(x^2) erfc(x), so that one exponential serves both
+// terms of Eq. (2.10) (53 issue slots of a pair against 65, errors no larger).
+// Lists rebuilt every step, and every energy, keep the plain form: the MD state
+// integrated from those forces, and the FP64 energies, virials and LJ gradients
+// summed from the FP32 terms, resolve a change of their last bits, and runs are
+// to be reproduced bit for bit.
+
+// Separation in quanta (minimum image).
+template <typename real>
+__device__ __forceinline__ void separation_q(uint4 a, uint4 b, real& dx, real& dy, real& dz)
+{
+    dx = (real)(int32_t)(b.x - a.x);
+    dy = (real)(int32_t)(b.y - a.y);
+    dz = (real)(int32_t)(b.z - a.z);
+}
+
 template <typename real>
 __device__ __forceinline__ void separation(uint4 a, uint4 b, real quantum, real& dx, real& dy, real& dz)
 {
     dx = (real)(int32_t)(b.x - a.x) * quantum;
     dy = (real)(int32_t)(b.y - a.y) * quantum;
     dz = (real)(int32_t)(b.z - a.z) * quantum;
+}
+
+// The radial parts of a pair: 1/r, 1/r^2, exp(-(beta r)^2) and
+// g = erfc(beta r)/r + cgauss exp(-(beta r)^2) (and erfc(beta r) for energies).
+template <typename real>
+struct Radial {
+    real rinv, rinv2, ex, ec, g;
+};
+
+template <typename real>
+__device__ __forceinline__ Radial<real> radial(real r2, const PairParams<real>& pp)
+{
+    using M = Math<real>;
+    Radial<real> o;
+    o.rinv = M::rsqrt_(r2);
+    const real r = r2 * o.rinv;
+    const real br = pp.beta * r;
+    o.ex = M::gauss_(br, pp.gexp * r2);
+    o.rinv2 = o.rinv * o.rinv;
+    if constexpr (std::is_same<real, float>::value) {
+        const float e1 = M::erfcx_(pp.kbeta, r);
+        o.ec = o.ex * e1;
+        o.g = o.ex * fmaf(e1, o.rinv, pp.cgauss);
+    } else {
+        o.ec = erfc(br);
+        o.g = o.ec * o.rinv + pp.cgauss * o.ex;
+    }
+    return o;
+}
+
+// phi of f_ij = phi r_ij (Eq. (2.10)), fused form.
+template <typename real>
+__device__ __forceinline__ real pair_phi_fused(real r2, real qq, const LJ<real>& lj, const PairParams<real>& pp)
+{
+    const Radial<real> o = radial(r2, pp);
+    const real r6 = o.rinv2 * o.rinv2 * o.rinv2;
+    const real ljf = r2 < lj.rc2 ? r6 * (lj.a12 * r6 - lj.b6) : (real)0;
+    return -o.rinv2 * (qq * o.g + ljf);
 }
 
 // phi of f_ij = phi r_ij (Eq. (2.10)) and, when EV, the pair energies.
@@ -102,22 +176,8 @@ __device__ __forceinline__ real pair_phi(real r2, real qq, const LJ<real>& lj, c
     return phi;
 }
 
-// psi of the excluded-pair correction f = psi r_ij and its energy.
-template <typename real, bool EV>
-__device__ __forceinline__ real excl_psi(real r2, real qq, const PairParams<real>& pp, real& ux)
-{
-    using M = Math<real>;
-    const real rinv = M::rsqrt_(r2);
-    const real r = r2 * rinv;
-    const real br = pp.beta * r;
-    const real ex = M::exp_(-br * br);
-    const real ef = M::erf_(br);
-    const real rinv2 = rinv * rinv;
-    if (EV) ux = -qq * ef * rinv;
-    return -qq * rinv2 * (pp.cgauss * ex - ef * rinv);
-}
-
-// Force, energy and virial sums of one list (core or shell batch).
+// Force, energy and virial sums of one list (core or shell batch). Fused form:
+// forces in quanta.
 template <typename real>
 struct PairSum {
     real fx = 0, fy = 0, fz = 0;
@@ -125,23 +185,32 @@ struct PairSum {
     real v[6] = {0, 0, 0, 0, 0, 0};
 };
 
-template <typename real, bool EV>
+template <typename real, bool EV, bool FUSED>
 __device__ __forceinline__ void add_pair(PairSum<real>& a, uint4 si, real qi, uint4 sj, real qj, const LJ<real>& lje,
                                          const PairParams<real>& pp)
 {
     real dx, dy, dz;
-    separation(si, sj, pp.quantum, dx, dy, dz);
-    const real r2 = dx * dx + dy * dy + dz * dz;
-    real uc, ul;
-    const real phi = pair_phi<real, EV>(r2, qi * qj, lje, pp, uc, ul);
-    a.fx += phi * dx;
-    a.fy += phi * dy;
-    a.fz += phi * dz;
-    if (EV) {
-        a.uc += uc;
-        a.ul += ul;
-        a.v[0] += phi * dx * dx; a.v[1] += phi * dy * dy; a.v[2] += phi * dz * dz;
-        a.v[3] += phi * dx * dy; a.v[4] += phi * dx * dz; a.v[5] += phi * dy * dz;
+    if constexpr (FUSED) {
+        separation_q(si, sj, dx, dy, dz);
+        const real r2 = (dx * dx + dy * dy + dz * dz) * pp.q2;
+        const real phi = pair_phi_fused<real>(r2, qi * qj, lje, pp);
+        a.fx += phi * dx;
+        a.fy += phi * dy;
+        a.fz += phi * dz;
+    } else {
+        separation(si, sj, pp.quantum, dx, dy, dz);
+        const real r2 = dx * dx + dy * dy + dz * dz;
+        real uc, ul;
+        const real phi = pair_phi<real, EV>(r2, qi * qj, lje, pp, uc, ul);
+        a.fx += phi * dx;
+        a.fy += phi * dy;
+        a.fz += phi * dz;
+        if (EV) {
+            a.uc += uc;
+            a.ul += ul;
+            a.v[0] += phi * dx * dx; a.v[1] += phi * dy * dy; a.v[2] += phi * dz * dz;
+            a.v[3] += phi * dx * dy; a.v[4] += phi * dx * dz; a.v[5] += phi * dy * dz;
+        }
     }
 }
 
@@ -504,23 +573,57 @@ __global__ __launch_bounds__(kDecodeBlock) void k_list_decode(int64_t n, int apw
     }
 }
 
-template <typename real>
-__device__ __forceinline__ real wave_sum_r(real v)
-{
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
-}
-
 constexpr int kCoopBlock = 256;
 
 // A core pair (ex = false, accumulated into pc) or an excluded pair (ex = true,
 // into px) with one code path: the excluded-pair correction -erf(br)/r equals
 // the real-space term erfc(br)/r minus the bare 1/r, so its force factor is the
-// Coulomb part of phi plus qq / r^3, without LJ. Forces only.
-template <typename real>
+// Coulomb part of phi plus qq / r^3, without LJ. Forces only. (Fused form: both
+// into pc.)
+template <typename real, bool FUSED>
 __device__ __forceinline__ void add_pair_or_excl(PairSum<real>& pc, PairSum<real>& px, uint4 si, real qi, uint4 sj,
                                                  real qj, const LJ<real>& lj, const PairParams<real>& pp, bool ex)
+{
+    real dx, dy, dz;
+    const real qq = qi * qj;
+    if constexpr (FUSED) {
+        separation_q(si, sj, dx, dy, dz);
+        const real r2 = (dx * dx + dy * dy + dz * dz) * pp.q2;
+        const Radial<real> o = radial(r2, pp);
+        const real r6 = o.rinv2 * o.rinv2 * o.rinv2;
+        const real ljf = r2 < lj.rc2 ? r6 * (lj.a12 * r6 - lj.b6) : (real)0;
+        const real phi = -o.rinv2 * (qq * o.g + (ex ? -qq * o.rinv : ljf));
+        pc.fx += phi * dx;
+        pc.fy += phi * dy;
+        pc.fz += phi * dz;
+    } else {
+        using M = Math<real>;
+        separation(si, sj, pp.quantum, dx, dy, dz);
+        const real r2 = dx * dx + dy * dy + dz * dz;
+        const real rinv = M::rsqrt_(r2);
+        const real r = r2 * rinv;
+        const real br = pp.beta * r;
+        const real e = M::exp_(-br * br);
+        const real ec = M::erfc_ex(br, e);
+        const real rinv2 = rinv * rinv;
+        const real r6 = rinv2 * rinv2 * rinv2;
+        const real coul = -qq * rinv2 * (ec * rinv + pp.cgauss * e);
+        const real ljf = r2 < lj.rc2 ? r6 * rinv2 * (lj.a12 * r6 - lj.b6) : (real)0;
+        const real phi = ex ? coul + qq * rinv2 * rinv : coul - ljf;
+        const real fx = phi * dx, fy = phi * dy, fz = phi * dz;
+        pc.fx += ex ? (real)0 : fx;
+        pc.fy += ex ? (real)0 : fy;
+        pc.fz += ex ? (real)0 : fz;
+        px.fx += ex ? fx : (real)0;
+        px.fy += ex ? fy : (real)0;
+        px.fz += ex ? fz : (real)0;
+    }
+}
+
+// Excluded-pair correction f = psi r_ij of one pair, accumulated into px.
+template <typename real, bool EV>
+__device__ __forceinline__ void add_excl(PairSum<real>& px, uint4 si, real qi, uint4 sj, real qj,
+                                         const PairParams<real>& pp)
 {
     using M = Math<real>;
     real dx, dy, dz;
@@ -530,37 +633,15 @@ __device__ __forceinline__ void add_pair_or_excl(PairSum<real>& pc, PairSum<real
     const real rinv = M::rsqrt_(r2);
     const real r = r2 * rinv;
     const real br = pp.beta * r;
-    const real e = M::exp_(-br * br);
-    const real ec = M::erfc_ex(br, e);
+    const real ex = M::exp_(-br * br);
+    const real ef = M::erf_(br);
     const real rinv2 = rinv * rinv;
-    const real r6 = rinv2 * rinv2 * rinv2;
-    const real coul = -qq * rinv2 * (ec * rinv + pp.cgauss * e);
-    const real ljf = r2 < lj.rc2 ? r6 * rinv2 * (lj.a12 * r6 - lj.b6) : (real)0;
-    const real phi = ex ? coul + qq * rinv2 * rinv : coul - ljf;
-    const real fx = phi * dx, fy = phi * dy, fz = phi * dz;
-    pc.fx += ex ? (real)0 : fx;
-    pc.fy += ex ? (real)0 : fy;
-    pc.fz += ex ? (real)0 : fz;
-    px.fx += ex ? fx : (real)0;
-    px.fy += ex ? fy : (real)0;
-    px.fz += ex ? fz : (real)0;
-}
-
-// Excluded-pair correction of one pair, accumulated into px.
-template <typename real, bool EV>
-__device__ __forceinline__ void add_excl(PairSum<real>& px, uint4 si, real qi, uint4 sj, real qj,
-                                         const PairParams<real>& pp)
-{
-    real dx, dy, dz;
-    separation(si, sj, pp.quantum, dx, dy, dz);
-    const real r2 = dx * dx + dy * dy + dz * dz;
-    real u;
-    const real psi = excl_psi<real, EV>(r2, qi * qj, pp, u);
+    const real psi = -qq * rinv2 * (pp.cgauss * ex - ef * rinv);
     px.fx += psi * dx;
     px.fy += psi * dy;
     px.fz += psi * dz;
     if (EV) {
-        px.uc += u;
+        px.uc += -qq * ef * rinv;
         px.v[0] += psi * dx * dx; px.v[1] += psi * dy * dy; px.v[2] += psi * dz * dz;
         px.v[3] += psi * dx * dy; px.v[4] += psi * dx * dz; px.v[5] += psi * dy * dz;
     }
@@ -674,24 +755,84 @@ __global__ __launch_bounds__(kCoopBlock, ENC && !EV && sizeof(real) == 4 ? 5 : 1
     // the shell entries of atom a + 1 and the first level of atom a + 2 are loaded
     // (issued after atom a's gathers, so that waiting for those does not wait for
     // them: the vector memory counter is in order)
+    // Full list without energies: the list and the excluded partners as one sequence
+    // of 64-entry passes, the indices of the pass after next and the atoms of the next
+    // one in flight while a pass is evaluated. Bound by vector issue (13 passes of a
+    // water atom's 728 entries at about 60 slots): 3,145,728 atoms 4.4 ms, 4.92 ms as
+    // a loop of dependent loads with the excluded pairs in a pass of their own.
+    constexpr bool kPass = FULL && !EV;
+    constexpr bool kFused = !EV && (FULL || SKIN);
+    if constexpr (kPass) {
+        auto entry = [&](int64_t a, int t, int pass) -> int {
+            const int ns = bcast(h_ns, t), nx = bcast(h_x.y, t);
+            const int e = pass * 64 + lane;
+            const int32_t* const srow = shell + a * (int64_t)cap_shell;
+            if (pass * 64 + 64 <= ns) return srow[e];  // (uniform: a pass of list entries only)
+            return e < ns ? srow[e] : (e < ns + nx ? sxidx[bcast(h_x.x, t) + e - ns] : -1);
+        };
+        int n_j0 = -1, n_j1 = -1;  // the next atom's first two passes
+        if (a0 < a1) {
+            n_j0 = entry(a0, 0, 0);
+            n_j1 = entry(a0, 0, 1);
+        }
+        for (int64_t a = a0; a < a1; ++a) {
+            const int t = (int)(a - a0);
+            const uint4 si = make_uint4(bcast(h_s.x, t), bcast(h_s.y, t), bcast(h_s.z, t), bcast(h_s.w, t));
+            const real qi = bcast(h_q, t) * pp.ke;
+            const LJ<real>* const lrow = lj + (int)si.w * n_types;
+            const int ns = bcast(h_ns, t);
+            const int passes = (ns + bcast(h_x.y, t) + 63) >> 6;
+            int j = n_j0, jn = n_j1;
+            uint4 pj;
+            real qj;
+            at.get(max(j, 0), pj, qj);
+            if (a + 1 < a1) {
+                n_j0 = entry(a + 1, t + 1, 0);
+                n_j1 = entry(a + 1, t + 1, 1);
+            }
+            PairSum<real> pc, px;  // (px unused)
+            for (int p = 0; p < passes; ++p) {
+                const uint4 sj = pj;
+                const real q = qj;
+                const bool in = j >= 0;
+                j = jn;
+                at.get(max(j, 0), pj, qj);
+                jn = p + 2 < passes ? entry(a, t, p + 2) : -1;
+                const bool ex = p * 64 + lane >= ns;
+                if (in && (ex || !SKIN || dist2_q(si, sj) <= t_shell))
+                    add_pair_or_excl<real, kFused>(pc, px, si, qi, sj, q, lrow[sj.w], pp, ex);
+            }
+            const real fx = pp.quantum * wave_sum(pc.fx);
+            const real fy = pp.quantum * wave_sum(pc.fy);
+            const real fz = pp.quantum * wave_sum(pc.fz);
+            if (lane == 0) {
+                fsr[3 * a + 0] = fx;
+                fsr[3 * a + 1] = fy;
+                fsr[3 * a + 2] = fz;
+                fc_sum[0] += (double)fx;
+                fc_sum[1] += (double)fy;
+                fc_sum[2] += (double)fz;
+            }
+        }
+    }
     int n_jc = -1, n_e0 = -1, n_e1 = -1, n_jx = -1;  // atom a: first level and shell entries
     int m_jc = -1, m_r0 = -1, m_r1 = -1, m_jx = -1;  // atom a + 1: first level
     uint4 m_mk = make_uint4(0u, 0u, 0u, 0u);         // ... and its mask words
-    if (a0 < a1) {
+    if (!kPass && a0 < a1) {
         int r0, r1;
         first_level(a0, 0, n_jc, r0, r1, n_jx, m_mk);
         second_level(a0, 0, r0, r1, m_mk, n_e0, n_e1);
         if (a0 + 1 < a1) first_level(a0 + 1, 1, m_jc, m_r0, m_r1, m_jx, m_mk);
     }
-    for (int64_t a = a0; a < a1; ++a) {
+    for (int64_t a = a0; !kPass && a < a1; ++a) {
         const int t = (int)(a - a0);
         const int jc = n_jc, e0 = n_e0, e1 = n_e1, jx = n_jx;
         const uint4 si = make_uint4(bcast(h_s.x, t), bcast(h_s.y, t), bcast(h_s.z, t),
                                     bcast(h_s.w, t));
         const real qi = bcast(h_q, t) * pp.ke;
-        // LJ coefficients of the pair types (32-bit LDS indexing; n_types^2 <= 256)
+        // LJ coefficients of the pair types
         const int li = (int)si.w * n_types;
-        auto ljof = [&](uint4 sj) -> const LJ<real>& { return lj[(li + (int)sj.w) & 255]; };
+        auto ljof = [&](uint4 sj) -> LJ<real> { return lj[li + (int)sj.w]; };
         const int nc = bcast(h_nc, t);
         const int ns = bcast(h_ns, t);
         const int2 xr = make_int2(bcast(h_x.x, t), bcast(h_x.y, t));
@@ -743,15 +884,15 @@ __global__ __launch_bounds__(kCoopBlock, ENC && !EV && sizeof(real) == 4 ? 5 : 1
             return d2 <= t_shell && (FULL || d2 > t_core);
         };
         if (kFold) {
-            if (jc >= 0 && (lane >= nc || core_ok(pjc))) add_pair_or_excl(pc, px, si, qi, pjc, qjc, ljof(pjc), pp, lane >= nc);
+            if (jc >= 0 && (lane >= nc || core_ok(pjc))) add_pair_or_excl<real, kFused>(pc, px, si, qi, pjc, qjc, ljof(pjc), pp, lane >= nc);
         } else {
-            if (jc >= 0 && core_ok(pjc)) add_pair<real, EV>(pc, si, qi, pjc, qjc, ljof(pjc), pp);
+            if (jc >= 0 && core_ok(pjc)) add_pair<real, EV, kFused>(pc, si, qi, pjc, qjc, ljof(pjc), pp);
             if (jx >= 0) add_excl<real, EV>(px, si, qi, pjx, qjx, pp);
         }
         if (STENCIL ? stencil_member(a, js0, mi, mj0, si, pj0, t_core, t_shell) : (js0 >= 0 && shell_ok(pj0)))
-            add_pair<real, EV>(ps, si, qi, pj0, qj0, ljof(pj0), pp);
+            add_pair<real, EV, kFused>(ps, si, qi, pj0, qj0, ljof(pj0), pp);
         if (STENCIL ? stencil_member(a, js1, mi, mj1, si, pj1, t_core, t_shell) : (js1 >= 0 && shell_ok(pj1)))
-            add_pair<real, EV>(ps, si, qi, pj1, qj1, ljof(pj1), pp);
+            add_pair<real, EV, kFused>(ps, si, qi, pj1, qj1, ljof(pj1), pp);
         // the rest (long lists and large batches)
         if (kFold) {
             for (int c = lane + 64; c < nc + xr.y; c += 64) {
@@ -759,7 +900,7 @@ __global__ __launch_bounds__(kCoopBlock, ENC && !EV && sizeof(real) == 4 ? 5 : 1
                 uint4 sj;
                 real qj;
                 at.get(j, sj, qj);
-                if (c >= nc || core_ok(sj)) add_pair_or_excl(pc, px, si, qi, sj, qj, ljof(sj), pp, c >= nc);
+                if (c >= nc || core_ok(sj)) add_pair_or_excl<real, kFused>(pc, px, si, qi, sj, qj, ljof(sj), pp, c >= nc);
             }
         } else {
             for (int c = lane + 64; c < nc; c += 64) {
@@ -767,7 +908,7 @@ __global__ __launch_bounds__(kCoopBlock, ENC && !EV && sizeof(real) == 4 ? 5 : 1
                 uint4 sj;
                 real qj;
                 at.get(j, sj, qj);
-                if (core_ok(sj)) add_pair<real, EV>(pc, si, qi, sj, qj, ljof(sj), pp);
+                if (core_ok(sj)) add_pair<real, EV, kFused>(pc, si, qi, sj, qj, ljof(sj), pp);
             }
             for (int c = lane + 64; c < xr.y; c += 64) {
                 uint4 sj;
@@ -795,21 +936,22 @@ __global__ __launch_bounds__(kCoopBlock, ENC && !EV && sizeof(real) == 4 ? 5 : 1
                 real qj;
                 at.get(j, sj, qj);
                 if (stencil_member(a, j, mi, mj, si, sj, t_core, t_shell))
-                    add_pair<real, EV>(ps, si, qi, sj, qj, ljof(sj), pp);
+                    add_pair<real, EV, kFused>(ps, si, qi, sj, qj, ljof(sj), pp);
             } else {
                 const int j = member(sample ? (int)rrow[c] : c);
                 if (!FULL && bj_out) bj_out[a * (int64_t)p_stride + c] = j;
                 uint4 sj;
                 real qj;
                 at.get(j, sj, qj);
-                if (shell_ok(sj)) add_pair<real, EV>(ps, si, qi, sj, qj, ljof(sj), pp);
+                if (shell_ok(sj)) add_pair<real, EV, kFused>(ps, si, qi, sj, qj, ljof(sj), pp);
             }
         }
         // one set of sums: the excluded-pair forces cancel pairwise, so the momentum
         // correction may sum them with the rest
-        const real fx = wave_sum_r(pc.fx + w * ps.fx + px.fx);
-        const real fy = wave_sum_r(pc.fy + w * ps.fy + px.fy);
-        const real fz = wave_sum_r(pc.fz + w * ps.fz + px.fz);
+        const real fu = kFused ? pp.quantum : (real)1;
+        const real fx = fu * wave_sum(pc.fx + w * ps.fx + px.fx);
+        const real fy = fu * wave_sum(pc.fy + w * ps.fy + px.fy);
+        const real fz = fu * wave_sum(pc.fz + w * ps.fz + px.fz);
         if (lane == 0) {
             fsr[3 * a + 0] = fx;
             fsr[3 * a + 1] = fy;
@@ -826,22 +968,30 @@ __global__ __launch_bounds__(kCoopBlock, ENC && !EV && sizeof(real) == 4 ? 5 : 1
             for (int c = 0; c < 6; ++c) ev.v[c] += pc.v[c] + w * ps.v[c] + px.v[c];
         }
     }
-    double vals[kPairPartials];
-    vals[0] = fc_sum[0];
-    vals[1] = fc_sum[1];
-    vals[2] = fc_sum[2];
+    // per-block sums: the force sums sit in one lane per wavefront; with energies nine
+    // more values, summed over the lanes
+    constexpr int NW = kCoopBlock / 64;
+    if (lane == 0)
+        for (int c = 0; c < 3; ++c) red[c * NW + wave] = fc_sum[c];
     if (EV) {
-        vals[3] = 0.5 * (double)ev.uc;
-        vals[4] = 0.5 * (double)ev.ul;
-        vals[5] = 0.5 * (double)ev.fx;
-        for (int c = 0; c < 6; ++c) vals[6 + c] = -0.5 * (double)ev.v[c];
-    } else {
-        for (int c = 3; c < 12; ++c) vals[c] = 0.0;
+        double vals[9];
+        vals[0] = 0.5 * (double)ev.uc;
+        vals[1] = 0.5 * (double)ev.ul;
+        vals[2] = 0.5 * (double)ev.fx;
+        for (int c = 0; c < 6; ++c) vals[3 + c] = -0.5 * (double)ev.v[c];
+#pragma unroll
+        for (int c = 0; c < 9; ++c) {
+            const double t = wave_sum(vals[c]);
+            if (lane == 0) red[(3 + c) * NW + wave] = t;
+        }
     }
-    for (int c = 12; c < kPairPartials; ++c) vals[c] = 0.0;
-    double out;
-    block_sum_vec<12, kCoopBlock>(vals, red, threadIdx.x, out);
-    if (threadIdx.x < 12) part[blk * (int64_t)kPairPartials + threadIdx.x] = out;
+    __syncthreads();
+    if (threadIdx.x < (EV ? 12 : 3)) {
+        double t = 0.0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) t += red[threadIdx.x * NW + w];
+        part[blk * (int64_t)kPairPartials + threadIdx.x] = t;
+    }
 }
 
 // Core entries and batch slots of the first pass of k_pair_thread.
@@ -868,17 +1018,18 @@ __global__ __launch_bounds__(kCoopBlock) void k_pair_thread(
     __syncthreads();
     const int64_t blk = xcd_block(blockIdx.x, gridDim.x);
     const int64_t a = blk * kCoopBlock + threadIdx.x;
-    double vals[kPairPartials];
-    for (int c = 0; c < kPairPartials; ++c) vals[c] = 0.0;
+    constexpr int NV = EV ? 12 : 3;
+    double vals[NV];
+    for (int c = 0; c < NV; ++c) vals[c] = 0.0;
     const Atoms<real> at{spos, sqr, spq};
     if (a < n) {
         uint4 si;
         real qi;
         at.get(a, si, qi);
         qi *= pp.ke;
-        // LJ coefficients of the pair types (32-bit LDS indexing; n_types^2 <= 256)
+        // LJ coefficients of the pair types
         const int li = (int)si.w * n_types;
-        auto ljof = [&](uint4 sj) -> const LJ<real>& { return lj[(li + (int)sj.w) & 255]; };
+        auto ljof = [&](uint4 sj) -> LJ<real> { return lj[li + (int)sj.w]; };
         PairSum<real> pc, ps, px;
         const int nc = ncore[a];
         const int32_t* crow = core + a * (int64_t)cap_core;
@@ -914,11 +1065,11 @@ __global__ __launch_bounds__(kCoopBlock) void k_pair_thread(
 #pragma unroll
         for (int u = 0; u < kThreadFirst; ++u)
             if (jc[u] >= 0 && (!skin || dist2_q(si, sc[u]) <= t_core))
-                add_pair<real, EV>(pc, si, qi, sc[u], qc[u], ljof(sc[u]), pp);
+                add_pair<real, EV, false>(pc, si, qi, sc[u], qc[u], ljof(sc[u]), pp);
 #pragma unroll
         for (int u = 0; u < kThreadFirst; ++u)
             if (js[u] >= 0 && (!skin || in_annulus(si, ss[u], t_core, t_shell)))
-                add_pair<real, EV>(ps, si, qi, ss[u], qs[u], ljof(ss[u]), pp);
+                add_pair<real, EV, false>(ps, si, qi, ss[u], qs[u], ljof(ss[u]), pp);
         // the rest four entries at a time: their index and position loads go out together
         for (int c0 = kThreadFirst; c0 < nc; c0 += 4) {
             int j[4];
@@ -931,7 +1082,7 @@ __global__ __launch_bounds__(kCoopBlock) void k_pair_thread(
 #pragma unroll
             for (int u = 0; u < 4; ++u)
                 if (j[u] >= 0 && (!skin || dist2_q(si, sj[u]) <= t_core))
-                    add_pair<real, EV>(pc, si, qi, sj[u], qj[u], ljof(sj[u]), pp);
+                    add_pair<real, EV, false>(pc, si, qi, sj[u], qj[u], ljof(sj[u]), pp);
         }
         const int2 xr = sxr[a];
         for (int c = 0; c < xr.y; ++c) {
@@ -959,7 +1110,7 @@ __global__ __launch_bounds__(kCoopBlock) void k_pair_thread(
 #pragma unroll
             for (int u = 0; u < 4; ++u)
                 if (j[u] >= 0 && (!skin || in_annulus(si, sj[u], t_core, t_shell)))
-                    add_pair<real, EV>(ps, si, qi, sj[u], qj[u], ljof(sj[u]), pp);
+                    add_pair<real, EV, false>(ps, si, qi, sj[u], qj[u], ljof(sj[u]), pp);
         }
         const real w = sample ? (real)((double)ns / (double)p_shell) : (real)1;
         const real fx = pc.fx + w * ps.fx + px.fx;
@@ -979,8 +1130,8 @@ __global__ __launch_bounds__(kCoopBlock) void k_pair_thread(
         }
     }
     double out;
-    block_sum_vec<12, kCoopBlock>(vals, red, threadIdx.x, out);
-    if (threadIdx.x < 12) part[blk * (int64_t)kPairPartials + threadIdx.x] = out;
+    block_sum_vec<NV, kCoopBlock>(vals, red, threadIdx.x, out);
+    if (threadIdx.x < NV) part[blk * (int64_t)kPairPartials + threadIdx.x] = out;
 }
 
 static StencilArgs stencil_args(const irbe_ctx* h)
@@ -1087,11 +1238,7 @@ template <typename real, bool FULL, bool EV, bool STENCIL, bool SKIN, bool ENC =
 static hipError_t launch_coop_t(irbe_ctx* h, uint64_t step)
 {
     const int64_t n = h->cfg.n_atoms;
-    PairParams<real> pp;
-    pp.quantum = (real)h->geo.quantum;
-    pp.beta = (real)h->cfg.ewald_beta;
-    pp.cgauss = (real)(2.0 * h->cfg.ewald_beta / 1.7724538509055160273);
-    pp.ke = (real)h->cfg.coulomb_k;
+    const PairParams<real> pp = pair_params<real>(h);
     hipError_t e = launch_draw(h, step);
     if (e != hipSuccess) return e;
     // stencil sampling keeps one cell's stencil rows for consecutive atoms: longer
@@ -1116,11 +1263,7 @@ template <typename real, bool EV>
 static hipError_t launch_thread_t(irbe_ctx* h, uint64_t step)
 {
     const int64_t n = h->cfg.n_atoms;
-    PairParams<real> pp;
-    pp.quantum = (real)h->geo.quantum;
-    pp.beta = (real)h->cfg.ewald_beta;
-    pp.cgauss = (real)(2.0 * h->cfg.ewald_beta / 1.7724538509055160273);
-    pp.ke = (real)h->cfg.coulomb_k;
+    const PairParams<real> pp = pair_params<real>(h);
     hipError_t e = launch_draw(h, step);
     if (e != hipSuccess) return e;
     const unsigned nb = (unsigned)blocks_for(n, kCoopBlock);
@@ -1173,41 +1316,49 @@ static hipError_t launch_coop_r(irbe_ctx* h, uint64_t step, bool ev)
 // force) / N when rbl.
 constexpr int kReduceSlices = 256;
 
+template <int NV>
 __global__ __launch_bounds__(kReduceBlock) void k_pair_reduce1(int64_t nb, const double* __restrict__ part,
                                                                double* __restrict__ slices)
 {
-    __shared__ double lds[12 * (kReduceBlock / 64)];
-    const int64_t per = (nb + kReduceSlices - 1) / kReduceSlices;
+    __shared__ double lds[NV * (kReduceBlock / 64)];
+    const int64_t per = (nb + gridDim.x - 1) / gridDim.x;
     const int64_t b0 = blockIdx.x * per, b1 = min(nb, b0 + per);
-    double vals[12];
-    for (int c = 0; c < 12; ++c) vals[c] = 0.0;
+    double vals[NV];
+    for (int c = 0; c < NV; ++c) vals[c] = 0.0;
     for (int64_t b = b0 + threadIdx.x; b < b1; b += kReduceBlock)
-        for (int c = 0; c < 12; ++c) vals[c] += part[b * kPairPartials + c];
+        for (int c = 0; c < NV; ++c) vals[c] += part[b * kPairPartials + c];
     double out;
-    block_sum_vec<12, kReduceBlock>(vals, lds, threadIdx.x, out);
-    if (threadIdx.x < 12) slices[blockIdx.x * 12 + threadIdx.x] = out;
+    block_sum_vec<NV, kReduceBlock>(vals, lds, threadIdx.x, out);
+    if (threadIdx.x < NV) slices[blockIdx.x * 12 + threadIdx.x] = out;
 }
 
-__global__ __launch_bounds__(kReduceBlock) void k_pair_reduce2(const double* __restrict__ slices, int64_t n, int rbl,
-                                                               double* __restrict__ ev_pair,
+template <int NV>
+__global__ __launch_bounds__(kReduceBlock) void k_pair_reduce2(int n_slices, const double* __restrict__ slices,
+                                                               int64_t n, int rbl, double* __restrict__ ev_pair,
                                                                double* __restrict__ fcorr)
 {
-    __shared__ double lds[12 * (kReduceBlock / 64)];
-    double vals[12];
-    for (int c = 0; c < 12; ++c) vals[c] = 0.0;
-    for (int b = threadIdx.x; b < kReduceSlices; b += kReduceBlock)
-        for (int c = 0; c < 12; ++c) vals[c] += slices[b * 12 + c];
+    __shared__ double lds[NV * (kReduceBlock / 64)];
+    double vals[NV];
+    for (int c = 0; c < NV; ++c) vals[c] = 0.0;
+    for (int b = threadIdx.x; b < n_slices; b += kReduceBlock)
+        for (int c = 0; c < NV; ++c) vals[c] += slices[b * 12 + c];
     double out;
-    block_sum_vec<12, kReduceBlock>(vals, lds, threadIdx.x, out);
-    if (threadIdx.x < 12) ev_pair[threadIdx.x] = out;
+    block_sum_vec<NV, kReduceBlock>(vals, lds, threadIdx.x, out);
+    if (threadIdx.x < NV) ev_pair[threadIdx.x] = out;
     if (threadIdx.x < 3) fcorr[threadIdx.x] = rbl ? out / (double)n : 0.0;
 }
 
-hipError_t launch_pair_reduce(irbe_ctx* h)
+hipError_t launch_pair_reduce(irbe_ctx* h, bool ev)
 {
-    k_pair_reduce1<<<kReduceSlices, kReduceBlock, 0, h->stream>>>(h->pair_nb, h->pair_part, h->pair_slices);
-    k_pair_reduce2<<<1, kReduceBlock, 0, h->stream>>>(h->pair_slices, h->cfg.n_atoms, h->full_list ? 0 : 1,
-                                                      h->ev_pair, h->fcorr);
+    // (without energies the blocks write the three force sums only)
+    auto run = [&](auto nv) {
+        constexpr int NV = decltype(nv)::value;
+        k_pair_reduce1<NV><<<kReduceSlices, kReduceBlock, 0, h->stream>>>(h->pair_nb, h->pair_part, h->pair_slices);
+        k_pair_reduce2<NV><<<1, kReduceBlock, 0, h->stream>>>(kReduceSlices, h->pair_slices, h->cfg.n_atoms,
+                                                              h->full_list ? 0 : 1, h->ev_pair, h->fcorr);
+    };
+    if (ev) run(std::integral_constant<int, 12>{});
+    else run(std::integral_constant<int, 3>{});
     return hipGetLastError();
 }
 
@@ -1290,30 +1441,23 @@ template <typename real>
 __device__ __forceinline__ PairGrad<real> pair_grad(real r2, real qq, const LJGrad<real>& L, const PairParams<real>& pp,
                                                     bool xp = false)
 {
-    using M = Math<real>;
-    const real rinv = M::rsqrt_(r2);
-    const real r = r2 * rinv;
-    const real br = pp.beta * r;
-    const real ex = M::exp_(-br * br);
-    const real ec = M::erfc_ex(br, ex);
-    const real rinv2 = rinv * rinv;
-    const real rinv3 = rinv2 * rinv;
-    const real A = ec * rinv3;
-    const real B = pp.cgauss * ex * rinv2;
-    const real dA = -rinv * (B + (real)3 * A);
-    const real dB = -B * ((real)2 * pp.beta * pp.beta * r + (real)2 * rinv);
+    // with A = erfc/r^3, B = cgauss e^{-b^2 r^2}/r^2 and a = A + B (- 1/r^3): phi = -qq a and
+    // phi'/r = qq (3 a / r^2 + 2 b^2 B) for the Coulomb part
+    const Radial<real> o = radial(r2, pp);
+    const real rinv2 = o.rinv2;
+    const real B = pp.cgauss * o.ex * rinv2;
+    const real a = (xp ? o.g - o.rinv : o.g) * rinv2;
     const real r6 = rinv2 * rinv2 * rinv2;
     const real r8 = r6 * rinv2;
-    const real on = (xp || !(r2 < L.rc2)) ? (real)0 : (real)1;
-    const real C = on * r8 * (L.a48 * r6 - L.b24);
-    const real dC = on * rinv * r8 * (L.b192 - L.a672 * r6);
-    const real eps = on * L.eps;
+    const real on = (xp || !(r2 < L.rc2)) ? (real)0 : r8;
+    const real C = on * (L.a48 * r6 - L.b24);
+    const real dC = on * rinv2 * (L.b192 - L.a672 * r6);
     PairGrad<real> g;
-    g.a_coul = xp ? A + B - rinv3 : A + B;
-    g.phi = -qq * g.a_coul - eps * C;
-    g.dphi_r = (-qq * (dA + dB) - eps * dC) * rinv - (xp ? (real)3 * qq * rinv2 * rinv3 : (real)0);
+    g.a_coul = a;
+    g.phi = -qq * a - L.eps * C;
+    g.dphi_r = qq * ((real)3 * rinv2 * a + (real)2 * pp.beta * pp.beta * B) - L.eps * dC;
     g.c_lj = C;
-    g.dc_dsig = on * r8 * (L.as * r6 - L.bs);
+    g.dc_dsig = on * (L.as * r6 - L.bs);
     return g;
 }
 
@@ -1509,7 +1653,7 @@ __global__ __launch_bounds__(kCoopBlock) void k_pair_adjoint(
         if (BK) key_cell(bk, a, si, zi, yi);
         // with every sigma of its row zero, the atom has no LJ term and no LJ gradient
         const bool lj_i = WANT_LJ && lj_row[ti];
-        const real qi = bcast(h_q, t_a);
+        const real qi = ke * bcast(h_q, t_a);
         const real gx = bcast(h_gx, t_a), gy = bcast(h_gy, t_a), gz = bcast(h_gz, t_a);
         const real pgx = gx - mx, pgy = gy - my, pgz = gz - mz;  // G'_i
         const int nsym = bcast(h_nsym, t_a);
@@ -1534,13 +1678,14 @@ __global__ __launch_bounds__(kCoopBlock) void k_pair_adjoint(
             separation(si, sj, pp.quantum, dx, dy, dz);
             const real r2 = dx * dx + dy * dy + dz * dz;
             const LJGrad<real>& L = ljg[li + (int)sj.w];
-            const PairGrad<real> g = pair_grad(r2, ke * qi * qj, L, pp, xp);
+            const PairGrad<real> g = pair_grad(r2, qi * qj, L, pp, xp);
             const real ex_ = gjx - gx, ey_ = gjy - gy, ez_ = gjz - gz;
             const real gd = dx * ex_ + dy * ey_ + dz * ez_;
-            rx += g.phi * ex_ + g.dphi_r * dx * gd;
-            ry += g.phi * ey_ + g.dphi_r * dy * gd;
-            rz += g.phi * ez_ + g.dphi_r * dz * gd;
-            rq += ke * qj * g.a_coul * gd;
+            const real dg = g.dphi_r * gd;
+            rx += g.phi * ex_ + dg * dx;
+            ry += g.phi * ey_ + dg * dy;
+            rz += g.phi * ez_ + dg * dz;
+            rq += qj * g.a_coul * gd;
             if (lj_i) {
                 const real gdi = dx * pgx + dy * pgy + dz * pgz;
                 const int tj = (int)sj.w;
@@ -1558,16 +1703,18 @@ __global__ __launch_bounds__(kCoopBlock) void k_pair_adjoint(
             separation(si, sj, pp.quantum, dx, dy, dz);
             const real r2 = dx * dx + dy * dy + dz * dz;
             const LJGrad<real>& L = ljg[li + (int)sj.w];
-            const PairGrad<real> g = pair_grad(r2, ke * qi * qj, L, pp);
+            const PairGrad<real> g = pair_grad(r2, qi * qj, L, pp);
             const real gdi = dx * pgx + dy * pgy + dz * pgz;
-            const real jx_ = w * (g.phi * pgx + g.dphi_r * dx * gdi);
-            const real jy_ = w * (g.phi * pgy + g.dphi_r * dy * gdi);
-            const real jz_ = w * (g.phi * pgz + g.dphi_r * dz * gdi);
+            const real wphi = w * g.phi, dg = w * g.dphi_r * gdi;
+            const real jx_ = wphi * pgx + dg * dx;
+            const real jy_ = wphi * pgy + dg * dy;
+            const real jz_ = wphi * pgz + dg * dz;
             rx -= jx_;
             ry -= jy_;
             rz -= jz_;
-            rq += w * (-ke * qj * g.a_coul) * gdi;
-            const real jq_ = w * (-ke * qi * g.a_coul) * gdi;
+            const real wag = w * g.a_coul * gdi;
+            rq -= qj * wag;
+            const real jq_ = -qi * wag;
             bool staged = false;
             if (BK) {
                 // key: (source row - row0, row offset of j), on the cells of the build
@@ -1660,10 +1807,10 @@ __global__ __launch_bounds__(kCoopBlock) void k_pair_adjoint(
                     if (!SKIN || in_annulus(si, sj, t_core, t_shell)) shell_pair(j, sj, qj);
                 }
             }
-        rx = wave_sum_r(rx);
-        ry = wave_sum_r(ry);
-        rz = wave_sum_r(rz);
-        rq = wave_sum_r(rq);
+        rx = wave_sum(rx);
+        ry = wave_sum(ry);
+        rz = wave_sum(rz);
+        rq = ke * wave_sum(rq);
         if (lane == 0) {
             gself[3 * a + 0] = rx;
             gself[3 * a + 1] = ry;
@@ -1673,8 +1820,8 @@ __global__ __launch_bounds__(kCoopBlock) void k_pair_adjoint(
         if (lj_i && ti < kMaxTypesGrad) {
 #pragma unroll
             for (int t = 0; t < kMaxTypesGrad; ++t) {
-                const real s_sig = wave_sum_r(acc_sig[t]);
-                const real s_eps = wave_sum_r(acc_eps[t]);
+                const real s_sig = wave_sum(acc_sig[t]);
+                const real s_eps = wave_sum(acc_eps[t]);
                 if (lane == 0) {
                     ljacc[wave][ti * kMaxTypesGrad + t] += (double)s_sig;
                     ljacc[wave][kMaxTypesGrad * kMaxTypesGrad + ti * kMaxTypesGrad + t] += (double)s_eps;
@@ -1830,11 +1977,7 @@ template <typename real, bool FULL, bool WANT_LJ, bool BK, bool STENCIL, bool BA
 static hipError_t launch_adj_t(irbe_ctx* h, uint64_t step, int apw, const BucketArgs& bk, int rec_cap, size_t lds)
 {
     const int64_t n = h->cfg.n_atoms;
-    PairParams<real> pp;
-    pp.quantum = (real)h->geo.quantum;
-    pp.beta = (real)h->cfg.ewald_beta;
-    pp.cgauss = (real)(2.0 * h->cfg.ewald_beta / 1.7724538509055160273);
-    pp.ke = (real)h->cfg.coulomb_k;
+    const PairParams<real> pp = pair_params<real>(h);
     hipError_t e = launch_draw(h, step);
     if (e != hipSuccess) return e;
     if (STENCIL && !h->batch_j_valid) {
