@@ -260,8 +260,8 @@ irbe_status irbe_sync(irbe_handle h);
 enum {
     IRBE_STAGE_BIN = 0,        /* quantize, histogram, scan, scatter, in-cell sort, gather */
     IRBE_STAGE_LISTS = 1,      /* core/shell list build kernel                             */
-    IRBE_STAGE_QUANTIZE = 2,   /* re-quantize positions for a force evaluation             */
-    IRBE_STAGE_KSAMPLE = 3,    /* k-vector draw                                            */
+    IRBE_STAGE_QUANTIZE = 2,   /* re-quantize positions for a force evaluation, k draw     */
+    IRBE_STAGE_KSAMPLE = 3,    /* unused: the k-vector draw runs in the QUANTIZE launch     */
     IRBE_STAGE_RHO = 4,        /* structure factor (partials + final reduction)            */
     IRBE_STAGE_PAIR = 5,       /* pair force kernel                                        */
     IRBE_STAGE_PAIR_REDUCE = 6,/* momentum-correction / energy reduction                   */

@@ -91,6 +91,40 @@ irbe_status hip_fail(irbe_ctx* h, hipError_t e, const char* where)
         if (e_ != hipSuccess) return hip_fail(h, e_, where); \
     } while (0)
 
+// The per-call buffers of one force evaluation, carved from a scratch array.
+struct NoAllocBuffers {
+    void *fsr, *kforce;
+    double *pair_part, *pair_slices, *ev_pair, *fcorr, *kcoef, *rho_part, *rho;
+    int4* kvec;
+    uint16_t* ranks;
+    size_t used;
+};
+
+NoAllocBuffers noalloc_carve(const irbe_ctx* h, unsigned char* base)
+{
+    const size_t n = (size_t)h->cfg.n_atoms, rs = h->real_size, P = (size_t)h->cfg.p_kspace;
+    NoAllocBuffers b{};
+    auto take = [&](size_t bytes) {
+        void* const p = (void*)((uintptr_t)base + b.used);
+        b.used += (bytes + 255) / 256 * 256;
+        return p;
+    };
+    b.fsr = take(3 * n * rs);
+    b.pair_part = (double*)take((size_t)h->part_blocks * kPairPartials * sizeof(double));
+    b.pair_slices = (double*)take(256 * 12 * sizeof(double));
+    b.ev_pair = (double*)take(kPairPartials * sizeof(double));
+    b.fcorr = (double*)take(3 * sizeof(double));
+    b.kvec = (int4*)take(P * sizeof(int4));
+    b.kcoef = (double*)take(4 * P * sizeof(double));
+    b.rho_part = (double*)take(2 * P * (size_t)rho_blocks(h) * sizeof(double));
+    b.rho = (double*)take(2 * P * sizeof(double));
+    b.kforce = take(P * (h->fp64 ? sizeof(KForce<double>) : sizeof(KForce<float>)));
+    b.ranks = h->p_stride > 0 ? (uint16_t*)take(n * (size_t)h->p_stride * sizeof(uint16_t)) : nullptr;
+    return b;
+}
+
+size_t noalloc_bytes(const irbe_ctx* h) { return noalloc_carve(h, nullptr).used; }
+
 // A launcher bracketed by timing events when timing is on.
 #define IRBE_STAGE(h, stage, expr, where) \
     do {                                  \
@@ -133,8 +167,7 @@ namespace irbe {
 hipError_t ensure_buckets(irbe_ctx* h, int64_t records)
 {
     hipError_t e = hipSuccess;
-    if (!h->bk_cursor) e = dalloc(h, &h->bk_cursor, 2 * (size_t)h->geo.n_c * (size_t)h->geo.n_c);
-    if (e != hipSuccess || records <= h->bk_total) return e;
+    if (records <= h->bk_total) return e;
     dfree(h, h->bk_c);
     dfree(h, h->bk_j);
     h->bk_c = nullptr;
@@ -315,11 +348,11 @@ void expand_mask_row(const uint32_t* mask, const int32_t* base, int nw, int64_t 
 
 irbe_status check_device_error(irbe_ctx* h)
 {
-    uint32_t err = 0;
-    int32_t mx[3] = {0, 0, 0};
-    IRBE_TRY(h, hipMemcpyAsync(&err, h->err, sizeof(err), hipMemcpyDeviceToHost, h->stream), "read error word");
-    IRBE_TRY(h, hipMemcpyAsync(mx, h->maxcnt, sizeof(mx), hipMemcpyDeviceToHost, h->stream), "read list sizes");
+    int32_t chk[4] = {0, 0, 0, 0};
+    IRBE_TRY(h, hipMemcpyAsync(chk, h->err, sizeof(chk), hipMemcpyDeviceToHost, h->stream), "read the list check");
     IRBE_TRY(h, hipStreamSynchronize(h->stream), "synchronize");
+    const uint32_t err = (uint32_t)chk[0];
+    const int32_t* const mx = chk + 1;
     if (err) {
         IRBE_TRY(h, launch_fill_i32(h->stream, (int32_t*)h->err, 0, 1), "clear error word");
         if (err & ERR_NONFINITE) return fail(h, IRBE_ENONFINITE, "non-finite position");
@@ -531,14 +564,23 @@ irbe_status irbe_create(const irbe_config* cfg, void* hip_stream, irbe_handle* o
     // blocks of four wavefronts with two or more atoms each
     // (the bucketed pair adjoint runs blocks of as few as 8 atoms)
     const int64_t nb64 = std::max(blocks_for(c.n_atoms, 64), blocks_for(c.n_atoms, 8));
-    const int64_t nbr = rho_blocks(c.n_atoms);
     const size_t P = (size_t)c.p_kspace;
     const int nt2 = c.n_types * c.n_types;
 #define ALLOC(expr)                      \
     if (e == hipSuccess) e = (expr);
-    ALLOC(dalloc(h, &h->err, 1));
-    ALLOC(dalloc(h, &h->maxcnt, 3));
-    ALLOC(dalloc(h, &h->adj_atomics, 1));
+    {
+        // the error word, the list maxima, the cell counts and the block slots in one array:
+        // one copy reads the first two back, one fill clears the last three
+        uint32_t* base = nullptr;
+        const int64_t slots = list_block_slots(h->geo, h->stencil, c.n_atoms);
+        ALLOC(dalloc(h, &base, 4 + (size_t)h->geo.n_cells + (size_t)slots));
+        if (base) {
+            h->err = base;
+            h->maxcnt = (int32_t*)base + 1;
+            h->cell_count = (int32_t*)base + 4;
+            h->blk_start = (int32_t*)base + 4 + h->geo.n_cells;
+        }
+    }
     ALLOC(dalloc(h, &h->ktab, U.size()));
     ALLOC(dalloc_bytes(h, &h->q_orig, n * rs));
     ALLOC(dalloc(h, &h->type_orig, n));
@@ -548,7 +590,6 @@ irbe_status irbe_create(const irbe_config* cfg, void* hip_stream, irbe_handle* o
     ALLOC(dalloc(h, &h->sumq2, 1));
     ALLOC(dalloc(h, &h->q2part, (size_t)nb));
     ALLOC(dalloc(h, &h->sq, n));
-    ALLOC(dalloc(h, &h->cell_count, (size_t)h->geo.n_cells));
     ALLOC(dalloc(h, &h->cell_start, (size_t)h->geo.n_cells + 1));
     ALLOC(dalloc(h, &h->cell_bound, (size_t)h->geo.n_c + 1));
     {
@@ -563,7 +604,6 @@ irbe_status irbe_create(const irbe_config* cfg, void* hip_stream, irbe_handle* o
         ALLOC(dalloc(h, &lv, 2));
         h->scan_levels.push_back(lv);
     }
-    ALLOC(dalloc(h, &h->blk_start, (size_t)list_block_slots(h->geo, h->stencil, c.n_atoms)));
     ALLOC(dalloc(h, &h->perm, n));
     ALLOC(dalloc(h, &h->rank, n));
     ALLOC(dalloc(h, &h->spos, n));
@@ -586,7 +626,15 @@ irbe_status irbe_create(const irbe_config* cfg, void* hip_stream, irbe_handle* o
     ALLOC(dalloc(h, &h->ev_pair, kPairPartials));
     ALLOC(dalloc(h, &h->kvec, P));
     ALLOC(dalloc(h, &h->kcoef, 4 * P));
-    ALLOC(dalloc(h, &h->rho_part, 4 * P * (size_t)nbr));
+    h->p_stride = c.p_shell > 0 ? (c.p_shell + 3) / 4 * 4 : 0;
+    h->part_blocks = nb64;
+    // (a small system's structure factors in many blocks take more partial sums: not
+    // where they alone would exceed the no-allocation scratch)
+    if (noalloc_bytes(h) > kNoAllocScratchBytes) {
+        h->rho_wide = true;
+        h->rho_wide = noalloc_bytes(h) <= kNoAllocScratchBytes;
+    }
+    ALLOC(dalloc(h, &h->rho_part, 4 * P * (size_t)rho_blocks(h)));
     ALLOC(dalloc(h, &h->rho, 2 * P));
     ALLOC(dalloc(h, &h->Avec, 2 * P));
     ALLOC(dalloc_bytes(h, &h->kforce, P * sizeof(KForce<double>)));
@@ -595,9 +643,20 @@ irbe_status irbe_create(const irbe_config* cfg, void* hip_stream, irbe_handle* o
     ALLOC(dalloc(h, &h->gpart, (size_t)nb * 3));
     ALLOC(dalloc(h, &h->gmean, 3));
     ALLOC(dalloc_bytes(h, &h->gself, 3 * n * rs));
-    ALLOC(dalloc_bytes(h, &h->gscat, 3 * n * rs));
+    {
+        // cleared by one fill before every pair adjoint: the scatter sums of positions and
+        // charges, the buckets' cursors and maxima, the atomics counter
+        unsigned char* base = nullptr;
+        const size_t rows = (size_t)h->geo.n_c * (size_t)h->geo.n_c;
+        ALLOC(dalloc(h, &base, 4 * n * rs + (2 * rows + 1) * 8));
+        if (base) {
+            h->gscat = base;
+            h->gqscat = base + 3 * n * rs;
+            h->bk_cursor = (unsigned long long*)(base + 4 * n * rs);
+            h->adj_atomics = h->bk_cursor + 2 * rows;
+        }
+    }
     ALLOC(dalloc_bytes(h, &h->gqself, n * rs));
-    ALLOC(dalloc_bytes(h, &h->gqscat, n * rs));
     ALLOC(dalloc(h, &h->ljpart, (size_t)nb64 * 2 * kMaxTypesGrad * kMaxTypesGrad));
     ALLOC(dalloc(h, &h->lj_slices, 256 * 2 * kMaxTypesGrad * kMaxTypesGrad));
 #undef ALLOC
@@ -748,10 +807,8 @@ irbe_status irbe_build_lists(irbe_handle h, const void* pos, uint64_t step)
         if (st != IRBE_OK) return st;
         IRBE_TRY(h, ensure_shell_rows_32(h), "reallocate the shell rows");
         IRBE_STAGE(h, IRBE_STAGE_BIN, launch_bin(h, pos), "binning");
-        IRBE_TRY(h, launch_fill_i32(h->stream, h->maxcnt, 0, 3), "list build");
         IRBE_STAGE(h, IRBE_STAGE_LISTS, launch_build_lists(h), "list build");
-        IRBE_TRY(h, hipMemcpyAsync(h->chk_host, h->err, 4, hipMemcpyDeviceToHost, h->stream), "list check");
-        IRBE_TRY(h, hipMemcpyAsync(h->chk_host + 1, h->maxcnt, 12, hipMemcpyDeviceToHost, h->stream), "list check");
+        IRBE_TRY(h, hipMemcpyAsync(h->chk_host, h->err, 16, hipMemcpyDeviceToHost, h->stream), "list check");
         IRBE_TRY(h, hipEventRecord(h->chk_event, h->stream), "list check");
         h->chk_pending = true;
         h->have_lists = true;
@@ -762,13 +819,13 @@ irbe_status irbe_build_lists(irbe_handle h, const void* pos, uint64_t step)
     IRBE_STAGE(h, IRBE_STAGE_BIN, launch_bin(h, pos), "binning");
     for (int attempt = 0; attempt < 4; ++attempt) {
         IRBE_TRY(h, ensure_shell_rows_32(h), "reallocate the shell rows");
-        IRBE_TRY(h, launch_fill_i32(h->stream, h->maxcnt, 0, 3), "list build");
+        if (attempt > 0) IRBE_TRY(h, launch_fill_i32(h->stream, h->maxcnt, 0, 3), "list build");
         IRBE_STAGE(h, IRBE_STAGE_LISTS, launch_build_lists(h), "list build");
-        int32_t mx[3] = {0, 0, 0};
-        uint32_t err = 0;
-        IRBE_TRY(h, hipMemcpyAsync(mx, h->maxcnt, sizeof(mx), hipMemcpyDeviceToHost, h->stream), "read list sizes");
-        IRBE_TRY(h, hipMemcpyAsync(&err, h->err, sizeof(err), hipMemcpyDeviceToHost, h->stream), "read error word");
+        int32_t chk[4] = {0, 0, 0, 0};
+        IRBE_TRY(h, hipMemcpyAsync(chk, h->err, sizeof(chk), hipMemcpyDeviceToHost, h->stream), "read the list check");
         IRBE_TRY(h, hipStreamSynchronize(h->stream), "synchronize");
+        const uint32_t err = (uint32_t)chk[0];
+        const int32_t* const mx = chk + 1;
         if (err) {
             IRBE_TRY(h, launch_fill_i32(h->stream, (int32_t*)h->err, 0, 1), "clear error word");
             if (err & ERR_NONFINITE) return fail(h, IRBE_ENONFINITE, "non-finite position");
@@ -807,8 +864,7 @@ irbe_status irbe_compute_forces(irbe_handle h, const void* pos, uint64_t step, v
     if (flags && !energy_virial) return fail(h, IRBE_EINVAL, "energy/virial requested without a buffer");
     if (!h->have_lists) return fail(h, IRBE_ESTATE, "irbe_compute_forces before irbe_build_lists");
     const bool ev = flags != 0;
-    IRBE_STAGE(h, IRBE_STAGE_QUANTIZE, launch_requantize(h, pos), "quantize");
-    IRBE_STAGE(h, IRBE_STAGE_KSAMPLE, launch_ksample(h, step), "k sampling");
+    IRBE_STAGE(h, IRBE_STAGE_QUANTIZE, launch_requantize(h, pos, step), "quantize, k sampling");
     IRBE_STAGE(h, IRBE_STAGE_RHO, launch_rho(h, nullptr, false), "structure factor");
     IRBE_STAGE(h, IRBE_STAGE_PAIR, launch_pair_forces(h, step, ev), "pair forces");
     IRBE_STAGE(h, IRBE_STAGE_PAIR_REDUCE, launch_pair_reduce(h, ev), "pair reduction");
@@ -835,28 +891,10 @@ irbe_status irbe_compute_forces_noalloc(irbe_handle h, const void* pos, uint64_t
     unsigned char* base = (unsigned char*)scratch_addr(h->device, &se);
     if (!base) return hip_fail(h, se, "irbe_compute_forces_noalloc: device address of the scratch array");
 
-    // the per-call buffers of one force evaluation, carved from the scratch array
-    const size_t n = (size_t)h->cfg.n_atoms, rs = h->real_size, P = (size_t)h->cfg.p_kspace;
-    size_t used = 0;
-    auto take = [&](size_t bytes) {
-        unsigned char* p = base + used;
-        used += (bytes + 255) / 256 * 256;
-        return (void*)p;
-    };
-    void* fsr = take(3 * n * rs);
-    double* pair_part = (double*)take((size_t)h->part_blocks * kPairPartials * sizeof(double));
-    double* pair_slices = (double*)take(256 * 12 * sizeof(double));
-    double* ev_pair = (double*)take(kPairPartials * sizeof(double));
-    double* fcorr = (double*)take(3 * sizeof(double));
-    int4* kvec = (int4*)take(P * sizeof(int4));
-    double* kcoef = (double*)take(4 * P * sizeof(double));
-    double* rho_part = (double*)take(2 * P * (size_t)rho_blocks(h->cfg.n_atoms) * sizeof(double));
-    double* rho = (double*)take(2 * P * sizeof(double));
-    void* kforce = take(P * (h->fp64 ? sizeof(KForce<double>) : sizeof(KForce<float>)));
-    uint16_t* ranks = h->p_stride > 0 ? (uint16_t*)take(n * (size_t)h->p_stride * sizeof(uint16_t)) : nullptr;
-    if (used > kNoAllocScratchBytes)
+    const NoAllocBuffers b = noalloc_carve(h, base);
+    if (b.used > kNoAllocScratchBytes)
         return fail(h, IRBE_ECAPACITY,
-                    "irbe_compute_forces_noalloc: this system needs " + std::to_string(used) +
+                    "irbe_compute_forces_noalloc: this system needs " + std::to_string(b.used) +
                         " bytes of scratch; the no-allocation scratch holds " + std::to_string(kNoAllocScratchBytes));
 
     // the launchers take their buffers from the handle: point it at the carved
@@ -886,23 +924,22 @@ irbe_status irbe_compute_forces_noalloc(irbe_handle h, const void* pos, uint64_t
         }
     } saved{h, h->fsr, h->kforce, h->pair_part, h->pair_slices, h->ev_pair, h->fcorr, h->kcoef,
             h->rho_part, h->rho, h->kvec, h->ranks};
-    h->fsr = fsr;
-    h->kforce = kforce;
-    h->pair_part = pair_part;
-    h->pair_slices = pair_slices;
-    h->ev_pair = ev_pair;
-    h->fcorr = fcorr;
-    h->kcoef = kcoef;
-    h->rho_part = rho_part;
-    h->rho = rho;
-    h->kvec = kvec;
-    h->ranks = ranks;
+    h->fsr = b.fsr;
+    h->kforce = b.kforce;
+    h->pair_part = b.pair_part;
+    h->pair_slices = b.pair_slices;
+    h->ev_pair = b.ev_pair;
+    h->fcorr = b.fcorr;
+    h->kcoef = b.kcoef;
+    h->rho_part = b.rho_part;
+    h->rho = b.rho;
+    h->kvec = b.kvec;
+    h->ranks = b.ranks;
     h->ranks_valid = false;
 
     // the launch sequence of irbe_compute_forces, without timing events
     const bool ev = flags != 0;
-    IRBE_TRY(h, launch_requantize(h, pos), "quantize");
-    IRBE_TRY(h, launch_ksample(h, step), "k sampling");
+    IRBE_TRY(h, launch_requantize(h, pos, step), "quantize, k sampling");
     IRBE_TRY(h, launch_rho(h, nullptr, false), "structure factor");
     IRBE_TRY(h, launch_pair_forces(h, step, ev), "pair forces");
     IRBE_TRY(h, launch_pair_reduce(h, ev), "pair reduction");
@@ -926,8 +963,7 @@ irbe_status irbe_compute_forces_backward(irbe_handle h, const void* pos, uint64_
         h->keep_batch = true;
     }
     h->fwd_pending = false;
-    IRBE_STAGE(h, IRBE_STAGE_QUANTIZE, launch_requantize(h, pos), "quantize");
-    IRBE_STAGE(h, IRBE_STAGE_KSAMPLE, launch_ksample(h, step), "k sampling");
+    IRBE_STAGE(h, IRBE_STAGE_QUANTIZE, launch_requantize(h, pos, step), "quantize, k sampling");
     IRBE_STAGE(h, IRBE_STAGE_GRAD_GATHER, launch_gather_grad(h, grad_force), "gather dL/dF");
     IRBE_STAGE(h, IRBE_STAGE_RHO_ADJ, launch_rho(h, grad_force, true), "structure factor (adjoint)");
     IRBE_STAGE(h, IRBE_STAGE_PAIR_ADJ, launch_pair_adjoint(h, step, grad_charge != nullptr, grad_lj != nullptr),

@@ -282,6 +282,8 @@ struct Math<double> {
 };
 
 // Exact k.r phase: (m . s) mod 2^32, returned in revolutions in [-1/2, 1/2).
+// (24-bit products of the low parts and a byte dot product of the high ones give the
+// same bits but measured 10-25 % slower in every kernel here.)
 template <typename real>
 __device__ __forceinline__ real phase_rev(int mx, int my, int mz, uint32_t sx, uint32_t sy, uint32_t sz)
 {

@@ -34,7 +34,6 @@ constexpr int kMaskMaxWords = 256;
 constexpr int kBlock = 256;          // threads per block of the per-atom kernels
 constexpr int kReduceBlock = 256;    // threads of the deterministic final reductions
 constexpr int kPairPartials = 16;    // FP64 values per block of the pair kernel
-constexpr int kRhoAtomsPerThread = 8;  // fewest atoms per thread of the structure-factor kernels
 constexpr int kMaxTypesGrad = 4;     // LJ parameter gradients: n_types <= 4
 // atoms per wavefront in the cooperative pair kernels: the adjoint, the forward
 // kernel with list-drawn batches, and the forward kernel with stencil sampling
@@ -113,7 +112,9 @@ struct ListBlockArgs {
     const uint32_t* bound;
     const int32_t* blk_start;        // first atom + 1 of every block slot (0: unused)
     const int2* sxr;
-    const int32_t* sxidx;
+    const int32_t* xidx;             // excluded partners (caller ids) and the caller ids' sorted indices
+    const int32_t* rank;
+    int32_t* sxidx;                  // the partners' sorted indices, written by the build
     int32_t *core, *ncore, *shell, *nshell, *maxcnt;
     uint32_t* err;
     // shell lists as masks (ShellMasks)
@@ -221,6 +222,7 @@ struct irbe_ctx {
     int4* kvec = nullptr;             // [P]
     double* kcoef = nullptr;          // [4P]: kx, ky, kz, c_l
     double* rho_part = nullptr;       // [2 * P * nb_rho] (x2 for the adjoint A)
+    bool rho_wide = false;            // structure factors in the widest shape always (fewest partial sums)
     double* rho = nullptr;            // [2P]
     double* Avec = nullptr;           // [2P]
     void* kforce = nullptr;           // KForce<real>[P]
@@ -278,13 +280,14 @@ struct irbe_ctx {
 namespace irbe {
 
 int64_t blocks_for(int64_t n, int block);
-int64_t rho_blocks(int64_t n);
+int64_t rho_blocks(const irbe_ctx* h);
 
 // Launchers (all on the handle's stream). Each returns the HIP status of the launch.
 hipError_t launch_fill_i32(hipStream_t s, int32_t* p, int32_t v, int64_t n);
 hipError_t launch_fill_bytes0(hipStream_t s, void* p, size_t bytes);
 hipError_t launch_bin(irbe_ctx* h, const void* pos);
-hipError_t launch_requantize(irbe_ctx* h, const void* pos);
+// Positions and charges of a force evaluation, and the k-vectors of `step`.
+hipError_t launch_requantize(irbe_ctx* h, const void* pos, uint64_t step);
 hipError_t launch_build_lists(irbe_ctx* h);
 // Mean atoms per cell below which the list build takes one lane per atom.
 constexpr double kLaneMaxPerCell = 4.0;
@@ -294,7 +297,6 @@ bool lists_by_lanes(const irbe_ctx* h);
 hipError_t launch_list_blocks(irbe_ctx* h);
 ListBlockShape list_block_shape(const Geometry& geo, bool core_only);
 int64_t list_block_slots(const Geometry& geo, bool core_only, int64_t n);
-hipError_t launch_ksample(irbe_ctx* h, uint64_t step);
 hipError_t launch_rho(irbe_ctx* h, const void* grad, bool with_adjoint);
 hipError_t launch_pair_forces(irbe_ctx* h, uint64_t step, bool ev);
 // True when the shell batch draw of the current lists keeps its Floyd bitmaps in
@@ -306,7 +308,7 @@ hipError_t launch_energy_finalize(irbe_ctx* h, double* ev);
 hipError_t launch_sum_q2(irbe_ctx* h);
 hipError_t launch_gather_grad(irbe_ctx* h, const void* grad);
 hipError_t launch_pair_adjoint(irbe_ctx* h, uint64_t step, bool want_q, bool want_lj);
-// Grow the shell-adjoint record buckets to hold `records` records (and create the row cursors).
+// Grow the shell-adjoint record buckets to hold `records` records.
 hipError_t ensure_buckets(irbe_ctx* h, int64_t records);
 // Stencil sampling: allocate the read-back array of the decoded batch, and fill it.
 hipError_t ensure_batch_atoms(irbe_ctx* h);

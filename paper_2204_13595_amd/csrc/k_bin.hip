@@ -144,10 +144,74 @@ __global__ __launch_bounds__(kScanBlock) void k_scan_add(int32_t* __restrict__ o
     if (i < n && blockIdx.x > 0) out[i] += sums[blockIdx.x];
 }
 
+// The last step of the scan: the block offsets, and the total behind the last element.
+__global__ __launch_bounds__(kScanBlock) void k_scan_finish(const int32_t* __restrict__ in, int32_t* __restrict__ out,
+                                                            const int32_t* __restrict__ sums, int64_t n)
+{
+    const int64_t i = (int64_t)blockIdx.x * kScanBlock + threadIdx.x;
+    if (i >= n) return;
+    const int32_t v = out[i] + (blockIdx.x > 0 ? sums[blockIdx.x] : 0);
+    out[i] = v;
+    if (i == n - 1) out[n] = v + in[i];
+}
+
+// The whole scan in one workgroup, for at most kScanSmall elements: each thread
+// its own run of ITEMS (a multiple of 4) in registers.
+constexpr int64_t kScanSmall = 16 * kScanBlock;
+
+template <int ITEMS>
+__global__ __launch_bounds__(kScanBlock) void k_scan_small(const int32_t* __restrict__ in, int32_t* __restrict__ out, int n)
+{
+    __shared__ int32_t wave_tot[kScanBlock / 64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int i0 = (int)threadIdx.x * ITEMS;
+    int32_t v[ITEMS];
+#pragma unroll
+    for (int q = 0; q < ITEMS; q += 4) {
+        int4 x = make_int4(0, 0, 0, 0);
+        if (i0 + q + 3 < n) {
+            x = *(const int4*)(in + i0 + q);
+        } else {
+            if (i0 + q < n) x.x = in[i0 + q];
+            if (i0 + q + 1 < n) x.y = in[i0 + q + 1];
+            if (i0 + q + 2 < n) x.z = in[i0 + q + 2];
+        }
+        v[q] = x.x;
+        v[q + 1] = x.y;
+        v[q + 2] = x.z;
+        v[q + 3] = x.w;
+    }
+    int32_t sum = 0;
+#pragma unroll
+    for (int q = 0; q < ITEMS; ++q) sum += v[q];
+    int32_t x = sum;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int32_t y = __shfl_up(x, off, 64);
+        if (lane >= off) x += y;
+    }
+    if (lane == 63) wave_tot[wave] = x;
+    __syncthreads();
+    int32_t base = x - sum;
+    for (int w = 0; w < wave; ++w) base += wave_tot[w];
+#pragma unroll
+    for (int q = 0; q < ITEMS; ++q) {
+        const int i = i0 + q;
+        if (i < n) out[i] = base;
+        base += v[q];
+        if (i == n - 1) out[n] = base;
+    }
+}
+
 // Exclusive scan of in[0..n) into out[0..n]; out[n] = total. levels holds the
 // per-level block-sum buffers sized at handle creation.
 static hipError_t scan_exclusive(irbe_ctx* h, const int32_t* in, int32_t* out, int64_t n)
 {
+    if (n <= kScanSmall) {
+        if (n <= 4 * kScanBlock) k_scan_small<4><<<1, kScanBlock, 0, h->stream>>>(in, out, (int)n);
+        else k_scan_small<16><<<1, kScanBlock, 0, h->stream>>>(in, out, (int)n);
+        return hipGetLastError();
+    }
     const int64_t nb = blocks_for(n, kScanBlock);
     int32_t* sums = h->scan_levels[0];
     k_scan_block<<<(unsigned)nb, kScanBlock, 0, h->stream>>>(in, out, sums, n);
@@ -168,14 +232,8 @@ static hipError_t scan_exclusive(irbe_ctx* h, const int32_t* in, int32_t* out, i
         k_scan_add<<<(unsigned)blocks_for(m, kScanBlock), kScanBlock, 0, h->stream>>>(h->scan_levels[lv],
                                                                                       h->scan_levels[lv + 1], m);
     }
-    k_scan_add<<<(unsigned)nb, kScanBlock, 0, h->stream>>>(out, h->scan_levels[0], n);
-    // total: out[n] = out[n-1] + in[n-1]
+    k_scan_finish<<<(unsigned)nb, kScanBlock, 0, h->stream>>>(in, out, h->scan_levels[0], n);
     return hipGetLastError();
-}
-
-__global__ void k_scan_total(const int32_t* __restrict__ in, int32_t* __restrict__ out, int64_t n)
-{
-    if (threadIdx.x == 0 && blockIdx.x == 0) out[n] = n > 0 ? out[n - 1] + in[n - 1] : 0;
 }
 
 __global__ __launch_bounds__(kBlock) void k_scatter(int64_t n, const uint4* __restrict__ sq,
@@ -187,30 +245,6 @@ __global__ __launch_bounds__(kBlock) void k_scatter(int64_t n, const uint4* __re
     perm[cell_start[sq[i].w] + slot[i]] = (int32_t)i;
 }
 
-// Order each cell's atoms by (fixed-point x coordinate, atom id); sorting by x
-// lets the list build trim each atom's candidate range to its exact x extent.
-// Slot k of the cell-grouped order `in` holds atom i; its place in the cell is
-// the number of the cell's atoms with a smaller key (keys are distinct, as the
-// ids are): one thread per atom over the cell's few tens of atoms, whose loads
-// the threads of one cell share.
-__global__ __launch_bounds__(kBlock) void k_cell_rank(int64_t n, const int32_t* __restrict__ cell_start,
-                                                      const uint4* __restrict__ sq, const int32_t* __restrict__ in,
-                                                      int32_t* __restrict__ perm)
-{
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= n) return;
-    const int32_t i = in[k];
-    const uint4 si = sq[i];
-    const int32_t b = cell_start[si.w], e = cell_start[si.w + 1];
-    int32_t r = 0;
-    for (int32_t t = b; t < e; ++t) {
-        const int32_t u = in[t];
-        const uint32_t xu = sq[u].x;
-        r += (xu < si.x || (xu == si.x && u < i)) ? 1 : 0;
-    }
-    perm[b + r] = i;
-}
-
 // The FP32 pair kernels' record of an atom: the fixed-point coordinates and the
 // charge rounded to 19 mantissa bits (to nearest, ties away from zero), whose
 // freed 4 low bits carry the type (n_types <= 16).
@@ -220,32 +254,56 @@ __device__ __forceinline__ uint4 pos_charge_record(uint4 s, float q, int32_t typ
     return make_uint4(s.x, s.y, s.z, b | ((uint32_t)type & 15u));
 }
 
+// Order each cell's atoms by (fixed-point x coordinate, atom id); sorting by x
+// lets the list build trim its candidate ranges. Slot t of the cell-grouped
+// order `in` holds an atom; its place in the cell is the number of the cell's
+// atoms with a smaller key (keys are distinct, as the ids are): one thread per
+// atom over the cell's few tens of atoms, whose loads the threads of one cell
+// share. The thread then writes the atom's sorted records there (and, where it
+// opens a block of the list build, the block).
 template <typename real>
-__global__ __launch_bounds__(kBlock) void k_gather_sorted(int64_t n, const int32_t* __restrict__ perm,
-                                                          const uint4* __restrict__ sq,
-                                                          const int32_t* __restrict__ type,
-                                                          const real* __restrict__ q, const int32_t* __restrict__ mol,
-                                                          const int32_t* __restrict__ xoff,
-                                                          uint4* __restrict__ spos, real* __restrict__ sqr,
-                                                          uint4* __restrict__ spq, int32_t* __restrict__ smol,
-                                                          int2* __restrict__ sxr, int32_t* __restrict__ rank,
-                                                          int n_c, int32_t* __restrict__ brow)
+__global__ __launch_bounds__(kBlock) void k_cell_order(int64_t n, const int32_t* __restrict__ cell_start,
+                                                       const uint4* __restrict__ sq, const int32_t* __restrict__ in,
+                                                       int32_t* __restrict__ perm, const int32_t* __restrict__ type,
+                                                       const real* __restrict__ q, const int32_t* __restrict__ mol,
+                                                       const int32_t* __restrict__ xoff, uint4* __restrict__ spos,
+                                                       real* __restrict__ sqr, uint4* __restrict__ spq,
+                                                       int32_t* __restrict__ smol, int2* __restrict__ sxr,
+                                                       int32_t* __restrict__ rank, int n_c, int32_t* __restrict__ brow,
+                                                       int G, int gpr, int32_t* __restrict__ blk_start)
 {
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= n) return;
-    const int32_t i = perm[k];
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= n) return;
+    const int32_t i = in[t];
     const uint4 s = sq[i];
-    if (brow) {
-        // the cell's (z, y) at this build (s.w is the cell id)
-        const uint32_t row = s.w / (uint32_t)n_c;
-        brow[k] = (int32_t)(((row / (uint32_t)n_c) << 16) | (row % (uint32_t)n_c));
+    const int32_t b = cell_start[s.w], e = cell_start[s.w + 1];
+    int32_t r = 0;
+    for (int32_t u = b; u < e; ++u) {
+        const int32_t o = in[u];
+        const uint32_t xo = sq[o].x;
+        r += (xo < s.x || (xo == s.x && o < i)) ? 1 : 0;
     }
+    const int32_t k = b + r;
+    perm[k] = i;
+    // the cell's row (z, y) and x (s.w is the cell id)
+    const uint32_t row = s.w / (uint32_t)n_c;
+    if (brow) brow[k] = (int32_t)(((row / (uint32_t)n_c) << 16) | (row % (uint32_t)n_c));
     spos[k] = make_uint4(s.x, s.y, s.z, (uint32_t)type[i]);
     sqr[k] = q[i];
     if (std::is_same<real, float>::value) spq[k] = pos_charge_record(s, (float)q[i], type[i]);
     smol[k] = mol[i];
     sxr[k] = make_int2(xoff[i], xoff[i + 1] - xoff[i]);
-    rank[i] = (int32_t)k;
+    rank[i] = k;
+    if (gpr > 0) {
+        // blocks of 32 atoms of a segment (G consecutive cells of a cell row, at most the cells
+        // that keep a block's window within one period): those of the segment whose first atom
+        // is f take the slots floor(f / 32) + segment + 0, 1, ..., which are disjoint for any
+        // atom counts (at most n / 32 + segments slots, the unused ones stay 0)
+        const uint32_t g = (s.w - row * (uint32_t)n_c) / (uint32_t)G;
+        const int32_t f = cell_start[row * (uint32_t)n_c + g * (uint32_t)G];
+        const int32_t o = k - f;
+        if ((o & 31) == 0) blk_start[(f >> 5) + (int32_t)(row * (uint32_t)gpr + g) + (o >> 5)] = k + 1;
+    }
 }
 
 // Excluded partners as sorted indices (same layout as the caller-order table).
@@ -260,7 +318,10 @@ hipError_t launch_bin(irbe_ctx* h, const void* pos)
 {
     const int64_t n = h->cfg.n_atoms;
     const unsigned nb = (unsigned)blocks_for(n, kBlock);
-    hipError_t e = launch_fill_i32(h->stream, h->cell_count, 0, h->geo.n_cells);
+    // the list maxima, the cell counts and the block slots lie in one array
+    const bool blocks = !lists_by_lanes(h);
+    const int64_t slots = blocks ? list_block_slots(h->geo, h->stencil, n) : 0;
+    hipError_t e = launch_fill_i32(h->stream, h->maxcnt, 0, (h->cell_count - h->maxcnt) + h->geo.n_cells + slots);
     if (e != hipSuccess) return e;
     if (h->fp64)
         k_quantize_hist<double><<<nb, kBlock, 0, h->stream>>>(n, (const double*)pos, h->geo.inv_l, h->geo.n_c, h->sq,
@@ -270,37 +331,88 @@ hipError_t launch_bin(irbe_ctx* h, const void* pos)
                                                              h->cell_count, h->smol, h->err);
     e = scan_exclusive(h, h->cell_count, h->cell_start, h->geo.n_cells);
     if (e != hipSuccess) return e;
-    k_scan_total<<<1, 64, 0, h->stream>>>(h->cell_count, h->cell_start, h->geo.n_cells);
-    // the atoms grouped by cell into rank, each at the place its histogram atomic
-    // returned (held in smol), then each cell ordered into perm; rank and smol are
-    // free until k_gather_sorted rewrites them
-    k_scatter<<<nb, kBlock, 0, h->stream>>>(n, h->sq, h->cell_start, h->smol, h->rank);
-    k_cell_rank<<<nb, kBlock, 0, h->stream>>>(n, h->cell_start, h->sq, h->rank, h->perm);
+    // the atoms grouped by cell into nshell, each at the place its histogram atomic
+    // returned (held in smol), then each cell ordered; nshell and smol are free until
+    // the list build and k_cell_order rewrite them
+    k_scatter<<<nb, kBlock, 0, h->stream>>>(n, h->sq, h->cell_start, h->smol, h->nshell);
+    const ListBlockShape s = list_block_shape(h->geo, h->stencil);
+    const int gpr = blocks ? s.gpr : 0;
     if (h->fp64)
-        k_gather_sorted<double><<<nb, kBlock, 0, h->stream>>>(n, h->perm, h->sq, h->type_orig, (const double*)h->q_orig,
-                                                              h->mol_orig, h->xoff, h->spos, (double*)h->sq_r,
-                                                              nullptr, h->smol, h->sxr, h->rank, h->geo.n_c,
-                                                              h->brow);
+        k_cell_order<double><<<nb, kBlock, 0, h->stream>>>(n, h->cell_start, h->sq, h->nshell, h->perm, h->type_orig,
+                                                           (const double*)h->q_orig, h->mol_orig, h->xoff, h->spos,
+                                                           (double*)h->sq_r, nullptr, h->smol, h->sxr, h->rank,
+                                                           h->geo.n_c, h->brow, s.G, gpr, h->blk_start);
     else
-        k_gather_sorted<float><<<nb, kBlock, 0, h->stream>>>(n, h->perm, h->sq, h->type_orig, (const float*)h->q_orig,
-                                                             h->mol_orig, h->xoff, h->spos, (float*)h->sq_r, h->spq,
-                                                             h->smol, h->sxr, h->rank, h->geo.n_c, h->brow);
-    if (h->n_excl > 0)
+        k_cell_order<float><<<nb, kBlock, 0, h->stream>>>(n, h->cell_start, h->sq, h->nshell, h->perm, h->type_orig,
+                                                          (const float*)h->q_orig, h->mol_orig, h->xoff, h->spos,
+                                                          (float*)h->sq_r, h->spq, h->smol, h->sxr, h->rank,
+                                                          h->geo.n_c, h->brow, s.G, gpr, h->blk_start);
+    // (the block form of the list build writes the excluded partners' sorted indices itself)
+    if (!blocks && h->n_excl > 0)
         k_excl_sorted<<<(unsigned)blocks_for(h->n_excl, kBlock), kBlock, 0, h->stream>>>(h->n_excl, h->xidx, h->rank,
                                                                                         h->sxidx);
     return hipGetLastError();
 }
 
+// The k-vector draw: one thread per sample l draws m_l and its FP64 constants
+// kcoef[4l..4l+3] = (kx, ky, kz, c_l) with c_l = ke (S/p) 4 pi / (V k^2)
+// (Eqs. (2.6)-(2.8)): per axis by inverse CDF on 64-bit Philox words, the triple
+// (0,0,0) redrawn.
+struct KDraw {
+    int P, M;
+    uint64_t seed, step;
+    const uint64_t* U;
+    double two_pi_l, coef0;
+    int4* kvec;
+    double* kcoef;
+};
+
+__device__ void k_draw_sample(const KDraw& d, int l)
+{
+    WordStream st(d.seed, d.step, (uint32_t)l, kTagKspace);
+    int m[3];
+    do {
+        for (int a = 0; a < 3; ++a) {
+            const uint64_t hi = st.next();
+            const uint64_t lo = st.next();
+            const uint64_t u = (hi << 32) | lo;
+            // least t in [0, 2M] with u < U[t] (U is non-decreasing, U[2M] = max)
+            int a0 = 0, b0 = 2 * d.M;
+            while (a0 < b0) {
+                const int mid = (a0 + b0) >> 1;
+                if (u < d.U[mid]) b0 = mid;
+                else a0 = mid + 1;
+            }
+            m[a] = a0 - d.M;
+        }
+    } while (m[0] == 0 && m[1] == 0 && m[2] == 0);
+    d.kvec[l] = make_int4(m[0], m[1], m[2], 0);
+    const double kx = d.two_pi_l * m[0], ky = d.two_pi_l * m[1], kz = d.two_pi_l * m[2];
+    const double k2 = kx * kx + ky * ky + kz * kz;
+    d.kcoef[4 * l + 0] = kx;
+    d.kcoef[4 * l + 1] = ky;
+    d.kcoef[4 * l + 2] = kz;
+    d.kcoef[4 * l + 3] = d.coef0 / k2;
+}
+
 // Re-quantize positions for a force evaluation on the lists of the last build:
-// the sorted order (perm) is kept, positions and charges are refreshed.
+// the sorted order (perm) is kept, positions and charges are refreshed. The first
+// kd_blocks blocks draw the k-vectors instead (a chain of table look-ups that one
+// launch hides behind the atoms).
 template <typename real>
 __global__ __launch_bounds__(kBlock) void k_requantize(int64_t n, const real* __restrict__ pos, double inv_l,
                                                        const int32_t* __restrict__ rank,
                                                        const int32_t* __restrict__ type, const real* __restrict__ q,
                                                        uint4* __restrict__ sq, uint4* __restrict__ spos,
-                                                       real* __restrict__ sqr, uint4* __restrict__ spq, uint32_t* err)
+                                                       real* __restrict__ sqr, uint4* __restrict__ spq, uint32_t* err,
+                                                       int kd_blocks, KDraw kd)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if ((int)blockIdx.x < kd_blocks) {
+        const int l = (int)(blockIdx.x * kBlock + threadIdx.x);
+        if (l < kd.P) k_draw_sample(kd, l);
+        return;
+    }
+    const int64_t i = (int64_t)(blockIdx.x - kd_blocks) * blockDim.x + threadIdx.x;
     if (i >= n) return;
     bool bad = false;
     const uint32_t sx = quantize1((double)pos[3 * i + 0], inv_l, bad);
@@ -315,18 +427,25 @@ __global__ __launch_bounds__(kBlock) void k_requantize(int64_t n, const real* __
     if (bad) atomicOr(err, ERR_NONFINITE);
 }
 
-hipError_t launch_requantize(irbe_ctx* h, const void* pos)
+hipError_t launch_requantize(irbe_ctx* h, const void* pos, uint64_t step)
 {
     const int64_t n = h->cfg.n_atoms;
-    const unsigned nb = (unsigned)blocks_for(n, kBlock);
+    const int P = h->cfg.p_kspace;
+    const double L = h->cfg.box_length;
+    const double V = L * L * L;
+    const double pi = 3.14159265358979323846;
+    const KDraw kd{P, h->kM, h->cfg.seed, step, h->ktab, 2.0 * pi / L,
+                   h->cfg.coulomb_k * (h->kS / (double)P) * 4.0 * pi / V, h->kvec, h->kcoef};
+    const int kdb = (int)blocks_for(P, kBlock);
+    const unsigned nb = (unsigned)(blocks_for(n, kBlock) + kdb);
     if (h->fp64)
         k_requantize<double><<<nb, kBlock, 0, h->stream>>>(n, (const double*)pos, h->geo.inv_l, h->rank, h->type_orig,
                                                            (const double*)h->q_orig, h->sq, h->spos,
-                                                           (double*)h->sq_r, nullptr, h->err);
+                                                           (double*)h->sq_r, nullptr, h->err, kdb, kd);
     else
         k_requantize<float><<<nb, kBlock, 0, h->stream>>>(n, (const float*)pos, h->geo.inv_l, h->rank, h->type_orig,
                                                           (const float*)h->q_orig, h->sq, h->spos, (float*)h->sq_r,
-                                                          h->spq, h->err);
+                                                          h->spq, h->err, kdb, kd);
     return hipGetLastError();
 }
 

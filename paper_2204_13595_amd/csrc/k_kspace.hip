@@ -10,79 +10,51 @@
 //            in the caller's atom order.
 // Plus the adjoint (A_l = sum_m q_m (G_m . k_l) e^{i theta_ml}) and the
 // energy/virial finalisation.
+#include <algorithm>
+#include <type_traits>
+
 #include "irbe_device.hpp"
 #include "irbe_internal.hpp"
 
 namespace irbe {
 
-// Atoms per thread and k-vectors per block row of the structure-factor kernels
-// (measured optima at 3.1M atoms and p = 100: 16 atoms per thread in FP32, 8
-// k-vectors per row forward and 16 in the adjoint, whose row also carries A).
-template <typename real, bool ADJ>
-struct RhoShape {
-    static constexpr int atoms = sizeof(real) == 4 ? 16 : 8;
-    static constexpr int chunk = ADJ ? 16 : 8;
-};
+// k-vectors per block row of the structure-factor kernels (measured optima at 3.1M
+// atoms and p = 100: 8 forward and 16 in the adjoint, whose row also carries A).
+constexpr int rho_chunk(bool adj) { return adj ? 16 : 8; }
 
-// Blocks of the partial sums for the largest block count of any shape.
-int64_t rho_blocks(int64_t n) { return blocks_for(n, kBlock * kRhoAtomsPerThread); }
+// Atoms per thread: 16 in FP32 and 8 in FP64 (the optima at 3.1M atoms) while that
+// gives kRhoMinBlocks blocks, else a quarter, else one, so that small systems
+// still spread over the chip (2,703 atoms, p = 200: 25 blocks of 128 sines and
+// cosines per thread and k-vector row took 14 us).
+constexpr int64_t kRhoMinBlocks = 256;
+constexpr int rho_most(bool fp64) { return fp64 ? 8 : 16; }
 
-// One thread per sample l: draw m_l and its FP64 constants
-// kcoef[4l..4l+3] = (kx, ky, kz, c_l) with c_l = ke (S/p) 4 pi / (V k^2).
-__global__ void k_ksample(int P, uint64_t seed, uint64_t step, int M, const uint64_t* __restrict__ U, double two_pi_l,
-                          double coef0, int4* __restrict__ kvec, double* __restrict__ kcoef)
+int rho_atoms(const irbe_ctx* h, bool adj)
 {
-    const int l = blockIdx.x * blockDim.x + threadIdx.x;
-    if (l >= P) return;
-    WordStream st(seed, step, (uint32_t)l, kTagKspace);
-    int m[3];
-    do {
-        for (int a = 0; a < 3; ++a) {
-            const uint64_t hi = st.next();
-            const uint64_t lo = st.next();
-            const uint64_t u = (hi << 32) | lo;
-            // least t in [0, 2M] with u < U[t] (U is non-decreasing, U[2M] = max)
-            int a0 = 0, b0 = 2 * M;
-            while (a0 < b0) {
-                const int mid = (a0 + b0) >> 1;
-                if (u < U[mid]) b0 = mid;
-                else a0 = mid + 1;
-            }
-            m[a] = a0 - M;
-        }
-    } while (m[0] == 0 && m[1] == 0 && m[2] == 0);
-    kvec[l] = make_int4(m[0], m[1], m[2], 0);
-    const double kx = two_pi_l * m[0], ky = two_pi_l * m[1], kz = two_pi_l * m[2];
-    const double k2 = kx * kx + ky * ky + kz * kz;
-    kcoef[4 * l + 0] = kx;
-    kcoef[4 * l + 1] = ky;
-    kcoef[4 * l + 2] = kz;
-    kcoef[4 * l + 3] = coef0 / k2;
+    const int most = rho_most(h->fp64);
+    if (h->rho_wide) return most;
+    const int64_t rows = blocks_for(h->cfg.p_kspace, rho_chunk(adj));
+    for (int a = most; a > 1; a /= 4)
+        if (blocks_for(h->cfg.n_atoms, (int64_t)kBlock * a) * rows >= kRhoMinBlocks) return a;
+    return 1;
 }
 
-hipError_t launch_ksample(irbe_ctx* h, uint64_t step)
+// Blocks of partial sums: the larger count of the two shapes.
+int64_t rho_blocks(const irbe_ctx* h)
 {
-    const int P = h->cfg.p_kspace;
-    const double L = h->cfg.box_length;
-    const double V = L * L * L;
-    const double coef0 = h->cfg.coulomb_k * (h->kS / (double)P) * 4.0 * 3.14159265358979323846 / V;
-    k_ksample<<<(unsigned)blocks_for(P, 64), 64, 0, h->stream>>>(P, h->cfg.seed, step, h->kM, h->ktab,
-                                                                 2.0 * 3.14159265358979323846 / L, coef0, h->kvec,
-                                                                 h->kcoef);
-    return hipGetLastError();
+    return blocks_for(h->cfg.n_atoms, (int64_t)kBlock * std::min(rho_atoms(h, false), rho_atoms(h, true)));
 }
 
 // Partial structure factors: block (b, c) sums atoms [b*kBlock*A, ...) for the
 // k-vectors of chunk c. part layout: [(l * nb + b) * NV + v], NV = 2 (rho) or
 // 4 (rho and A).
-template <typename real, bool ADJ>
+template <typename real, bool ADJ, int A>
 __global__ __launch_bounds__(kBlock) void k_rho_partial(int64_t n, int P, const uint4* __restrict__ sq,
                                                         const real* __restrict__ q, const int4* __restrict__ kvec,
                                                         const double* __restrict__ kcoef, const real* __restrict__ G,
                                                         double* __restrict__ part)
 {
-    constexpr int A = RhoShape<real, ADJ>::atoms;
-    constexpr int RC = RhoShape<real, ADJ>::chunk;
+    constexpr int RC = rho_chunk(ADJ);
     constexpr int NV = ADJ ? 4 : 2;
     __shared__ double lds[NV * RC * (kBlock / 64)];
     const int64_t nb = gridDim.x;
@@ -194,34 +166,34 @@ __global__ __launch_bounds__(kReduceBlock) void k_rho_final(int64_t nb, const do
     }
 }
 
-template <typename real>
-static hipError_t launch_rho_t(irbe_ctx* h, const void* grad, bool adj)
+template <typename real, bool ADJ, int A>
+static hipError_t launch_rho_a(irbe_ctx* h, const void* grad)
 {
     const int64_t n = h->cfg.n_atoms;
     const int P = h->cfg.p_kspace;
-    if (adj) {
-        using S = RhoShape<real, true>;
-        const int64_t nb = blocks_for(n, kBlock * S::atoms);
-        const dim3 grid((unsigned)nb, (unsigned)((P + S::chunk - 1) / S::chunk));
-        k_rho_partial<real, true><<<grid, kBlock, 0, h->stream>>>(n, P, h->sq, (const real*)h->q_orig, h->kvec,
-                                                                   h->kcoef, (const real*)grad, h->rho_part);
-        k_rho_final<real, true><<<P, kReduceBlock, 0, h->stream>>>(nb, h->rho_part, h->kcoef, h->rho, h->Avec,
-                                                                    h->kadj);
-    } else {
-        using S = RhoShape<real, false>;
-        const int64_t nb = blocks_for(n, kBlock * S::atoms);
-        const dim3 grid((unsigned)nb, (unsigned)((P + S::chunk - 1) / S::chunk));
-        k_rho_partial<real, false><<<grid, kBlock, 0, h->stream>>>(n, P, h->sq, (const real*)h->q_orig, h->kvec,
-                                                                    h->kcoef, nullptr, h->rho_part);
-        k_rho_final<real, false><<<P, kReduceBlock, 0, h->stream>>>(nb, h->rho_part, h->kcoef, h->rho, h->Avec,
-                                                                     h->kforce);
-    }
+    const int64_t nb = blocks_for(n, kBlock * A);
+    const dim3 grid((unsigned)nb, (unsigned)((P + rho_chunk(ADJ) - 1) / rho_chunk(ADJ)));
+    k_rho_partial<real, ADJ, A><<<grid, kBlock, 0, h->stream>>>(n, P, h->sq, (const real*)h->q_orig, h->kvec, h->kcoef,
+                                                                 (const real*)grad, h->rho_part);
+    k_rho_final<real, ADJ><<<P, kReduceBlock, 0, h->stream>>>(nb, h->rho_part, h->kcoef, h->rho, h->Avec,
+                                                               ADJ ? h->kadj : h->kforce);
     return hipGetLastError();
+}
+
+template <typename real, bool ADJ>
+static hipError_t launch_rho_t(irbe_ctx* h, const void* grad)
+{
+    constexpr int most = rho_most(sizeof(real) == 8);
+    const int a = rho_atoms(h, ADJ);
+    if (a == most) return launch_rho_a<real, ADJ, most>(h, grad);
+    if (a == most / 4) return launch_rho_a<real, ADJ, most / 4>(h, grad);
+    return launch_rho_a<real, ADJ, 1>(h, grad);
 }
 
 hipError_t launch_rho(irbe_ctx* h, const void* grad, bool with_adjoint)
 {
-    return h->fp64 ? launch_rho_t<double>(h, grad, with_adjoint) : launch_rho_t<float>(h, grad, with_adjoint);
+    if (with_adjoint) return h->fp64 ? launch_rho_t<double, true>(h, grad) : launch_rho_t<float, true>(h, grad);
+    return h->fp64 ? launch_rho_t<double, false>(h, nullptr) : launch_rho_t<float, false>(h, nullptr);
 }
 
 // Per atom (caller order): F_i = F_i^sr - F^corr + F_i^long,* with
@@ -255,21 +227,126 @@ __global__ __launch_bounds__(kBlock) void k_kspace_forces(int64_t n, int P, cons
     force[3 * i + 2] = fsr[3 * k + 2] - (real)fcorr[2] - qi * fz;
 }
 
-hipError_t launch_kspace_forces(irbe_ctx* h, void* force)
+// k-vectors whose constants a block of the lanes-per-atom kernels stages in LDS.
+constexpr int kKspaceTile = 128;
+
+// Value of lane J of the group of LPA lanes (4 or 16) that this lane belongs to.
+template <int LPA, int J>
+__device__ __forceinline__ int group_bcast(int v)
+{
+    // quad_perm (J, J, J, J) or row_newbcast:J
+    constexpr int ctrl = LPA == 4 ? J * 0x55 : 0x150 + J;
+    return __builtin_amdgcn_update_dpp(0, v, ctrl, 0xf, 0xf, true);
+}
+template <int LPA, int J>
+__device__ __forceinline__ float group_bcast(float v)
+{
+    return __int_as_float(group_bcast<LPA, J>(__float_as_int(v)));
+}
+template <int LPA, int J>
+__device__ __forceinline__ double group_bcast(double v)
+{
+    const long long b = __double_as_longlong(v);
+    const int lo = group_bcast<LPA, J>((int)(b & 0xffffffffll)), hi = group_bcast<LPA, J>((int)(b >> 32));
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
+// The same with LPA lanes per atom, for systems that leave the chip idle at one
+// thread per atom: the lanes evaluate the sines and cosines of LPA k-vectors at
+// once and then all add the LPA terms in the k-vectors' order (the additions of
+// the form above, bit for bit).
+template <typename real, int LPA>
+__global__ __launch_bounds__(kBlock) void k_kspace_forces_lanes(
+    int64_t n, int P, const uint4* __restrict__ sq, const real* __restrict__ q, const int32_t* __restrict__ rank,
+    const real* __restrict__ fsr, const int4* __restrict__ kvec, const KForce<real>* __restrict__ kf,
+    const double* __restrict__ fcorr, real* __restrict__ force)
+{
+    __shared__ int4 km[kKspaceTile];
+    __shared__ KForce<real> kc[kKspaceTile];
+    const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const int64_t i = min(t / LPA, n - 1);
+    const int ln = (int)(threadIdx.x % LPA);
+    const uint4 s = sq[i];
+    real fx = 0, fy = 0, fz = 0;
+    for (int l0 = 0; l0 < P; l0 += kKspaceTile) {
+        const int cnt = min(kKspaceTile, P - l0);
+        __syncthreads();
+        for (int l = threadIdx.x; l < kKspaceTile; l += kBlock) {
+            // (terms past the last k-vector are exact zeros)
+            km[l] = l < cnt ? kvec[l0 + l] : make_int4(0, 0, 0, 0);
+            kc[l] = l < cnt ? kf[l0 + l] : KForce<real>{};
+        }
+        __syncthreads();
+        for (int l = 0; l < cnt; l += LPA) {
+            real sn, cs;
+            const int4 m = km[l + ln];
+            Math<real>::sincos_rev(phase_rev<real>(m.x, m.y, m.z, s.x, s.y, s.z), &sn, &cs);
+            const real g = cs * kc[l + ln].a - sn * kc[l + ln].b;
+            auto add = [&](auto j) {
+                constexpr int J = decltype(j)::value;
+                const real gj = group_bcast<LPA, J>(g);
+                fx += gj * kc[l + J].kx;
+                fy += gj * kc[l + J].ky;
+                fz += gj * kc[l + J].kz;
+            };
+            add(std::integral_constant<int, 0>{});
+            add(std::integral_constant<int, 1>{});
+            add(std::integral_constant<int, 2>{});
+            add(std::integral_constant<int, 3>{});
+            if constexpr (LPA == 16) {
+                add(std::integral_constant<int, 4>{});
+                add(std::integral_constant<int, 5>{});
+                add(std::integral_constant<int, 6>{});
+                add(std::integral_constant<int, 7>{});
+                add(std::integral_constant<int, 8>{});
+                add(std::integral_constant<int, 9>{});
+                add(std::integral_constant<int, 10>{});
+                add(std::integral_constant<int, 11>{});
+                add(std::integral_constant<int, 12>{});
+                add(std::integral_constant<int, 13>{});
+                add(std::integral_constant<int, 14>{});
+                add(std::integral_constant<int, 15>{});
+            }
+        }
+    }
+    if (ln != 0 || t / LPA >= n) return;
+    const real qi = q[i];
+    const int64_t k = rank[i];
+    force[3 * i + 0] = fsr[3 * k + 0] - (real)fcorr[0] - qi * fx;
+    force[3 * i + 1] = fsr[3 * k + 1] - (real)fcorr[1] - qi * fy;
+    force[3 * i + 2] = fsr[3 * k + 2] - (real)fcorr[2] - qi * fz;
+}
+
+// Lanes per atom of the k-space kernels: one while that gives the chip its waves
+// (131,072 atoms: two waves on each of 1,024 SIMDs), four below, sixteen for the
+// smallest systems. One against several lanes, forces, p = 200: 45 -> 28 us at
+// 98,304 atoms (4), 43 -> 7.1 us at 2,703 atoms (16); FP64, p = 100, 98,304 atoms:
+// 48 -> 27 us. The several lanes repeat the additions, so a full chip loses by them.
+static int kspace_lanes(const irbe_ctx* h)
 {
     const int64_t n = h->cfg.n_atoms;
-    const unsigned nb = (unsigned)blocks_for(n, kBlock);
-    if (h->fp64)
-        k_kspace_forces<double><<<nb, kBlock, 0, h->stream>>>(n, h->cfg.p_kspace, h->sq, (const double*)h->q_orig,
-                                                              h->rank, (const double*)h->fsr, h->kvec,
-                                                              (const KForce<double>*)h->kforce, h->fcorr,
-                                                              (double*)force);
-    else
-        k_kspace_forces<float><<<nb, kBlock, 0, h->stream>>>(n, h->cfg.p_kspace, h->sq, (const float*)h->q_orig,
-                                                             h->rank, (const float*)h->fsr, h->kvec,
-                                                             (const KForce<float>*)h->kforce, h->fcorr,
-                                                             (float*)force);
+    return n >= 131072 ? 1 : (n >= 16384 ? 4 : 16);
+}
+
+template <typename real>
+static hipError_t launch_kspace_forces_t(irbe_ctx* h, void* force)
+{
+    const int64_t n = h->cfg.n_atoms;
+    const int lpa = kspace_lanes(h);
+    const unsigned nb = (unsigned)blocks_for(n * lpa, kBlock);
+#define IRBE_KSPACE_ARGS                                                                                             \
+    n, h->cfg.p_kspace, h->sq, (const real*)h->q_orig, h->rank, (const real*)h->fsr, h->kvec,                        \
+        (const KForce<real>*)h->kforce, h->fcorr, (real*)force
+    if (lpa == 1) k_kspace_forces<real><<<nb, kBlock, 0, h->stream>>>(IRBE_KSPACE_ARGS);
+    else if (lpa == 4) k_kspace_forces_lanes<real, 4><<<nb, kBlock, 0, h->stream>>>(IRBE_KSPACE_ARGS);
+    else k_kspace_forces_lanes<real, 16><<<nb, kBlock, 0, h->stream>>>(IRBE_KSPACE_ARGS);
+#undef IRBE_KSPACE_ARGS
     return hipGetLastError();
+}
+
+hipError_t launch_kspace_forces(irbe_ctx* h, void* force)
+{
+    return h->fp64 ? launch_kspace_forces_t<double>(h, force) : launch_kspace_forces_t<float>(h, force);
 }
 
 // ev[0..10] = U_coul, U_lj, U_long, U_self, U_excl, W_xx, W_yy, W_zz, W_xy, W_xz, W_yz.
@@ -377,7 +454,9 @@ hipError_t launch_gather_grad(irbe_ctx* h, const void* grad)
 // Per atom (caller order): the k-space adjoint plus the short-range parts.
 //   dL/dr_n = -ke q_n sum_l c_l k_l [Re(e^{i th} conj A_l) - g_nl Re(e^{-i th} rho_l)]
 //   dL/dq_n = -ke sum_l c_l [Im(e^{i th} conj A_l) + g_nl Im(e^{-i th} rho_l)]
-template <typename real>
+// LPA lanes per atom (1, 4 or 16) take every LPA-th k-vector; their sums are then
+// added in the group.
+template <typename real, int LPA>
 __global__ __launch_bounds__(kBlock) void k_kspace_adjoint(int64_t n, int P, const uint4* __restrict__ sq,
                                                            const real* __restrict__ q, const real* __restrict__ G,
                                                            const int32_t* __restrict__ rank,
@@ -389,12 +468,15 @@ __global__ __launch_bounds__(kBlock) void k_kspace_adjoint(int64_t n, int P, con
                                                            const real* __restrict__ gqscat, real* __restrict__ gpos,
                                                            real* __restrict__ gq)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
+    const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (LPA == 1 && t >= n) return;
+    const int64_t i = LPA == 1 ? t : min(t / LPA, n - 1);
+    const int ln = LPA == 1 ? 0 : (int)(threadIdx.x % LPA);
     const uint4 s = sq[i];
     const real gx = G[3 * i], gy = G[3 * i + 1], gz = G[3 * i + 2];
     real px = 0, py = 0, pz = 0, pq = 0;
-    for (int l = 0; l < P; ++l) {
+#pragma unroll LPA > 1 ? 4 : 1
+    for (int l = ln; l < P; l += LPA) {
         const int4 m = kvec[l];
         const KAdj<real> c = ka[l];
         real sn, cs;
@@ -404,12 +486,28 @@ __global__ __launch_bounds__(kBlock) void k_kspace_adjoint(int64_t n, int P, con
         const real eA_im = sn * c.ar - cs * c.ai;
         const real er_re = cs * c.rr + sn * c.ri;
         const real er_im = cs * c.ri - sn * c.rr;
-        const real t = eA_re - g * er_re;
-        px += t * c.kx;
-        py += t * c.ky;
-        pz += t * c.kz;
+        const real tt = eA_re - g * er_re;
+        px += tt * c.kx;
+        py += tt * c.ky;
+        pz += tt * c.kz;
         pq += eA_im + g * er_im;
     }
+    auto group_sum = [](real v) {
+        if (LPA == 16) {
+            v = butterfly_add<8>(v);
+            v = butterfly_add<4>(v);
+        }
+        if (LPA >= 4) {
+            v = butterfly_add<2>(v);
+            v = butterfly_add<1>(v);
+        }
+        return v;
+    };
+    px = group_sum(px);
+    py = group_sum(py);
+    pz = group_sum(pz);
+    pq = group_sum(pq);
+    if (LPA > 1 && (ln != 0 || t / LPA >= n)) return;
     const real qi = q[i];
     const int64_t k = rank[i];
     gpos[3 * i + 0] = gself[3 * k + 0] + gscat[3 * k + 0] - qi * px;
@@ -421,6 +519,7 @@ __global__ __launch_bounds__(kBlock) void k_kspace_adjoint(int64_t n, int P, con
 // LJ table gradients: fixed-order two-stage sum of the per-block partials
 // (slices of contiguous blocks, then the slices).
 constexpr int kLjSlices = 256;
+constexpr int64_t kLjDirect = 2 * kReduceBlock;
 
 __global__ __launch_bounds__(kReduceBlock) void k_lj_reduce1(int64_t nb, const double* __restrict__ part,
                                                              double* __restrict__ slices)
@@ -438,14 +537,14 @@ __global__ __launch_bounds__(kReduceBlock) void k_lj_reduce1(int64_t nb, const d
     if (threadIdx.x < NLJ) slices[blockIdx.x * NLJ + threadIdx.x] = o;
 }
 
-__global__ __launch_bounds__(kReduceBlock) void k_lj_reduce2(const double* __restrict__ slices, int n_types,
-                                                             double* __restrict__ out)
+__global__ __launch_bounds__(kReduceBlock) void k_lj_reduce2(int n_slices, const double* __restrict__ slices,
+                                                             int n_types, double* __restrict__ out)
 {
     constexpr int NLJ = 2 * kMaxTypesGrad * kMaxTypesGrad;
     __shared__ double lds[NLJ * (kReduceBlock / 64)];
     double vals[NLJ];
     for (int v = 0; v < NLJ; ++v) vals[v] = 0.0;
-    for (int b = threadIdx.x; b < kLjSlices; b += kReduceBlock)
+    for (int b = threadIdx.x; b < n_slices; b += kReduceBlock)
         for (int v = 0; v < NLJ; ++v) vals[v] += slices[b * NLJ + v];
     double o;
     block_sum_vec<NLJ, kReduceBlock>(vals, lds, threadIdx.x, o);
@@ -458,24 +557,35 @@ __global__ __launch_bounds__(kReduceBlock) void k_lj_reduce2(const double* __res
     }
 }
 
-hipError_t launch_kspace_adjoint(irbe_ctx* h, const void* grad, void* grad_pos, void* grad_q, double* grad_lj)
+template <typename real>
+static hipError_t launch_kspace_adjoint_t(irbe_ctx* h, const void* grad, void* grad_pos, void* grad_q)
 {
     const int64_t n = h->cfg.n_atoms;
-    const unsigned nb = (unsigned)blocks_for(n, kBlock);
-    if (h->fp64)
-        k_kspace_adjoint<double><<<nb, kBlock, 0, h->stream>>>(
-            n, h->cfg.p_kspace, h->sq, (const double*)h->q_orig, (const double*)grad, h->rank, h->kvec,
-            (const KAdj<double>*)h->kadj, (const double*)h->gself, (const double*)h->gscat, (const double*)h->gqself,
-            (const double*)h->gqscat, (double*)grad_pos, (double*)grad_q);
-    else
-        k_kspace_adjoint<float><<<nb, kBlock, 0, h->stream>>>(
-            n, h->cfg.p_kspace, h->sq, (const float*)h->q_orig, (const float*)grad, h->rank, h->kvec,
-            (const KAdj<float>*)h->kadj, (const float*)h->gself, (const float*)h->gscat, (const float*)h->gqself,
-            (const float*)h->gqscat, (float*)grad_pos, (float*)grad_q);
-    if (grad_lj) {
-        k_lj_reduce1<<<kLjSlices, kReduceBlock, 0, h->stream>>>(h->adj_nb, h->ljpart, h->lj_slices);
-        k_lj_reduce2<<<1, kReduceBlock, 0, h->stream>>>(h->lj_slices, h->cfg.n_types, grad_lj);
+    const int lpa = kspace_lanes(h);
+    const unsigned nb = (unsigned)blocks_for(n * lpa, kBlock);
+#define IRBE_KADJ_ARGS                                                                                              \
+    n, h->cfg.p_kspace, h->sq, (const real*)h->q_orig, (const real*)grad, h->rank, h->kvec,                          \
+        (const KAdj<real>*)h->kadj, (const real*)h->gself, (const real*)h->gscat, (const real*)h->gqself,            \
+        (const real*)h->gqscat, (real*)grad_pos, (real*)grad_q
+    if (lpa == 1) k_kspace_adjoint<real, 1><<<nb, kBlock, 0, h->stream>>>(IRBE_KADJ_ARGS);
+    else if (lpa == 4) k_kspace_adjoint<real, 4><<<nb, kBlock, 0, h->stream>>>(IRBE_KADJ_ARGS);
+    else k_kspace_adjoint<real, 16><<<nb, kBlock, 0, h->stream>>>(IRBE_KADJ_ARGS);
+#undef IRBE_KADJ_ARGS
+    return hipGetLastError();
+}
+
+hipError_t launch_kspace_adjoint(irbe_ctx* h, const void* grad, void* grad_pos, void* grad_q, double* grad_lj)
+{
+    const hipError_t e = h->fp64 ? launch_kspace_adjoint_t<double>(h, grad, grad_pos, grad_q)
+                                 : launch_kspace_adjoint_t<float>(h, grad, grad_pos, grad_q);
+    if (e != hipSuccess || !grad_lj) return e;
+    if (h->adj_nb <= kLjDirect) {
+        // few blocks: summed in one launch, as slices of one block each
+        k_lj_reduce2<<<1, kReduceBlock, 0, h->stream>>>((int)h->adj_nb, h->ljpart, h->cfg.n_types, grad_lj);
+        return hipGetLastError();
     }
+    k_lj_reduce1<<<kLjSlices, kReduceBlock, 0, h->stream>>>(h->adj_nb, h->ljpart, h->lj_slices);
+    k_lj_reduce2<<<1, kReduceBlock, 0, h->stream>>>(kLjSlices, h->lj_slices, h->cfg.n_types, grad_lj);
     return hipGetLastError();
 }
 

@@ -46,11 +46,13 @@
 
 namespace irbe {
 
-constexpr int kMaskBlock = 256;  // threads per block of atoms
-constexpr int kMaskWaves = kMaskBlock / 64;
+// Threads per block of atoms: four wavefronts, and eight where the stencil wraps
+// the box, as those are the smallest systems, of fewer blocks than the chip has
+// compute units (2,703 atoms: 128 blocks, 54 us with four).
+constexpr int mask_threads(bool narrow) { return narrow ? 256 : 512; }
 constexpr int kMaskWords = 128;  // words per tile (two per lane when the masks are read back by atom)
 constexpr int kMaskMaxRow = 1024;  // candidates of one stencil row beyond which shell lists are not kept as masks
-constexpr int kMaskRows = kMaskBlock / 2;  // stencil rows per pass (two index ranges each)
+constexpr int kMaskRows = 128;  // stencil rows per pass (two index ranges each)
 constexpr float kMaskUnit = 64.0f;  // the list radius in the units of the half-precision coordinates
 constexpr float kMaskNorm = 64.0f;  // the norms are carried divided by this
 
@@ -126,12 +128,14 @@ struct MaskSeg {
 };
 
 template <int MODE, bool NARROW, bool MASK>
-__global__ __launch_bounds__(kMaskBlock, 4) void k_list_blocks(ListBlockArgs p)
+__global__ __launch_bounds__(mask_threads(NARROW), NARROW ? 4 : 2) void k_list_blocks(ListBlockArgs p)
 {
+    constexpr int kMaskBlock = mask_threads(NARROW);
+    constexpr int kMaskWaves = kMaskBlock / 64;
     constexpr bool kTwo = MODE == kListsSplit || MODE == kListsSplitSkin;  // C(i) beside S(i)
     __shared__ uint32_t ms[kMaskWords][33];              // masks of the outer list (S(i), the full list, or C(i) alone)
     __shared__ uint32_t mc[kTwo ? kMaskWords : 1][33];   // masks of C(i)
-    __shared__ MaskSeg seg[kMaskBlock];
+    __shared__ MaskSeg seg[2 * kMaskRows];
     __shared__ int2 wt[2 * kMaskWords];                  // a half word's first candidate and number of candidates
     __shared__ uint4 cpos[NARROW ? 1 : kMaskWaves][NARROW ? 1 : 64];
     __shared__ int wsum[kMaskWaves];
@@ -160,8 +164,16 @@ __global__ __launch_bounds__(kMaskBlock, 4) void k_list_blocks(ListBlockArgs p)
     // the excluded partner this thread clears in the first round (its loads go out early)
     const int xa = tid & 31, xe = tid >> 5;
     const int2 xr = p.sxr[k0 + min(xa, na - 1)];
-    int xj = xe == 0 ? k0 + xa : (xe <= xr.y ? p.sxidx[xr.x + xe - 1] : -1);
-    if (xa >= na) xj = -1;
+    auto partner = [&](int e) {
+        // entry e of the atom itself and its excluded partners, whose sorted indices are
+        // written for the pair kernels on the way
+        if (xa >= na || e > xr.y) return -1;
+        if (e == 0) return k0 + xa;
+        const int j = p.rank[p.xidx[xr.x + e - 1]];
+        p.sxidx[xr.x + e - 1] = j;
+        return j;
+    };
+    const int xj = partner(xe);
     uint4 xs = p.spos[max(xj, 0)];
     // centre and half extents of the block's bounding box
     const uint32_t bx = xlo + xext / 2;
@@ -207,7 +219,7 @@ __global__ __launch_bounds__(kMaskBlock, 4) void k_list_blocks(ListBlockArgs p)
         int sb = 0, sl = 0;
         {
             const int r = rb + (tid >> 1);
-            if (r < nrows) {
+            if (r < nrows && tid < 2 * kMaskRows) {
                 // (r / span: r and span are small enough for the FP32 quotient)
                 const int rz = (int)(((float)r + 0.5f) * p.inv_span);
                 const int dz = lo + rz, dy = lo + r - rz * span;
@@ -265,7 +277,7 @@ __global__ __launch_bounds__(kMaskBlock, 4) void k_list_blocks(ListBlockArgs p)
             total += wsum[w];
         }
         w0 += inc - wn;
-        seg[tid] = MaskSeg{sb, sl, w0};
+        if (tid < 2 * kMaskRows) seg[tid] = MaskSeg{sb, sl, w0};
         const int wend = wbase + ((total + 1) >> 1);
         for (int t0 = wbase; t0 < wend; t0 += kMaskWords) {
             const int tw = min(kMaskWords, wend - t0);  // words of this tile
@@ -396,7 +408,7 @@ __global__ __launch_bounds__(kMaskBlock, 4) void k_list_blocks(ListBlockArgs p)
                 int j = xj;
                 uint4 sj = xs;
                 if (e != xe) {
-                    j = e <= xr.y && xa < na ? p.sxidx[xr.x + e - 1] : -1;
+                    j = partner(e);
                     sj = p.spos[max(j, 0)];
                 }
                 if (e <= xr.y && j >= 0) {
@@ -573,27 +585,6 @@ __global__ __launch_bounds__(kMaskBlock, 4) void k_list_blocks(ListBlockArgs p)
     }
 }
 
-// First atom (plus one) of every block of 32 atoms: the blocks of a segment (G
-// consecutive cells of a cell row, at most the cells that keep the block's
-// window within one period) start at its first atom s and take the slots
-// floor(s / 32) + segment + 0, 1, ..., which are disjoint for any atom counts
-// (at most n / 32 + segments slots, the unused ones stay 0).
-__global__ __launch_bounds__(kBlock) void k_block_starts(int64_t n, int n_c, int G, int gpr,
-                                                         const uint4* __restrict__ spos,
-                                                         const int32_t* __restrict__ cell_start,
-                                                         int32_t* __restrict__ blk_start)
-{
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= n) return;
-    const uint4 s = spos[k];
-    auto cell_of = [&](uint32_t v) { return (int)(((uint64_t)v * (uint32_t)n_c) >> 32); };
-    const int row = cell_of(s.z) * n_c + cell_of(s.y);
-    const int g = cell_of(s.x) / G;
-    const int first = cell_start[row * n_c + g * G];
-    const int o = (int)k - first;
-    if ((o & 31) == 0) blk_start[(first >> 5) + row * gpr + g + (o >> 5)] = (int32_t)k + 1;
-}
-
 ListBlockShape list_block_shape(const Geometry& geo, bool core_only)
 {
     ListBlockShape s;
@@ -655,10 +646,6 @@ hipError_t launch_list_blocks(irbe_ctx* h)
     const ListBlockShape s = list_block_shape(g, h->stencil);
     const int64_t n = h->cfg.n_atoms;
     const int64_t slots = list_block_slots(g, h->stencil, n);
-    hipError_t e = launch_fill_i32(h->stream, h->blk_start, 0, slots);
-    if (e != hipSuccess) return e;
-    k_block_starts<<<(unsigned)blocks_for(n, kBlock), kBlock, 0, h->stream>>>(n, g.n_c, s.G, s.gpr, h->spos,
-                                                                             h->cell_start, h->blk_start);
     ListBlockArgs p{};
     p.n_c = g.n_c;
     p.lo = s.lo;
@@ -687,6 +674,8 @@ hipError_t launch_list_blocks(irbe_ctx* h)
     p.blk_start = h->blk_start;
     p.sxr = h->sxr;
     p.sxidx = h->sxidx;
+    p.xidx = h->xidx;
+    p.rank = h->rank;
     p.core = h->core;
     p.ncore = h->ncore;
     p.shell = h->shell;
@@ -701,8 +690,8 @@ hipError_t launch_list_blocks(irbe_ctx* h)
     auto run = [&](auto mode, auto mask) {
         constexpr int M = decltype(mode)::value;
         constexpr bool K = decltype(mask)::value;
-        if (s.narrow) k_list_blocks<M, true, K><<<(unsigned)slots, kMaskBlock, 0, h->stream>>>(p);
-        else k_list_blocks<M, false, K><<<(unsigned)slots, kMaskBlock, 0, h->stream>>>(p);
+        if (s.narrow) k_list_blocks<M, true, K><<<(unsigned)slots, mask_threads(true), 0, h->stream>>>(p);
+        else k_list_blocks<M, false, K><<<(unsigned)slots, mask_threads(false), 0, h->stream>>>(p);
     };
     using std::false_type;
     using std::true_type;

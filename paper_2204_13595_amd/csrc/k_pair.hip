@@ -1315,6 +1315,9 @@ static hipError_t launch_coop_r(irbe_ctx* h, uint64_t step, bool ev)
 // slices: ev_pair[0..11] = totals, fcorr = (sum of the uncorrected short-range
 // force) / N when rbl.
 constexpr int kReduceSlices = 256;
+// blocks up to which the second stage sums the partials itself: four per thread,
+// one launch of about 5 us in place of two
+constexpr int64_t kReduceDirect = 4 * kReduceBlock;
 
 template <int NV>
 __global__ __launch_bounds__(kReduceBlock) void k_pair_reduce1(int64_t nb, const double* __restrict__ part,
@@ -1333,15 +1336,16 @@ __global__ __launch_bounds__(kReduceBlock) void k_pair_reduce1(int64_t nb, const
 }
 
 template <int NV>
-__global__ __launch_bounds__(kReduceBlock) void k_pair_reduce2(int n_slices, const double* __restrict__ slices,
-                                                               int64_t n, int rbl, double* __restrict__ ev_pair,
+__global__ __launch_bounds__(kReduceBlock) void k_pair_reduce2(int n_slices, int stride,
+                                                               const double* __restrict__ slices, int64_t n, int rbl,
+                                                               double* __restrict__ ev_pair,
                                                                double* __restrict__ fcorr)
 {
     __shared__ double lds[NV * (kReduceBlock / 64)];
     double vals[NV];
     for (int c = 0; c < NV; ++c) vals[c] = 0.0;
     for (int b = threadIdx.x; b < n_slices; b += kReduceBlock)
-        for (int c = 0; c < NV; ++c) vals[c] += slices[b * 12 + c];
+        for (int c = 0; c < NV; ++c) vals[c] += slices[b * stride + c];
     double out;
     block_sum_vec<NV, kReduceBlock>(vals, lds, threadIdx.x, out);
     if (threadIdx.x < NV) ev_pair[threadIdx.x] = out;
@@ -1350,11 +1354,18 @@ __global__ __launch_bounds__(kReduceBlock) void k_pair_reduce2(int n_slices, con
 
 hipError_t launch_pair_reduce(irbe_ctx* h, bool ev)
 {
-    // (without energies the blocks write the three force sums only)
+    // (without energies the blocks write the three force sums only; few blocks are summed
+    // in one launch, as slices of one block each)
     auto run = [&](auto nv) {
         constexpr int NV = decltype(nv)::value;
+        if (h->pair_nb <= kReduceDirect) {
+            k_pair_reduce2<NV><<<1, kReduceBlock, 0, h->stream>>>((int)h->pair_nb, kPairPartials, h->pair_part,
+                                                                  h->cfg.n_atoms, h->full_list ? 0 : 1, h->ev_pair,
+                                                                  h->fcorr);
+            return;
+        }
         k_pair_reduce1<NV><<<kReduceSlices, kReduceBlock, 0, h->stream>>>(h->pair_nb, h->pair_part, h->pair_slices);
-        k_pair_reduce2<NV><<<1, kReduceBlock, 0, h->stream>>>(kReduceSlices, h->pair_slices, h->cfg.n_atoms,
+        k_pair_reduce2<NV><<<1, kReduceBlock, 0, h->stream>>>(kReduceSlices, 12, h->pair_slices, h->cfg.n_atoms,
                                                               h->full_list ? 0 : 1, h->ev_pair, h->fcorr);
     };
     if (ev) run(std::integral_constant<int, 12>{});
@@ -2050,9 +2061,9 @@ hipError_t launch_pair_adjoint(irbe_ctx* h, uint64_t step, bool want_q, bool wan
 {
     (void)want_q;
     const int64_t n = h->cfg.n_atoms;
-    hipError_t e = launch_fill_bytes0(h->stream, h->gscat, 3 * (size_t)n * h->real_size);
-    if (e != hipSuccess) return e;
-    e = launch_fill_bytes0(h->stream, h->gqscat, (size_t)n * h->real_size);
+    // the scatter sums, the buckets' cursors and the atomics counter lie in one array
+    const int64_t rows = (int64_t)h->geo.n_c * h->geo.n_c;
+    hipError_t e = launch_fill_bytes0(h->stream, h->gscat, 4 * (size_t)n * h->real_size + (2 * (size_t)rows + 1) * 8);
     if (e != hipSuccess) return e;
     // bucketed transpose of the shell scatter when a block of >= 8 atoms' records
     // fits the LDS staging area and the keys fit their table
@@ -2091,13 +2102,8 @@ hipError_t launch_pair_adjoint(irbe_ctx* h, uint64_t step, bool want_q, bool wan
     size_t lds = 0;
     if (use_bk) {
         bk.p9 = 9 * (int64_t)p_eff;
-        const int64_t rows = (int64_t)bk.n_c * bk.n_c;
         const int64_t total = ((int64_t)n * bk.p9 >> 3) + (int64_t)kBucketSlack * (rows + 1);
         e = ensure_buckets(h, total);
-        if (e != hipSuccess) return e;
-        e = launch_fill_i32(h->stream, (int32_t*)h->bk_cursor, 0, 4 * rows);
-        if (e != hipSuccess) return e;
-        e = launch_fill_i32(h->stream, (int32_t*)h->adj_atomics, 0, 2);
         if (e != hipSuccess) return e;
         bk.n_atomic = h->adj_atomics;
         bk.brow = h->geo.skin ? h->brow : nullptr;
