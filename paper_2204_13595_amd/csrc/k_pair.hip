@@ -199,7 +199,8 @@ __device__ __forceinline__ void add_pair(PairSum<real>& a, uint4 si, real qi, ui
         a.fz += phi * dz;
     } else {
         separation(si, sj, pp.quantum, dx, dy, dz);
-        const real r2 = dx * dx + dy * dy + dz * dz;
+        // (written out, so that every kernel rounds the terms alike)
+        const real r2 = fma(dz, dz, fma(dx, dx, dy * dy));
         real uc, ul;
         const real phi = pair_phi<real, EV>(r2, qi * qj, lje, pp, uc, ul);
         a.fx += phi * dx;
@@ -994,13 +995,19 @@ __global__ __launch_bounds__(kCoopBlock, ENC && !EV && sizeof(real) == 4 ? 5 : 1
     }
 }
 
-// Core entries and batch slots of the first pass of k_pair_thread.
+// Entries of a lane's first pass in k_pair_thread (a multiple of 4).
 constexpr int kThreadFirst = 12;
 
 // Sparse lists (every atom's core list and batch within a few dozen entries, as
-// in the dilute electrolytes): one thread per atom walks its own core list,
-// excluded partners and batch, so that no wavefront lane idles on an atom with
-// a handful of pairs. Same sums and partials as k_pair_coop (split lists).
+// in the dilute electrolytes): two lanes per atom, the even one walking its core
+// list and excluded partners, the odd one its batch, so that no wavefront idles on
+// an atom with a handful of pairs. Same sums and partials as k_pair_coop (split
+// lists; the two lanes' sums are the ones that kernel adds at the end). The loads
+// bound it: ten or so dependent gathers per atom over three levels (ranks, shell
+// entries, positions), one cache line and address each; the lane pair keeps half
+// the registers of one thread per atom and so twice the gathers in flight, and
+// indices come four to a load. 10^6 ions, 10 of 136 drawn: 239 -> 217 us
+// (218 -> 193 us on kept lists); 14 L2 requests of 700 cycles per atom are what is left.
 template <typename real, bool EV>
 __global__ __launch_bounds__(kCoopBlock) void k_pair_thread(
     int64_t n, PairParams<real> pp, const uint4* __restrict__ spos, const real* __restrict__ sqr,
@@ -1017,7 +1024,8 @@ __global__ __launch_bounds__(kCoopBlock) void k_pair_thread(
     for (int t = threadIdx.x; t < nt2; t += kCoopBlock) lj[t] = lj_g[t];
     __syncthreads();
     const int64_t blk = xcd_block(blockIdx.x, gridDim.x);
-    const int64_t a = blk * kCoopBlock + threadIdx.x;
+    const int64_t a = blk * (kCoopBlock / 2) + (threadIdx.x >> 1);
+    const bool batch = threadIdx.x & 1;
     constexpr int NV = EV ? 12 : 3;
     double vals[NV];
     for (int c = 0; c < NV; ++c) vals[c] = 0.0;
@@ -1030,103 +1038,106 @@ __global__ __launch_bounds__(kCoopBlock) void k_pair_thread(
         // LJ coefficients of the pair types
         const int li = (int)si.w * n_types;
         auto ljof = [&](uint4 sj) -> LJ<real> { return lj[li + (int)sj.w]; };
-        PairSum<real> pc, ps, px;
-        const int nc = ncore[a];
-        const int32_t* crow = core + a * (int64_t)cap_core;
         const int ns = nshell[a];
         const bool sample = ns > p_shell;
-        const int cnt = sample ? p_shell : ns;
+        const int cnt = batch ? min(ns, p_shell) : ncore[a];
+        const int32_t* crow = core + a * (int64_t)cap_core;
         const int32_t* srow = shell + a * (int64_t)cap_shell;
         const uint16_t* rrow = ranks + a * (int64_t)p_stride;
-        // first pass over up to kThreadFirst core entries and batch slots, each
-        // level's loads issued together: core indices and batch ranks, then core
-        // positions and shell entries, then shell positions
-        int jc[kThreadFirst], js[kThreadFirst];
-#pragma unroll
-        for (int u = 0; u < kThreadFirst; ++u) jc[u] = u < nc ? crow[u] : -1;
-#pragma unroll
-        for (int u = 0; u < kThreadFirst; ++u) js[u] = u < cnt ? (sample ? (int)rrow[u] : u) : -1;
-        uint4 sc[kThreadFirst];
-        real qc[kThreadFirst];
-#pragma unroll
-        for (int u = 0; u < kThreadFirst; ++u) at.get(max(jc[u], 0), sc[u], qc[u]);
-#pragma unroll
-        for (int u = 0; u < kThreadFirst; ++u) js[u] = js[u] >= 0 ? srow[js[u]] : -1;
-        if (bj_out) {
-            // the batch atoms, for the backward expected at this step
-#pragma unroll
-            for (int u = 0; u < kThreadFirst; ++u)
-                if (u < cnt) bj_out[a * (int64_t)p_stride + u] = js[u];
-        }
-        uint4 ss[kThreadFirst];
-        real qs[kThreadFirst];
-#pragma unroll
-        for (int u = 0; u < kThreadFirst; ++u) at.get(max(js[u], 0), ss[u], qs[u]);
-#pragma unroll
-        for (int u = 0; u < kThreadFirst; ++u)
-            if (jc[u] >= 0 && (!skin || dist2_q(si, sc[u]) <= t_core))
-                add_pair<real, EV, false>(pc, si, qi, sc[u], qc[u], ljof(sc[u]), pp);
-#pragma unroll
-        for (int u = 0; u < kThreadFirst; ++u)
-            if (js[u] >= 0 && (!skin || in_annulus(si, ss[u], t_core, t_shell)))
-                add_pair<real, EV, false>(ps, si, qi, ss[u], qs[u], ljof(ss[u]), pp);
-        // the rest four entries at a time: their index and position loads go out together
-        for (int c0 = kThreadFirst; c0 < nc; c0 += 4) {
-            int j[4];
-            uint4 sj[4];
-            real qj[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) j[u] = c0 + u < nc ? crow[c0 + u] : -1;
-#pragma unroll
-            for (int u = 0; u < 4; ++u) at.get(max(j[u], 0), sj[u], qj[u]);
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                if (j[u] >= 0 && (!skin || dist2_q(si, sj[u]) <= t_core))
-                    add_pair<real, EV, false>(pc, si, qi, sj[u], qj[u], ljof(sj[u]), pp);
-        }
-        const int2 xr = sxr[a];
-        for (int c = 0; c < xr.y; ++c) {
-            uint4 sj;
-            real qj;
-            at.get(sxidx[xr.x + c], sj, qj);
-            add_excl<real, EV>(px, si, qi, sj, qj, pp);
-        }
-        for (int c0 = kThreadFirst; c0 < cnt; c0 += 4) {
-            int r[4], j[4];
-            uint4 sj[4];
-            real qj[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) r[u] = c0 + u < cnt ? (sample ? (int)rrow[c0 + u] : c0 + u) : -1;
-#pragma unroll
-            for (int u = 0; u < 4; ++u) j[u] = r[u] >= 0 ? srow[r[u]] : -1;
-            if (bj_out) {
-                // the batch atoms, for the backward expected at this step
-#pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    if (c0 + u < cnt) bj_out[a * (int64_t)p_stride + c0 + u] = j[u];
+        // entries c0 .. c0 + 3 of this lane's list (-1 past its end; the rows and their
+        // capacities are multiples of four entries)
+        auto ranks4 = [&](int c0) -> int4 {
+            if (!sample) return make_int4(c0, c0 + 1, c0 + 2, c0 + 3);
+            const uint2 r = *(const uint2*)(rrow + c0);
+            return make_int4((int)(r.x & 0xffffu), (int)(r.x >> 16), (int)(r.y & 0xffffu), (int)(r.y >> 16));
+        };
+        auto first4 = [&](int c0) -> int4 {
+            if (c0 >= cnt) return make_int4(-1, -1, -1, -1);
+            return batch ? ranks4(c0) : *(const int4*)(crow + c0);
+        };
+        auto entries4 = [&](int c0, int4 r, int* j) {
+            j[0] = c0 < cnt ? (batch ? srow[r.x] : r.x) : -1;
+            j[1] = c0 + 1 < cnt ? (batch ? srow[r.y] : r.y) : -1;
+            j[2] = c0 + 2 < cnt ? (batch ? srow[r.z] : r.z) : -1;
+            j[3] = c0 + 3 < cnt ? (batch ? srow[r.w] : r.w) : -1;
+        };
+        // the batch atoms, for the backward expected at this step
+        auto keep4 = [&](int c0, const int* j) {
+            if (bj_out && batch && c0 < cnt)
+                *(int4*)(bj_out + a * (int64_t)p_stride + c0) = make_int4(j[0], j[1], j[2], j[3]);
+        };
+        PairSum<real> p, px;
+        auto pair = [&](int j, uint4 sj, real qj) {
+            if (j < 0) return;
+            if (skin) {
+                const uint64_t d2 = dist2_q(si, sj);
+                if (batch ? d2 <= t_core || d2 > t_shell : d2 > t_core) return;
             }
+            add_pair<real, EV, false>(p, si, qi, sj, qj, ljof(sj), pp);
+        };
+        // the first pass, each level's loads issued together
+        int4 r[kThreadFirst / 4];
+        int j[kThreadFirst];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) at.get(max(j[u], 0), sj[u], qj[u]);
+        for (int u = 0; u < kThreadFirst; u += 4) r[u / 4] = first4(u);
 #pragma unroll
-            for (int u = 0; u < 4; ++u)
-                if (j[u] >= 0 && (!skin || in_annulus(si, sj[u], t_core, t_shell)))
-                    add_pair<real, EV, false>(ps, si, qi, sj[u], qj[u], ljof(sj[u]), pp);
+        for (int u = 0; u < kThreadFirst; u += 4) entries4(u, r[u / 4], j + u);
+        uint4 sj[kThreadFirst];
+        real qj[kThreadFirst];
+#pragma unroll
+        for (int u = 0; u < kThreadFirst; ++u) at.get(max(j[u], 0), sj[u], qj[u]);
+#pragma unroll
+        for (int u = 0; u < kThreadFirst; u += 4) keep4(u, j + u);
+#pragma unroll
+        for (int u = 0; u < kThreadFirst; ++u) pair(j[u], sj[u], qj[u]);
+        // the rest four entries at a time
+        for (int c0 = kThreadFirst; c0 < cnt; c0 += 4) {
+            int jt[4];
+            uint4 st[4];
+            real qt[4];
+            entries4(c0, first4(c0), jt);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) at.get(max(jt[u], 0), st[u], qt[u]);
+            keep4(c0, jt);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) pair(jt[u], st[u], qt[u]);
         }
-        const real w = sample ? (real)((double)ns / (double)p_shell) : (real)1;
-        const real fx = pc.fx + w * ps.fx + px.fx;
-        const real fy = pc.fy + w * ps.fy + px.fy;
-        const real fz = pc.fz + w * ps.fz + px.fz;
-        fsr[3 * a + 0] = fx;
-        fsr[3 * a + 1] = fy;
-        fsr[3 * a + 2] = fz;
-        vals[0] = (double)fx;
-        vals[1] = (double)fy;
-        vals[2] = (double)fz;
+        if (!batch) {
+            const int2 xr = sxr[a];
+            for (int c = 0; c < xr.y; ++c) {
+                uint4 sx;
+                real qx;
+                at.get(sxidx[xr.x + c], sx, qx);
+                add_excl<real, EV>(px, si, qi, sx, qx, pp);
+            }
+        }
+        // the batch lane's sums to the even lane
+        PairSum<real> ps;
+        ps.fx = __shfl_xor(p.fx, 1, 64);
+        ps.fy = __shfl_xor(p.fy, 1, 64);
+        ps.fz = __shfl_xor(p.fz, 1, 64);
         if (EV) {
-            vals[3] = 0.5 * (double)(pc.uc + w * ps.uc);
-            vals[4] = 0.5 * (double)(pc.ul + w * ps.ul);
-            vals[5] = 0.5 * (double)px.uc;
-            for (int c = 0; c < 6; ++c) vals[6 + c] = -0.5 * (double)(pc.v[c] + w * ps.v[c] + px.v[c]);
+            ps.uc = __shfl_xor(p.uc, 1, 64);
+            ps.ul = __shfl_xor(p.ul, 1, 64);
+            for (int c = 0; c < 6; ++c) ps.v[c] = __shfl_xor(p.v[c], 1, 64);
+        }
+        if (!batch) {
+            const real w = sample ? (real)((double)ns / (double)p_shell) : (real)1;
+            const real fx = p.fx + w * ps.fx + px.fx;
+            const real fy = p.fy + w * ps.fy + px.fy;
+            const real fz = p.fz + w * ps.fz + px.fz;
+            fsr[3 * a + 0] = fx;
+            fsr[3 * a + 1] = fy;
+            fsr[3 * a + 2] = fz;
+            vals[0] = (double)fx;
+            vals[1] = (double)fy;
+            vals[2] = (double)fz;
+            if (EV) {
+                vals[3] = 0.5 * (double)(p.uc + w * ps.uc);
+                vals[4] = 0.5 * (double)(p.ul + w * ps.ul);
+                vals[5] = 0.5 * (double)px.uc;
+                for (int c = 0; c < 6; ++c) vals[6 + c] = -0.5 * (double)(p.v[c] + w * ps.v[c] + px.v[c]);
+            }
         }
     }
     double out;
@@ -1266,7 +1277,7 @@ static hipError_t launch_thread_t(irbe_ctx* h, uint64_t step)
     const PairParams<real> pp = pair_params<real>(h);
     hipError_t e = launch_draw(h, step);
     if (e != hipSuccess) return e;
-    const unsigned nb = (unsigned)blocks_for(n, kCoopBlock);
+    const unsigned nb = (unsigned)blocks_for(n, kCoopBlock / 2);
     if ((int64_t)nb > h->part_blocks) return hipErrorInvalidValue;
     // the batch atoms for the backward, as in launch_coop_t
     int32_t* bj_out = h->keep_batch ? h->batch_j : nullptr;
