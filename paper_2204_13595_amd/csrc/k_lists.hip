@@ -35,14 +35,19 @@ using PackedBounds = Bounds<uint32_t>;
 
 __device__ __forceinline__ int wrap(int c, int n) { return c < 0 ? c + n : (c >= n ? c - n : c); }
 
-// Squared separation of two packed positions (x | y << 16, z): exact in the
-// 16-bit units (differences modulo 2^16); the sum of the three squares stays
-// below 2^32.
-__device__ __forceinline__ uint32_t d2_packed(uint32_t cxy, uint32_t cz, uint32_t axy, uint32_t az)
+// Squared separation of two packed positions (x | y << 16, z) minus t: exact in
+// the 16-bit units (differences modulo 2^16), saturated to 32 bits.
+__device__ __forceinline__ int d2_minus(uint32_t cxy, uint32_t cz, uint32_t axy, uint32_t az, int t)
 {
     const s16x2 dxy = __builtin_bit_cast(s16x2, cxy) - __builtin_bit_cast(s16x2, axy);
     const int dz = (short)(cz - az);
-    return (uint32_t)__builtin_amdgcn_sdot2(dxy, dxy, dz * dz, false);
+    return __builtin_amdgcn_sdot2(dxy, dxy, dz * dz - t, true);
+}
+
+// bits shifted up by one with the sign of v below.
+__device__ __forceinline__ uint32_t shift_sign(uint32_t bits, int v)
+{
+    return __builtin_amdgcn_alignbit(bits, (uint32_t)v, 31);
 }
 
 // Lanes with p set (a wave-uniform mask).
@@ -74,28 +79,34 @@ __device__ __forceinline__ void store_counts(int k, int cc, int cs, int cap_core
 // primitive-model electrolytes) with cells narrower than the box
 // (2R + 1 <= n_c). The same lists in the same order as the block form, whose
 // blocks of 32 atoms are far longer than the list radius there; here one wavefront
-// takes up to 64 atoms of consecutive cells of one cell row, one atom per lane.
+// takes a run of up to 64 consecutive atoms of one cell row, one atom per lane (the
+// row's atoms in equal runs: groups of a fixed number of cells overflowed 64 atoms
+// one time in four, for a second pass of a few).
 // For every stencil row (dz, dy) the union of the atoms' x ranges is staged in
-// LDS as above. The first atom and atom count of every row's union (two index
-// ranges at most) are loaded once per group into a table held in registers,
+// LDS. The first atom and atom count of every row's union (two index
+// ranges at most) are loaded once per run into a table held in registers,
 // so that a row's cell starts and the records of its first tile are loaded in
 // one memory round trip, issued before the pruning of the rows that follow.
-// Each lane computes its own cell range in the union (row pruning) and
-// the lanes then walk their ranges in lockstep, lane a testing its k-th
-// candidate at step k. A lane appends its shell members (or full-list
-// members) to a ring of 8 entries in LDS and every 4 steps the lanes whose
-// ring holds 4 unwritten entries store them as one aligned 16-byte segment of
-// their list row (at most 3 + 4 entries wait in the ring); core members are
-// stored directly. Candidates between the
-// packed bounds take the exact test on full positions read from memory (the
-// LDS footprint, about 4.4 KB, leaves room for the wavefronts that hide the
-// per-row latencies).
+// Each lane computes its own cell range in the union (row pruning, in cell edges
+// and FP32 with a margin) and the lanes then walk their ranges in lockstep, lane a
+// testing its k-th candidate at step k and shifting the sign of squared separation
+// minus bound into bit masks: no branch per candidate. Candidates between two
+// bounds take the exact test on full positions read from memory; then each lane
+// appends its bits, four at a time, to a stage in LDS, from which full segments go
+// to its list row. What bounds it: the vector instructions (260 per atom, 70 % of
+// the issue slots) and the latency of the 48 rows' serial chain; segments of 16 bytes
+// were written twice to memory (1.35 GB against 0.73), as the open lines of all
+// wavefronts exceed the L2. 10^6 ions, 1.28 per cell, 136 + 5 members: 880 -> 705 us,
+// with a skin 1,060 -> 730 us.
 // ---------------------------------------------------------------------------
 constexpr int kLaneTile = 128;           // staged candidates per pass of a row
-constexpr int kRing = 8;                 // ring entries per lane
-constexpr int kSeg = 4;                  // entries per stored segment (16 bytes)
-constexpr int kRingStride = kRing + 1;   // words per lane's ring (odd: conflict-free lanes)
-constexpr double kLaneGroupAtoms = 60.0; // atoms per group the launch aims at (at most 64 per pass)
+constexpr int kLanePass = 24;            // candidates per pass of a row's bits
+constexpr int kSeg = 16;                 // entries per stored segment (64 bytes)
+constexpr int kAppend = 4;               // entries appended between two looks for full segments
+constexpr int kStage = kSeg + 3;         // a lane's staged entries (an odd stride: conflict-free lanes)
+// Margin of the row pruning in cell edges, far above the rounding of its FP32
+// arithmetic (below 1e-5 for offsets of up to 11 cells): it never drops a member.
+constexpr float kPruneMargin = 1e-4f;
 
 // A stencil row of the lane-per-atom kernel as loaded: its union's two segments
 // (first atom and atoms of A; first atom of B; atoms of both), this lane's raw
@@ -106,158 +117,163 @@ struct RowLoad {
     u32x4 rec[kLaneTile / kListWave];
 };
 
-// (eight wavefronts per SIMD requested: the register bound of 64 gains the skin lists 8%, the others are the same)
+// (six wavefronts per SIMD: what the stage leaves of LDS; more registers' worth of them spill)
 template <int MODE>
-__global__ __launch_bounds__(kListWave, 8) void k_build_lists_lanes(
-    int n_c, int lo, int hi, int G, PackedBounds tb, uint64_t t_core, uint64_t t_lo, uint64_t t_shell, float tfs_hi,
+__global__ __launch_bounds__(kListWave, 6) void k_build_lists_lanes(
+    int n_c, int lo, int hi, int G, int parts, PackedBounds tb, uint64_t t_core, uint64_t t_lo, uint64_t t_shell, float r2_cells, bool excl,
     const uint4* __restrict__ spos, const u32x4* __restrict__ spk, const int32_t* __restrict__ cell_start,
-    const uint32_t* __restrict__ bound_g,
     int cap_core, int cap_shell, int32_t* __restrict__ core, int32_t* __restrict__ ncore,
     int32_t* __restrict__ shell, int32_t* __restrict__ nshell, int32_t* __restrict__ maxcnt,
     uint32_t* __restrict__ err)
 {
-    __shared__ u32x4 trec[kLaneTile + 1];          // packed x | y, packed z, exclusion id, sorted index
-    __shared__ int32_t ring[kListWave * kRingStride];
+    __shared__ uint2 trec[kLaneTile + kLanePass];     // packed x | y, packed z
+    __shared__ uint32_t tid[kLaneTile + kLanePass];   // exclusion id
+    __shared__ int32_t stage[kListWave * kStage];
     __shared__ int32_t tcs[64];                    // union positions of the row's cells (segment A, then B)
-    const uint32_t* bound = bound_g;
     const int lane = threadIdx.x;
+    // bounds relative to the first impossible squared separation of the list that is
+    // appended (the core list or the shell or full list)
+    constexpr bool kTwoLists = MODE == kListsSplit || MODE == kListsSplitSkin;
+    const int t_out = (int)(MODE == kListsCoreOnly ? tb.core_out : tb.shell_out) + 1;
+    const int t_width = t_out - (int)(MODE == kListsCoreOnly ? tb.core_in : tb.shell_in);
+    const int c_off = t_out - ((int)tb.core_out + 1), c_width = (int)tb.core_out + 1 - (int)tb.core_in;
+    const int l_off = t_out - ((int)tb.lo_out + 1), l_width = (int)tb.lo_out + 1 - (int)tb.lo_in;
     const int span = hi - lo + 1;
-    const int groups_per_row = (n_c + G - 1) / G;
     const int g = (int)xcd_block(blockIdx.x, gridDim.x);
-    const int rowid = g / groups_per_row;
+    const int rowid = g / parts;
     const int cz = rowid / n_c, cy = rowid % n_c;
-    const int x0 = (g % groups_per_row) * G;
-    const int gr = min(G, n_c - x0);
     const int home = (cz * n_c + cy) * n_c;
-    const int a0 = cell_start[home + x0], a1 = cell_start[home + x0 + gr];
-    const int span_u = gr - 1 + span;           // cells of the union x range
-    const int xu0 = wrap(x0 + lo, n_c);         // first cell of the union
-    const int lenA = min(span_u, n_c - xu0);    // cells before the wrap
-    int32_t* const myring = ring + lane * kRingStride;
-    // every stencil row's union: first atom and atom count of segment A (cells
-    // xu0 .. xu0 + lenA - 1) and of segment B (cells 0 .. lenB - 1, past the wrap),
-    // row ri = (dz, dy) = (lo + ri / span, lo + ri % span) in lane ri % 64 of
-    // rtab[ri / 64], loaded once for the group
+    const int r0 = cell_start[home], r1 = cell_start[home + n_c];
+    int32_t* const mine_st = stage + lane * kStage;
     const int nrows = span * span;  // at most 2 * kListWave (checked at the launch)
-    const int lenB = span_u - lenA;
-    int4 rtab[2];
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int ri = h * kListWave + lane;
-        rtab[h] = make_int4(0, 0, 0, 0);
-        if (ri < nrows) {
-            const int row = (wrap(cz + lo + ri / span, n_c) * n_c + wrap(cy + lo + ri % span, n_c)) * n_c;
-            const int ja = cell_start[row + xu0], jb = cell_start[row];
-            rtab[h] = make_int4(ja, cell_start[row + xu0 + lenA] - ja, jb, lenB > 0 ? cell_start[row + lenB] - jb : 0);
-        }
-    }
-    // a row's union from the table, this lane's cell start in it and the records of
-    // its first tile, issued together (one memory round trip)
-    // first and last coordinates of the stencil's z and y cell slabs, lane l for the
-    // offset lo + l (span <= 11 here), read back with readlane
-    const int ls = min(lane, span - 1);
-    const int zs = wrap(cz + lo + ls, n_c), ys = wrap(cy + lo + ls, n_c);
-    const uint32_t zlo = bound[zs], zhi = bound[zs + 1] - 1u, ylo = bound[ys], yhi = bound[ys + 1] - 1u;
-    // distance from coordinate s to the slab at offset d (the first coordinate of a slab above, the last of one below)
-    auto gap = [](uint32_t s, int d, uint32_t lo_t, uint32_t hi_t, int idx) __attribute__((always_inline)) {
-        if (d > 0) return (uint32_t)__builtin_amdgcn_readlane((int)lo_t, idx) - s;
-        if (d < 0) return s - (uint32_t)__builtin_amdgcn_readlane((int)hi_t, idx);
-        return 0u;
-    };
-    // the row after (dz, dy) in the stencil's lexicographic order
-    auto step_row = [&](int& dz, int& dy) __attribute__((always_inline)) {
-        if (++dy > hi) {
-            dy = lo;
-            ++dz;
-        }
-    };
-    auto row_load = [&](int ri, int dz, int dy) __attribute__((always_inline)) {
-        RowLoad d;
-        const int h = ri >> 6, rl = ri & (kListWave - 1);
-        d.jA = __builtin_amdgcn_readlane(h ? rtab[1].x : rtab[0].x, rl);
-        d.nA = __builtin_amdgcn_readlane(h ? rtab[1].y : rtab[0].y, rl);
-        d.jB = __builtin_amdgcn_readlane(h ? rtab[1].z : rtab[0].z, rl);
-        d.total = d.nA + __builtin_amdgcn_readlane(h ? rtab[1].w : rtab[0].w, rl);
-        const int row = (wrap(cz + dz, n_c) * n_c + wrap(cy + dy, n_c)) * n_c;
-        // (every lane loads, from an index inside the arrays, so that no load sits
-        // in a branch and the waits for these registers can be counted exactly;
-        // lanes past the union or the tile do not use theirs)
-        const int lc = min(lane, span_u);
-        d.cst = cell_start[lc < lenA ? row + xu0 + lc : row + lc - lenA];
-        const int cnt0 = min(kLaneTile, d.total);
-#pragma unroll
-        for (int q = 0; q < kLaneTile / kListWave; ++q) {
-            const int t = q * kListWave + lane;
-            d.rec[q] = spk[t < cnt0 ? (t < d.nA ? d.jA + t : d.jB + (t - d.nA)) : a0];
-        }
-        return d;
+    // the row's atoms in equal runs of at most 64; this wavefront takes run part, part + parts, ...
+    const int runs = (r1 - r0 + kListWave - 1) / kListWave;
+    const int run = runs > 0 ? (r1 - r0 + runs - 1) / runs : 0;
+    // (the last parts are often empty: they rotate with the row, because consecutive workgroups
+    // go to the shader engines in turn, and four parts in a fixed order left one of them idle)
+    int part = (g - rowid * parts + rowid) % parts;
+    auto cell_of = [&](uint32_t x) __attribute__((always_inline)) {
+        return (int)(((uint64_t)x * (uint32_t)n_c) >> 32);
     };
     int maxc = 0, maxs = 0;
-    for (int chunk = a0; chunk < a1; chunk += kListWave) {
-        const int k = chunk + lane;
+    for (int s = r0 + part * run, e = min(s + run, r1); s < e;) {
+        // the atoms from s on whose cells' union fits (all of the run but in sparse rows)
+        const int x0 = cell_of(spos[s].x);
+        const int a1 = min(e, cell_start[home + min(x0 + G, n_c)]);
+        const int span_u = cell_of(spos[a1 - 1].x) - x0 + span;  // cells of the union x range
+        const int xu0 = wrap(x0 + lo, n_c);                      // first cell of the union
+        const int lenA = min(span_u, n_c - xu0);                 // cells before the wrap
+        // every stencil row's union: first atom and atom count of segment A (cells
+        // xu0 .. xu0 + lenA - 1) and of segment B (cells 0 .. lenB - 1, past the wrap),
+        // row ri = (dz, dy) = (lo + ri / span, lo + ri % span) in lane ri % 64 of
+        // rtab[ri / 64], loaded once for the run
+        const int lenB = span_u - lenA;
+        int4 rtab[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int ri = h * kListWave + lane;
+            rtab[h] = make_int4(0, 0, 0, 0);
+            if (ri < nrows) {
+                const int row = (wrap(cz + lo + ri / span, n_c) * n_c + wrap(cy + lo + ri % span, n_c)) * n_c;
+                const int ja = cell_start[row + xu0], jb = cell_start[row];
+                rtab[h] = make_int4(ja, cell_start[row + xu0 + lenA] - ja, jb, lenB > 0 ? cell_start[row + lenB] - jb : 0);
+            }
+        }
+        // a row's union from the table, this lane's cell start in it and the records of
+        // its first tile, issued together (one memory round trip)
+        auto row_load = [&](int ri, int dz, int dy) __attribute__((always_inline)) {
+            RowLoad d;
+            const int h = ri >> 6, rl = ri & (kListWave - 1);
+            d.jA = __builtin_amdgcn_readlane(h ? rtab[1].x : rtab[0].x, rl);
+            d.nA = __builtin_amdgcn_readlane(h ? rtab[1].y : rtab[0].y, rl);
+            d.jB = __builtin_amdgcn_readlane(h ? rtab[1].z : rtab[0].z, rl);
+            d.total = d.nA + __builtin_amdgcn_readlane(h ? rtab[1].w : rtab[0].w, rl);
+            const int row = (wrap(cz + dz, n_c) * n_c + wrap(cy + dy, n_c)) * n_c;
+            // (every lane loads, from an index inside the arrays, so that no load sits
+            // in a branch and the waits for these registers can be counted exactly;
+            // lanes past the union or the tile do not use theirs)
+            const int lc = min(lane, span_u);
+            d.cst = cell_start[lc < lenA ? row + xu0 + lc : row + lc - lenA];
+            const int cnt0 = min(kLaneTile, d.total);
+#pragma unroll
+            for (int q = 0; q < kLaneTile / kListWave; ++q) {
+                const int t = q * kListWave + lane;
+                d.rec[q] = spk[t < cnt0 ? (t < d.nA ? d.jA + t : d.jB + (t - d.nA)) : s];
+            }
+            return d;
+        };
+        const int k = s + lane;
         const bool act = k < a1;
         const uint4 si = act ? spos[k] : make_uint4(0, 0, 0, 0);
-        const int cx = (int)(((uint64_t)si.x * (uint32_t)n_c) >> 32);
-        const int ti = act ? wrap(cx - x0, n_c) : 0;  // lane's home cell in [0, gr)
+        const int ti = act ? cell_of(si.x) - x0 : 0;  // lane's home cell from x0 on
         const u32x4 pk = act ? spk[k] : u32x4{0, 0, 0, 0};  // packed x | y, z, exclusion id
         const uint32_t axy = pk.x, az = pk.y, amol = pk.z;
         int32_t* const crow = core + (int64_t)k * cap_core;
         int32_t* const srow = shell + (int64_t)k * cap_shell;
-        int cc = 0, cs = 0;  // list lengths so far
-        int fs = 0;          // shell entries already stored (a multiple of kSeg)
-        // the lane's range in row ri = (dz, dy): cells [u_lo, u_hi] of the union, pruned by
-        // the row gap; the first row at or after ri that some lane needs (nrows: none),
-        // with (dz, dy) advanced to it
-        auto next_row = [&](int ri, int& dz, int& dy, int& u_lo, int& u_hi, bool& need)
-                            __attribute__((always_inline)) -> int {
-            for (; ri < nrows; ++ri, step_row(dz, dy)) {
-                if (MODE == kListsCoreOnly && (dz < -1 || dz > 1 || dy < -1 || dy > 1)) continue;
-                u_lo = ti;
-                u_hi = ti + span - 1;
-                need = act;
-                if (act) {
-                    const float gz = (float)gap(si.z, dz, zlo, zhi, dz - lo);
-                    const float gy = (float)gap(si.y, dy, ylo, yhi, dy - lo);
-                    const float rem = tfs_hi - gy * gy - gz * gz;
-                    if (rem < 0.0f) {
-                        need = false;
-                    } else {
-                        const uint32_t ext = (uint32_t)(__builtin_amdgcn_sqrtf(rem) * 1.000002f) + 2u;
-                        const int cl = (int)(((uint64_t)(uint32_t)(si.x - ext) * (uint32_t)n_c) >> 32);
-                        const int ch = (int)(((uint64_t)(uint32_t)(si.x + ext) * (uint32_t)n_c) >> 32);
-                        int ol = cl - cx, oh = ch - cx;
-                        if (ol > n_c / 2) ol -= n_c;
-                        if (ol < -n_c / 2) ol += n_c;
-                        if (oh > n_c / 2) oh -= n_c;
-                        if (oh < -n_c / 2) oh += n_c;
-                        u_lo = ti + (max(ol, lo) - lo);
-                        u_hi = ti + (min(oh, hi) - lo);
-                    }
-                }
-                if (ballot(need) != 0) return ri;
-            }
-            return nrows;
+        int cc = 0, cs = 0;  // list lengths so far (cs: without the staged entries)
+        int wait = 0;        // staged entries (fewer than kSeg between the appends)
+        // the atom in its home cell, in cell edges (x with the margin of either side)
+        const float fx_lo = (float)(si.x * (uint32_t)n_c) * 0x1p-32f - kPruneMargin, fx_hi = fx_lo + 2.0f * kPruneMargin;
+        const float fy = (float)(si.y * (uint32_t)n_c) * 0x1p-32f, fz = (float)(si.z * (uint32_t)n_c) * 0x1p-32f;
+        const int t0 = ti - lo;
+        // distance from the slab of cells at offset d
+        auto gap = [](float f, int d) __attribute__((always_inline)) {
+            const float t = (float)d - f;
+            return fmaxf(fmaxf(t, -1.0f - t), 0.0f);
         };
-        int u_lo = 0, u_hi = 0;
-        bool need = false;
-        int dz = lo, dy = lo;
-        int rc = next_row(0, dz, dy, u_lo, u_hi, need);
-        while (rc < nrows) {
+        auto slab = [&](int dz) __attribute__((always_inline)) {
+            const float g = gap(fz, dz);
+            return act ? r2_cells - g * g : -1.0f;
+        };
+        // the stencil rows in lexicographic order: row ri = (dz, dy), the squared radius left
+        // in slab dz, and the lane's range in the row, cells [u_lo, u_hi] of the union
+        struct Row {
+            int ri, dz, dy;
+            float left;
+            int u_lo, u_hi;
+            bool need;
+        };
+        // moves on to the first row that some lane needs (ri = nrows: none)
+        auto seek = [&](Row& w) __attribute__((always_inline)) {
+            for (; w.ri < nrows; ++w.ri) {
+                if (w.dy > hi) {
+                    w.dy = lo;
+                    ++w.dz;
+                    w.left = slab(w.dz);
+                }
+                const int dy = w.dy++;
+                if (MODE == kListsCoreOnly && (w.dz < -1 || w.dz > 1 || dy < -1 || dy > 1)) continue;
+                const float g = gap(fy, dy);
+                const float rem = w.left - g * g;
+                w.need = rem >= 0.0f;
+                if (ballot(w.need) != 0) {
+                    const float ext = __builtin_amdgcn_sqrtf(rem);
+                    w.u_lo = t0 + max((int)floorf(fx_lo - ext), lo);
+                    w.u_hi = t0 + min((int)floorf(fx_hi + ext), hi);
+                    return;
+                }
+            }
+        };
+        Row next{0, lo, lo, slab(lo), 0, 0, false};
+        seek(next);
+        while (next.ri < nrows) {
             // the row's loads are in flight while the next needed row is found
-            const RowLoad cur = row_load(rc, dz, dy);
-            int u_lo_n = 0, u_hi_n = 0;
-            bool need_n = false;
-            int dz_n = dz, dy_n = dy;
-            step_row(dz_n, dy_n);
-            const int rn = next_row(rc + 1, dz_n, dy_n, u_lo_n, u_hi_n, need_n);
+            const int dz = next.dz, dy = next.dy - 1, u_lo = next.u_lo, u_hi = next.u_hi;
+            const bool need = next.need;
+            const RowLoad cur = row_load(next.ri, dz, dy);
+            ++next.ri;
+            seek(next);
             const bool core_row = MODE != kListsFull && dz >= -1 && dz <= 1 && dy >= -1 && dy <= 1;
             const int jA = cur.jA, nA = cur.nA, jB = cur.jB, total = cur.total;
             // (LDS accesses of the one wavefront of the workgroup take effect in
             // order: the previous row's reads precede these writes)
             if (lane <= span_u) tcs[lane] = cur.cst - (lane < lenA ? jA : jB - nA);
 #pragma unroll
-            for (int h = 0; h < kLaneTile / kListWave; ++h)
-                if (h * kListWave + lane < min(kLaneTile, total)) trec[h * kListWave + lane] = cur.rec[h];
+            for (int h = 0; h < kLaneTile / kListWave; ++h) {
+                // (past the union: values that no lane's range covers)
+                trec[h * kListWave + lane] = make_uint2(cur.rec[h].x, cur.rec[h].y);
+                if (excl) tid[h * kListWave + lane] = cur.rec[h].z;
+            }
             asm volatile("" ::: "memory");
             const int p_lo = need ? tcs[u_lo] : 0;
             const int p_hi = need ? tcs[u_hi + 1] : 0;
@@ -269,100 +285,157 @@ __global__ __launch_bounds__(kListWave, 8) void k_build_lists_lanes(
                     for (int t = lane; t < cnt; t += kListWave) {
                         const int p = base + t;
                         const int j = p < nA ? jA + p : jB + (p - nA);
-                        trec[t] = spk[j];
+                        const u32x4 r = spk[j];
+                        trec[t] = make_uint2(r.x, r.y);
+                        tid[t] = r.z;
                     }
                     __syncthreads();
                 }
                 // this tile's part of the range, in tile positions
                 const int s0 = need ? max(p_lo, base) - base : 0;
                 const int len = need ? max(min(p_hi, base + cnt) - base - s0, 0) : 0;
-                int steps = len;
+                for (int c0 = 0; ballot(len > c0) != 0; c0 += kLanePass) {
+                    // this pass's candidates in bits: the sign of the squared separation minus
+                    // each bound is shifted in
+                    const int mine = min(max(len - c0, 0), kLanePass);
+                    const int sp = mine > 0 ? s0 + c0 : 0;  // (reads end before tile position kLaneTile + kLanePass)
+                    int done = 0;
+                    uint32_t in_p = 0, in_d = 0, co_p = 0, co_d = 0, lo_p = 0, lo_d = 0;
+                    auto candidates = [&](auto with_core, auto with_excl) __attribute__((always_inline)) {
+                        do {
+                            uint2 r[4];
+                            uint32_t id[4];
 #pragma unroll
-                for (int off = 32; off > 0; off >>= 1) steps = max(steps, __shfl_xor(steps, off, 64));
-                steps = __builtin_amdgcn_readfirstlane(steps);  // (every lane holds the maximum)
-                for (int st = 0; st < steps; ++st) {
-                    const bool k_in = st < len;
-                    const int tp = k_in ? s0 + st : kLaneTile;
-                    const u32x4 r = trec[tp];
-                    const uint32_t d2 = d2_packed(r.x, r.y, axy, az);
-                    const bool keep = k_in && r.z != amol;
-                    bool in_core = false, in_shell = false, amb;
-                    if (MODE == kListsCoreOnly) {
-                        in_core = keep && d2 < tb.core_in;
-                        amb = keep && !in_core && d2 <= tb.core_out;
-                    } else if (MODE == kListsSplitSkin) {
-                        const bool c_in = d2 < tb.core_in, c_out = d2 > tb.core_out;
-                        const bool l_in = d2 < tb.lo_in, l_out = d2 > tb.lo_out;
-                        const bool s_in = d2 < tb.shell_in, s_out = d2 > tb.shell_out;
-                        in_core = keep && c_in;
-                        in_shell = keep && l_out && s_in;
-                        amb = keep && !((c_in || c_out) && (l_in || (l_out && s_in) || s_out));
-                    } else if (MODE == kListsSplit) {
-                        const bool c_in = d2 < tb.core_in, c_out = d2 > tb.core_out;
-                        const bool s_in = d2 < tb.shell_in, s_out = d2 > tb.shell_out;
-                        in_core = keep && c_in;
-                        in_shell = keep && c_out && s_in;
-                        amb = keep && !c_in && !in_shell && !s_out;
+                            for (int u = 0; u < 4; ++u) {
+                                r[u] = trec[sp + done + u];
+                                if constexpr (decltype(with_excl)::value) id[u] = tid[sp + done + u];
+                            }
+#pragma unroll
+                            for (int u = 0; u < 4; ++u) {
+                                // squared separation - t_out, saturating
+                                int d = d2_minus(r[u].x, r[u].y, axy, az, t_out);
+                                if constexpr (decltype(with_excl)::value) d = id[u] != amol ? d : INT32_MAX;
+                                in_p = shift_sign(in_p, d);
+                                in_d = shift_sign(in_d, d + t_width);
+                                if constexpr (decltype(with_core)::value) {
+                                    const int c = __builtin_elementwise_add_sat(d, c_off);
+                                    co_p = shift_sign(co_p, c);
+                                    co_d = shift_sign(co_d, c + c_width);
+                                    if (MODE == kListsSplitSkin) {
+                                        const int l = __builtin_elementwise_add_sat(d, l_off);
+                                        lo_p = shift_sign(lo_p, l);
+                                        lo_d = shift_sign(lo_d, l + l_width);
+                                    }
+                                }
+                            }
+                            done += 4;
+                        } while (done < kLanePass && ballot(mine > done) != 0);
+                    };
+                    using yes = std::true_type;
+                    using no = std::false_type;
+                    if (excl) {
+                        if (kTwoLists && core_row) candidates(yes{}, yes{});
+                        else candidates(no{}, yes{});
                     } else {
-                        in_shell = keep && d2 < tb.shell_in;
-                        amb = keep && !in_shell && d2 <= tb.shell_out;
+                        if (kTwoLists && core_row) candidates(yes{}, no{});
+                        else candidates(no{}, no{});
                     }
-                    if (amb) {
-                        // between the bounds: the exact test on full positions decides
-                        const uint4 sj = spos[(int)r.w];
-                        const int32_t dx = (int32_t)(sj.x - si.x);
-                        const int32_t dy2 = (int32_t)(sj.y - si.y);
-                        const int32_t dz2 = (int32_t)(sj.z - si.z);
-                        const uint64_t d2x = (uint64_t)((int64_t)dx * dx) + (uint64_t)((int64_t)dy2 * dy2) +
-                                             (uint64_t)((int64_t)dz2 * dz2);
-                        in_core = MODE != kListsFull && d2x <= t_core;
-                        in_shell = MODE != kListsCoreOnly &&
-                                   (MODE == kListsSplitSkin ? d2x > t_lo : !in_core) && d2x <= t_shell;
+                    // the first candidate to the lowest bit
+                    uint32_t valid = (1u << mine) - 1u;
+                    if (!excl && dz == 0 && dy == 0) {
+                        // without excluded pairs only the atom itself is no candidate
+                        const int self = (k >= jA && k < jA + nA ? k - jA : k - jB + nA) - base - sp;
+                        if (self >= 0 && self < mine) valid &= ~(1u << self);
                     }
-                    if (MODE != kListsCoreOnly && in_shell) {
-                        myring[cs & (kRing - 1)] = (int32_t)r.w;
-                        ++cs;
+                    const int down = 32 - done;
+                    in_p = (__builtin_bitreverse32(in_p) >> down) & valid;
+                    in_d = (__builtin_bitreverse32(in_d) >> down) & in_p;
+                    co_p = (__builtin_bitreverse32(co_p) >> down) & valid;
+                    co_d = (__builtin_bitreverse32(co_d) >> down) & co_p;
+                    lo_p = (__builtin_bitreverse32(lo_p) >> down) & valid;
+                    lo_d = (__builtin_bitreverse32(lo_d) >> down) & lo_p;
+                    // certain members, and the candidates between two bounds (cells two or more
+                    // apart are farther than the core radius: the other rows have no core bound)
+                    uint32_t in_list = MODE == kListsSplitSkin ? in_d & ~lo_p : in_d & ~co_p;
+                    uint32_t in_core = co_d;
+                    uint32_t amb = (in_p & ~in_d) | (co_p & ~co_d) | (lo_p & ~lo_d);
+                    // sorted index of candidate p: p + jdA before the segments' border, p + jdB from it on
+                    const int border = nA - base - sp, jdA = jA + base + sp, jdB = jB + base + sp - nA;
+                    while (ballot(amb != 0) != 0) {
+                        if (amb != 0) {
+                            // between the bounds: the exact test on full positions decides
+                            const int p = __builtin_ctz(amb);
+                            const uint32_t bit = amb & -amb;
+                            amb ^= bit;
+                            const uint4 sj = spos[p + (p < border ? jdA : jdB)];
+                            const int32_t dx = (int32_t)(sj.x - si.x);
+                            const int32_t dy2 = (int32_t)(sj.y - si.y);
+                            const int32_t dz2 = (int32_t)(sj.z - si.z);
+                            const uint64_t d2x = (uint64_t)((int64_t)dx * dx) + (uint64_t)((int64_t)dy2 * dy2) +
+                                                 (uint64_t)((int64_t)dz2 * dz2);
+                            const bool c = d2x <= t_core;
+                            const bool l = MODE == kListsCoreOnly ? c
+                                           : d2x <= t_shell && (MODE == kListsFull ||
+                                                                (MODE == kListsSplitSkin ? d2x > t_lo : !c));
+                            in_list = l ? in_list | bit : in_list & ~bit;
+                            if (kTwoLists) in_core = c && core_row ? in_core | bit : in_core & ~bit;
+                        }
                     }
-                    if (MODE != kListsFull && core_row && in_core) {
-                        if (cc < cap_core) crow[cc] = (int32_t)r.w;
-                        ++cc;
+                    uint32_t to_core = MODE == kListsCoreOnly ? in_list : in_core;
+                    while (MODE != kListsFull && ballot(to_core != 0) != 0) {
+                        if (to_core != 0) {
+                            const int p = __builtin_ctz(to_core);
+                            to_core &= to_core - 1u;
+                            if (cc < cap_core) crow[cc] = p + (p < border ? jdA : jdB);
+                            ++cc;
+                        }
                     }
-                    if (MODE != kListsCoreOnly && (st & (kSeg - 1)) == kSeg - 1) {
-                        // lanes with a full segment store it (at most one per kSeg steps)
-                        if (cs - fs >= kSeg) {
-                            const int o = fs & (kRing - 1);
-                            if (fs + kSeg <= cap_shell)
-                                *(int4*)(srow + fs) = make_int4(myring[o], myring[o + 1], myring[o + 2], myring[o + 3]);
-                            fs += kSeg;
+                    int left = MODE != kListsCoreOnly ? __popc(in_list) : 0;
+                    while (MODE != kListsCoreOnly && ballot(left > 0) != 0) {
+                        int32_t* const at = mine_st + wait;
+#pragma unroll
+                        for (int u = 0; u < kAppend; ++u) {
+                            // (a lane with none left fills unused places)
+                            const int p = __builtin_ctz(in_list | 0x80000000u);
+                            at[u] = p + (p < border ? jdA : jdB);
+                            in_list &= in_list - 1u;
+                        }
+                        const int more = min(max(left, 0), kAppend);
+                        left -= kAppend;
+                        wait += more;
+                        // a lane with a full segment stores it and keeps the rest
+                        if (wait >= kSeg) {
+                            if (cs + kSeg <= cap_shell) {
+#pragma unroll
+                                for (int e = 0; e < kSeg; e += 4)
+                                    *(int4*)(srow + cs + e) = make_int4(mine_st[e], mine_st[e + 1], mine_st[e + 2],
+                                                                        mine_st[e + 3]);
+                            }
+#pragma unroll
+                            for (int e = 0; e < kAppend - 1; ++e) mine_st[e] = mine_st[kSeg + e];
+                            cs += kSeg;
+                            wait -= kSeg;
                         }
                     }
                 }
-                if (MODE != kListsCoreOnly) {
-                    // at most one full segment waits after the last step
-                    if (cs - fs >= kSeg) {
-                        const int o = fs & (kRing - 1);
-                        if (fs + kSeg <= cap_shell)
-                            *(int4*)(srow + fs) = make_int4(myring[o], myring[o + 1], myring[o + 2], myring[o + 3]);
-                        fs += kSeg;
-                    }
-                }
             }
-            rc = rn;
-            dz = dz_n;
-            dy = dy_n;
-            u_lo = u_lo_n;
-            u_hi = u_hi_n;
-            need = need_n;
         }
         if (MODE != kListsCoreOnly) {
             // the last, partial segment
-            for (int e = fs; e < cs; ++e)
-                if (e < cap_shell) srow[e] = myring[e & (kRing - 1)];
+            for (int e = 0; e < wait; ++e)
+                if (cs + e < cap_shell) srow[cs + e] = mine_st[e];
+            cs += wait;
         }
         if (act) {
             store_counts<MODE>(k, cc, cs, cap_core, cap_shell, ncore, nshell, err);
             maxc = max(maxc, cc);
             maxs = max(maxs, cs);
+        }
+        s = a1;
+        if (s == e) {
+            part += parts;
+            s = r0 + part * run;
+            e = min(s + run, r1);
         }
         __syncthreads();
     }
@@ -510,28 +583,26 @@ static hipError_t launch_list_lanes(irbe_ctx* h)
 {
     const Geometry g = list_geometry(h);
     const int n_c = g.n_c;
-    // cells per wavefront: groups of about kLaneGroupAtoms atoms, the union x range of
-    // the group's stencils within one period of the box and its cell starts within
-    // 64 LDS words, and the groups of a cell row balanced (a short last group leaves
-    // its wavefront mostly idle)
-    const double per_cell = (double)h->cfg.n_atoms / (double)g.n_cells;
-    const int g_want = (int)std::lround(std::min(64.0, std::max(1.0, kLaneGroupAtoms / std::max(per_cell, 0.75))));
-    const int g_cap = std::min(std::max(1, std::min(g_want, n_c - 2 * g.reach)), 64 - (g.hi - g.lo + 1));
-    const int groups_per_row = (n_c + g_cap - 1) / g_cap;
-    const int G = (n_c + groups_per_row - 1) / groups_per_row;
-    const int64_t groups = (int64_t)n_c * n_c * ((n_c + G - 1) / G);
+    // cells of a wavefront's run: the union x range of their stencils within one period
+    // of the box and its cell starts within 64 LDS words
+    const int G = std::max(1, std::min(n_c - 2 * g.reach, 64 - (g.hi - g.lo + 1)));
+    // wavefronts per cell row: its runs of 64 atoms, with two standard deviations of a
+    // random system's rows (fuller rows: their wavefronts take further runs)
+    const double per_row = (double)h->cfg.n_atoms / ((double)n_c * n_c);
+    const int parts = (int)std::ceil((per_row + 2.0 * std::sqrt(per_row)) / kListWave);
+    const int64_t groups = (int64_t)n_c * n_c * parts;
     // the packed records as for one cell per group: only a lane's own candidates
     // (within the stencil of its cell) are tested, so 16-bit differences of the
     // global coordinates are exact
     const PackedGeometry pl = packed_geometry(g);
-    // FP32 threshold of the outermost list with a relative margin of 2e-6, far
-    // above the FP32 rounding of the row gaps: the row pruning never drops a member.
-    const float tf_hi = (float)(h->stencil ? g.tl_core : g.tl_shell) * 1.000002f;
+    // the outermost list's radius in cell edges, with the margin of the row pruning
+    const double r_cells = std::sqrt((double)(h->stencil ? g.tl_core : g.tl_shell)) * n_c / 4294967296.0 + kPruneMargin;
+    const float r2_cells = (float)(r_cells * r_cells);
     k_pack_sorted<<<(unsigned)blocks_for(h->cfg.n_atoms, kBlock), kBlock, 0, h->stream>>>(
         h->cfg.n_atoms, pl.sh, h->spos, h->smol, (u32x4*)h->spk);
 #define IRBE_LANES_ARGS                                                                                            \
-    n_c, g.lo, g.hi, G, pl.tb, g.tl_core, g.tl_lo, g.tl_shell, tf_hi, h->spos, (const u32x4*)h->spk, h->cell_start, \
-        h->cell_bound, h->cap_core, h->cap_shell, h->core, h->ncore, h->shell, h->nshell, h->maxcnt, h->err
+    n_c, g.lo, g.hi, G, parts, pl.tb, g.tl_core, g.tl_lo, g.tl_shell, r2_cells, h->n_excl > 0, h->spos, (const u32x4*)h->spk, h->cell_start, \
+        h->cap_core, h->cap_shell, h->core, h->ncore, h->shell, h->nshell, h->maxcnt, h->err
     if (h->full_list)
         k_build_lists_lanes<kListsFull><<<(unsigned)groups, kListWave, 0, h->stream>>>(IRBE_LANES_ARGS);
     else if (h->stencil)
