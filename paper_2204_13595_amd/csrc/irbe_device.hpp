@@ -25,8 +25,8 @@ __device__ __forceinline__ Words4 philox10(uint32_t c0, uint32_t c1, uint32_t c2
         const uint64_t p1 = (uint64_t)0xCD9E8D57u * c2;
         const uint32_t lo0 = (uint32_t)p0, hi0 = (uint32_t)(p0 >> 32);
         const uint32_t lo1 = (uint32_t)p1, hi1 = (uint32_t)(p1 >> 32);
-        const uint32_t n0 = hi1 ^ c1 ^ k0;
-        const uint32_t n2 = hi0 ^ c3 ^ k1;
+        const uint32_t n0 = __builtin_amdgcn_bitop3_b32(hi1, c1, k0, 0x96);  // hi1 ^ c1 ^ k0
+        const uint32_t n2 = __builtin_amdgcn_bitop3_b32(hi0, c3, k1, 0x96);  // hi0 ^ c3 ^ k1
         c0 = n0;
         c1 = lo1;
         c2 = n2;
@@ -145,7 +145,7 @@ __device__ __forceinline__ void lane_swap(uint32_t x, uint32_t& a, uint32_t& b)
         // (once the values repeat every 2 OFF lanes, rotating a row by OFF is the exchange with lane ^ OFF)
         constexpr int ctrl = OFF == 8 ? 0x128 : (OFF == 4 ? 0x124 : (OFF == 2 ? 0x4e : 0xb1));
         a = x;
-        b = (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, ctrl, 0xf, 0xf, false);
+        b = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, ctrl, 0xf, 0xf, true);
     }
 }
 
@@ -177,6 +177,43 @@ __device__ __forceinline__ T wave_sum(T v)
 {
     v = butterfly_add<32>(v);
     v = butterfly_add<16>(v);
+    v = butterfly_add<8>(v);
+    v = butterfly_add<4>(v);
+    v = butterfly_add<2>(v);
+    return butterfly_add<1>(v);
+}
+
+// Two values at once: the first halves of each 2 OFF lanes get a's sums over the
+// lane distance OFF (32 or 16), the second halves b's.
+template <int OFF>
+__device__ __forceinline__ float merge_add(float a, float b)
+{
+    const auto s = OFF == 32 ? __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false)
+                             : __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(s[0]) + __uint_as_float(s[1]);
+}
+
+template <int OFF>
+__device__ __forceinline__ double merge_add(double a, double b)
+{
+    const unsigned long long u = (unsigned long long)__double_as_longlong(a);
+    const unsigned long long v = (unsigned long long)__double_as_longlong(b);
+    const auto l = OFF == 32 ? __builtin_amdgcn_permlane32_swap((uint32_t)u, (uint32_t)v, false, false)
+                             : __builtin_amdgcn_permlane16_swap((uint32_t)u, (uint32_t)v, false, false);
+    const auto h =
+        OFF == 32 ? __builtin_amdgcn_permlane32_swap((uint32_t)(u >> 32), (uint32_t)(v >> 32), false, false)
+                  : __builtin_amdgcn_permlane16_swap((uint32_t)(u >> 32), (uint32_t)(v >> 32), false, false);
+    return __longlong_as_double((long long)(((unsigned long long)h[0] << 32) | l[0])) +
+           __longlong_as_double((long long)(((unsigned long long)h[1] << 32) | l[1]));
+}
+
+// Four sums over the wavefront, each bit for bit wave_sum's: that of v0 in the first
+// row of 16 lanes, of v1 in the second, of v2 in the third, of v3 in the fourth. One
+// tree instead of four: 15 vector instructions in FP32 where four take 56.
+template <typename T>
+__device__ __forceinline__ T wave_sum4(T v0, T v1, T v2, T v3)
+{
+    T v = merge_add<16>(merge_add<32>(v0, v2), merge_add<32>(v1, v3));
     v = butterfly_add<8>(v);
     v = butterfly_add<4>(v);
     v = butterfly_add<2>(v);

@@ -673,7 +673,9 @@ __global__ __launch_bounds__(kCoopBlock, ENC && !EV && sizeof(real) == 4 ? 5 : 1
     const int64_t gw = blk * (kCoopBlock / 64) + wave;
     const int64_t a0 = gw * apw;
     const int64_t a1 = min(n, a0 + apw);
-    double fc_sum[3] = {0.0, 0.0, 0.0};
+    // lanes 0, 16 and 32 keep the force sums' components (wave_sum4)
+    const int f_comp = (lane & 15) == 0 && lane < 48 ? lane >> 4 : -1;
+    double fc_sum = 0.0;
     PairSum<real> ev;  // per-lane energy/virial totals (forces unused)
     const Atoms<real> at{spos, sqr, spq};
     // per-atom headers of the wavefront's atoms, one atom per lane, read once
@@ -803,16 +805,10 @@ __global__ __launch_bounds__(kCoopBlock, ENC && !EV && sizeof(real) == 4 ? 5 : 1
                 if (in && (ex || !SKIN || dist2_q(si, sj) <= t_shell))
                     add_pair_or_excl<real, kFused>(pc, px, si, qi, sj, q, lrow[sj.w], pp, ex);
             }
-            const real fx = pp.quantum * wave_sum(pc.fx);
-            const real fy = pp.quantum * wave_sum(pc.fy);
-            const real fz = pp.quantum * wave_sum(pc.fz);
-            if (lane == 0) {
-                fsr[3 * a + 0] = fx;
-                fsr[3 * a + 1] = fy;
-                fsr[3 * a + 2] = fz;
-                fc_sum[0] += (double)fx;
-                fc_sum[1] += (double)fy;
-                fc_sum[2] += (double)fz;
+            const real f = pp.quantum * wave_sum4(pc.fx, pc.fy, pc.fz, pc.fz);
+            if (f_comp >= 0) {
+                fsr[3 * a + f_comp] = f;
+                fc_sum += (double)f;
             }
         }
     }
@@ -950,16 +946,11 @@ __global__ __launch_bounds__(kCoopBlock, ENC && !EV && sizeof(real) == 4 ? 5 : 1
         // one set of sums: the excluded-pair forces cancel pairwise, so the momentum
         // correction may sum them with the rest
         const real fu = kFused ? pp.quantum : (real)1;
-        const real fx = fu * wave_sum(pc.fx + w * ps.fx + px.fx);
-        const real fy = fu * wave_sum(pc.fy + w * ps.fy + px.fy);
-        const real fz = fu * wave_sum(pc.fz + w * ps.fz + px.fz);
-        if (lane == 0) {
-            fsr[3 * a + 0] = fx;
-            fsr[3 * a + 1] = fy;
-            fsr[3 * a + 2] = fz;
-            fc_sum[0] += (double)fx;
-            fc_sum[1] += (double)fy;
-            fc_sum[2] += (double)fz;
+        const real tz = pc.fz + w * ps.fz + px.fz;
+        const real f = fu * wave_sum4(pc.fx + w * ps.fx + px.fx, pc.fy + w * ps.fy + px.fy, tz, tz);
+        if (f_comp >= 0) {
+            fsr[3 * a + f_comp] = f;
+            fc_sum += (double)f;
         }
         if (EV) {
             ev.uc += pc.uc + w * ps.uc;
@@ -969,11 +960,10 @@ __global__ __launch_bounds__(kCoopBlock, ENC && !EV && sizeof(real) == 4 ? 5 : 1
             for (int c = 0; c < 6; ++c) ev.v[c] += pc.v[c] + w * ps.v[c] + px.v[c];
         }
     }
-    // per-block sums: the force sums sit in one lane per wavefront; with energies nine
-    // more values, summed over the lanes
+    // per-block sums: the force sums sit in one lane per component and wavefront; with
+    // energies nine more values, summed over the lanes
     constexpr int NW = kCoopBlock / 64;
-    if (lane == 0)
-        for (int c = 0; c < 3; ++c) red[c * NW + wave] = fc_sum[c];
+    if (f_comp >= 0) red[f_comp * NW + wave] = fc_sum;
     if (EV) {
         double vals[9];
         vals[0] = 0.5 * (double)ev.uc;
@@ -1829,25 +1819,19 @@ __global__ __launch_bounds__(kCoopBlock) void k_pair_adjoint(
                     if (!SKIN || in_annulus(si, sj, t_core, t_shell)) shell_pair(j, sj, qj);
                 }
             }
-        rx = wave_sum(rx);
-        ry = wave_sum(ry);
-        rz = wave_sum(rz);
-        rq = ke * wave_sum(rq);
-        if (lane == 0) {
-            gself[3 * a + 0] = rx;
-            gself[3 * a + 1] = ry;
-            gself[3 * a + 2] = rz;
-            gqself[a] = rq;
+        const real r = wave_sum4(rx, ry, rz, rq);
+        if ((lane & 15) == 0) {
+            if (lane < 48) gself[3 * a + (lane >> 4)] = r;
+            else gqself[a] = ke * r;
         }
         if (lj_i && ti < kMaxTypesGrad) {
-#pragma unroll
-            for (int t = 0; t < kMaxTypesGrad; ++t) {
-                const real s_sig = wave_sum(acc_sig[t]);
-                const real s_eps = wave_sum(acc_eps[t]);
-                if (lane == 0) {
-                    ljacc[wave][ti * kMaxTypesGrad + t] += (double)s_sig;
-                    ljacc[wave][kMaxTypesGrad * kMaxTypesGrad + ti * kMaxTypesGrad + t] += (double)s_eps;
-                }
+            static_assert(kMaxTypesGrad == 4, "one row of lanes per partner type");
+            const real s_sig = wave_sum4(acc_sig[0], acc_sig[1], acc_sig[2], acc_sig[3]);
+            const real s_eps = wave_sum4(acc_eps[0], acc_eps[1], acc_eps[2], acc_eps[3]);
+            if ((lane & 15) == 0) {
+                const int t = ti * kMaxTypesGrad + (lane >> 4);
+                ljacc[wave][t] += (double)s_sig;
+                ljacc[wave][kMaxTypesGrad * kMaxTypesGrad + t] += (double)s_eps;
             }
         }
     }
