@@ -452,28 +452,30 @@ void lj_tables(const irbe_ctx* h, std::vector<LJ<real>>& tab, std::vector<real>&
     }
 }
 
-irbe_status upload_lj(irbe_ctx* h)
+// The tables to the device: as the arguments of a kernel where they fit (up to
+// kLjArgTypes types), in stream order and without a wait; otherwise, and into a
+// stream under capture, by copies and a wait for them.
+template <typename real>
+hipError_t upload_lj_t(irbe_ctx* h)
 {
     const int nt2 = h->cfg.n_types * h->cfg.n_types;
-    if (h->fp64) {
-        std::vector<LJ<double>> tab;
-        std::vector<double> raw;
-        lj_tables(h, tab, raw);
-        IRBE_TRY(h, hipMemcpyAsync(h->lj, tab.data(), sizeof(LJ<double>) * nt2, hipMemcpyHostToDevice, h->stream),
-                 "upload LJ");
-        IRBE_TRY(h, hipMemcpyAsync(h->lj_raw, raw.data(), sizeof(double) * 2 * nt2, hipMemcpyHostToDevice, h->stream),
-                 "upload LJ");
-        IRBE_TRY(h, hipStreamSynchronize(h->stream), "upload LJ");
-    } else {
-        std::vector<LJ<float>> tab;
-        std::vector<float> raw;
-        lj_tables(h, tab, raw);
-        IRBE_TRY(h, hipMemcpyAsync(h->lj, tab.data(), sizeof(LJ<float>) * nt2, hipMemcpyHostToDevice, h->stream),
-                 "upload LJ");
-        IRBE_TRY(h, hipMemcpyAsync(h->lj_raw, raw.data(), sizeof(float) * 2 * nt2, hipMemcpyHostToDevice, h->stream),
-                 "upload LJ");
-        IRBE_TRY(h, hipStreamSynchronize(h->stream), "upload LJ");
-    }
+    std::vector<LJ<real>> tab;
+    std::vector<real> raw;
+    lj_tables(h, tab, raw);
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    hipError_t e = hipStreamIsCapturing(h->stream, &cap);
+    if (e != hipSuccess) return e;
+    if (h->cfg.n_types <= kLjArgTypes && cap == hipStreamCaptureStatusNone)
+        return launch_store_lj<real>(h, tab.data(), raw.data());
+    e = hipMemcpyAsync(h->lj, tab.data(), sizeof(LJ<real>) * nt2, hipMemcpyHostToDevice, h->stream);
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(h->lj_raw, raw.data(), sizeof(real) * 2 * nt2, hipMemcpyHostToDevice, h->stream);
+    return e == hipSuccess ? hipStreamSynchronize(h->stream) : e;
+}
+
+irbe_status upload_lj(irbe_ctx* h)
+{
+    IRBE_TRY(h, h->fp64 ? upload_lj_t<double>(h) : upload_lj_t<float>(h), "upload LJ");
     return IRBE_OK;
 }
 

@@ -34,6 +34,7 @@ constexpr int kMaskMaxWords = 256;
 constexpr int kBlock = 256;          // threads per block of the per-atom kernels
 constexpr int kReduceBlock = 256;    // threads of the deterministic final reductions
 constexpr int kPairPartials = 16;    // FP64 values per block of the pair kernel
+constexpr int kLjArgTypes = 4;       // LJ tables of up to this many types are kernel arguments
 constexpr int kMaxTypesGrad = 4;     // LJ parameter gradients: n_types <= 4
 // atoms per wavefront in the cooperative pair kernels: the adjoint, the forward
 // kernel with list-drawn batches, and the forward kernel with stencil sampling
@@ -306,6 +307,8 @@ hipError_t launch_pair_reduce(irbe_ctx* h, bool ev);
 hipError_t launch_kspace_forces(irbe_ctx* h, void* force);
 hipError_t launch_energy_finalize(irbe_ctx* h, double* ev);
 hipError_t launch_sum_q2(irbe_ctx* h);
+template <typename real>
+hipError_t launch_store_lj(irbe_ctx* h, const LJ<real>* tab, const real* raw);
 hipError_t launch_gather_grad(irbe_ctx* h, const void* grad);
 hipError_t launch_pair_adjoint(irbe_ctx* h, uint64_t step, bool want_q, bool want_lj);
 // Grow the shell-adjoint record buckets to hold `records` records.

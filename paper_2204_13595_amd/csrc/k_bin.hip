@@ -2,6 +2,7 @@
 // positions, cell histogram, exclusive scan, scatter, in-cell ordering by
 // (x coordinate, atom id), and the gather of a cell-sorted structure-of-arrays
 // copy of the system.
+#include <algorithm>
 #include <type_traits>
 
 #include "irbe_device.hpp"
@@ -488,5 +489,36 @@ hipError_t launch_sum_q2(irbe_ctx* h)
     k_sum_part<<<1, kReduceBlock, 0, h->stream>>>(nb, h->q2part, h->sumq2);
     return hipGetLastError();
 }
+
+// The LJ tables as kernel arguments (at most 1 KiB).
+template <typename real>
+struct LjArg {
+    LJ<real> tab[kLjArgTypes * kLjArgTypes];
+    real raw[2 * kLjArgTypes * kLjArgTypes];
+};
+
+template <typename real>
+__global__ __launch_bounds__(64) void k_store_lj(LjArg<real> a, int nt2, LJ<real>* __restrict__ tab,
+                                                 real* __restrict__ raw)
+{
+    const int t = threadIdx.x;
+    if (t < nt2) tab[t] = a.tab[t];
+    if (t < 2 * nt2) raw[t] = a.raw[t];
+}
+
+template <typename real>
+hipError_t launch_store_lj(irbe_ctx* h, const LJ<real>* tab, const real* raw)
+{
+    const int nt2 = h->cfg.n_types * h->cfg.n_types;
+    if (h->cfg.n_types > kLjArgTypes) return hipErrorInvalidValue;
+    LjArg<real> a{};
+    std::copy(tab, tab + nt2, a.tab);
+    std::copy(raw, raw + 2 * nt2, a.raw);
+    k_store_lj<real><<<1, 64, 0, h->stream>>>(a, nt2, (LJ<real>*)h->lj, (real*)h->lj_raw);
+    return hipGetLastError();
+}
+
+template hipError_t launch_store_lj<float>(irbe_ctx*, const LJ<float>*, const float*);
+template hipError_t launch_store_lj<double>(irbe_ctx*, const LJ<double>*, const double*);
 
 }  // namespace irbe

@@ -286,6 +286,15 @@ class Handle:
             pass
 
 
+def _tables_on_host(lj_sigma: torch.Tensor, lj_eps: torch.Tensor):
+    """The values of both LJ tables, in one copy (and wait) where they are alike."""
+    s, e = lj_sigma.detach().reshape(-1), lj_eps.detach().reshape(-1)
+    if s.device == e.device and s.dtype == e.dtype:
+        both = torch.cat((s, e)).cpu().numpy()
+        return both[:s.numel()], both[s.numel():]
+    return s.cpu().numpy(), e.cpu().numpy()
+
+
 class IRBEForce(torch.autograd.Function):
     """F = IRBE force(pos, charge, LJ tables) at the samples of ``step`` and the
     lists of the handle's last build; backward gives dL/dpos, dL/dcharge and
@@ -293,11 +302,12 @@ class IRBEForce(torch.autograd.Function):
 
     @staticmethod
     def forward(ctx, pos, charge, lj_sigma, lj_eps, handle: Handle, step: int):
-        handle.update_parameters(charge=charge.detach().contiguous(), lj_sigma=lj_sigma.detach().cpu().numpy(),
-                                 lj_eps=lj_eps.detach().cpu().numpy())
+        sigma, eps = _tables_on_host(lj_sigma, lj_eps)
+        handle.update_parameters(charge=charge.detach().contiguous(), lj_sigma=sigma, lj_eps=eps)
         f = handle.compute_forces(pos.detach().contiguous(), step)
         ctx.handle = handle
         ctx.step = step
+        ctx.lj_host = (sigma, eps)  # the tables' values at the forward, which the backward takes again
         ctx.save_for_backward(pos, charge, lj_sigma, lj_eps)
         return f
 
@@ -305,8 +315,11 @@ class IRBEForce(torch.autograd.Function):
     def backward(ctx, grad_f):
         pos, charge, lj_sigma, lj_eps = ctx.saved_tensors
         h: Handle = ctx.handle
-        h.update_parameters(charge=charge.detach().contiguous(), lj_sigma=lj_sigma.detach().cpu().numpy(),
-                            lj_eps=lj_eps.detach().cpu().numpy())
+        current = torch.cuda.current_stream(h.device)
+        if current != h.stream:
+            current.synchronize()  # the handle's stream reads the gradient that this one may still compute
+        sigma, eps = ctx.lj_host
+        h.update_parameters(charge=charge.detach().contiguous(), lj_sigma=sigma, lj_eps=eps)
         gp, gq, gl = h.compute_forces_backward(pos.detach().contiguous(), ctx.step, grad_f.contiguous(),
                                                want_charge=True, want_lj=True)
         nt2 = h.n_types ** 2
