@@ -117,7 +117,7 @@ struct RowLoad {
     u32x4 rec[kLaneTile / kListWave];
 };
 
-// (six wavefronts per SIMD: what the stage leaves of LDS; more registers' worth of them spill)
+// (six wavefronts per SIMD, what the stage leaves of LDS: the register bounds of seven and eight spill)
 template <int MODE>
 __global__ __launch_bounds__(kListWave, 6) void k_build_lists_lanes(
     int n_c, int lo, int hi, int G, int parts, PackedBounds tb, uint64_t t_core, uint64_t t_lo, uint64_t t_shell, float r2_cells, bool excl,

@@ -1235,6 +1235,18 @@ static hipError_t launch_draw(irbe_ctx* h, uint64_t step)
     return e;
 }
 
+// Atoms per wavefront of a small system's forces: halved (down to 2, which the per-block
+// sums are sized for) while fewer than kWavesWanted wavefronts, four per SIMD, would run.
+// 2,703 atoms: 29 -> 10 us with 2 instead of 8; 1,536 atoms, full lists and energies in
+// FP64: 40 -> 23 us; 12,288 atoms: 26 -> 17 us.
+constexpr int64_t kWavesWanted = 4096;
+
+static int spread_atoms(int64_t n, int apw)
+{
+    while (apw > 2 && blocks_for(n, apw) < kWavesWanted) apw = std::max(2, apw / 2);
+    return apw;
+}
+
 template <typename real, bool FULL, bool EV, bool STENCIL, bool SKIN, bool ENC = false>
 static hipError_t launch_coop_t(irbe_ctx* h, uint64_t step)
 {
@@ -1244,7 +1256,9 @@ static hipError_t launch_coop_t(irbe_ctx* h, uint64_t step)
     if (e != hipSuccess) return e;
     // stencil sampling keeps one cell's stencil rows for consecutive atoms: longer
     // runs of atoms per wavefront pay there, shorter ones with list-drawn batches
-    const int apw = STENCIL ? kAtomsPerWaveStencil : (FULL ? kAtomsPerWaveList : kAtomsPerWaveSplit);
+    // (the FP32 energies add up over a wavefront's atoms in FP32: their runs stay as they are)
+    int apw = STENCIL ? kAtomsPerWaveStencil : (FULL ? kAtomsPerWaveList : kAtomsPerWaveSplit);
+    if (!EV || sizeof(real) == 8) apw = spread_atoms(n, apw);
     const int64_t waves = blocks_for(n, apw);
     const unsigned nb = (unsigned)blocks_for(waves, kCoopBlock / 64);
     if ((int64_t)nb > h->part_blocks) return hipErrorInvalidValue;
