@@ -337,6 +337,87 @@ __global__ __launch_bounds__(BLOCK) void k_draw_batches(int64_t n, const int32_t
     floyd_row_lds(k, ns, perm, p_shell, p_stride, seed, step, bitmap + threadIdx.x, BLOCK, ranks);
 }
 
+// The same for systems that leave the chip idle at one thread per atom: half a
+// wavefront per atom, lane l drawing steps 4 l .. 4 l + 3 from block l of the atom's
+// words (at most 128 steps). Floyd's rule without the order of the steps: the draw r
+// of step c is taken when an earlier step drew r too, or when r = t0 + c' is the t of
+// an earlier step c' whose draw was taken. The first comes from the smallest step of
+// each value (LDS minimum), the second by repetition until nothing changes. A half
+// that meets the rejection test of the multiply-shift takes the one-step form.
+// What bounds the other form there is one thread's chain of 25 blocks and bitmap round
+// trips, about 14 us for 100 draws however few the atoms. One thread against half a
+// wavefront: 14.3 and 4.8 us at 2,703 atoms, 14.9 and 7.8 at 12,288, but 29.6 and 33.3
+// at 98,304, where this form's idle lanes (25 of 32 draw) cost more than the chain.
+constexpr int kHalfDrawBlock = 256;
+constexpr int kHalfDrawMost = 128;         // steps
+constexpr int64_t kHalfDrawAtoms = 32768;
+
+__global__ __launch_bounds__(kHalfDrawBlock) void k_draw_batches_half(int64_t n, const int32_t* __restrict__ perm,
+                                                                      const int32_t* __restrict__ nshell, int p_shell,
+                                                                      int p_stride, uint64_t seed, uint64_t step,
+                                                                      int table, uint16_t* __restrict__ ranks)
+{
+    extern __shared__ uint32_t bitmap[];
+    const int half = (int)threadIdx.x >> 5, l = (int)threadIdx.x & 31;
+    const int64_t k = (int64_t)blockIdx.x * (kHalfDrawBlock / 32) + half;
+    if (k >= n) return;
+    const int ns = nshell[k];
+    if (ns <= p_shell) return;
+    uint32_t* const first = bitmap + half * table;  // [ns] smallest step that drew the value
+    const int t0 = ns - p_shell;
+    const Words4 w = philox10((uint32_t)perm[k], (uint32_t)l, (uint32_t)step,
+                              ((uint32_t)(step >> 32) << 1) | kTagShell, (uint32_t)seed, (uint32_t)(seed >> 32));
+    const uint32_t words[4] = {w.x, w.y, w.z, w.w};
+    int r[4];
+    bool in[4], taken[4], reject = false;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int c = 4 * l + u;
+        in[u] = c < p_shell;
+        const uint32_t bound = (uint32_t)(t0 + c) + 1u;
+        const uint64_t m = (uint64_t)words[u] * bound;
+        r[u] = in[u] ? (int)(m >> 32) : 0;
+        if (in[u] && (uint32_t)m < bound && (uint32_t)m < (0u - bound) % bound) reject = true;
+    }
+    // (the lanes of a half run together: the LDS operations below take effect in program order)
+    const uint64_t half_mask = 0xffffffffull << (threadIdx.x & 32);
+    if ((__builtin_amdgcn_ballot_w64(reject) & half_mask) != 0) {
+        if (l == 0) floyd_row(k, ns, perm, p_shell, p_stride, seed, step, first, 1, ranks);
+        return;
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+        if (in[u]) first[r[u]] = 0xffffffffu;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+        if (in[u]) atomicMin(&first[r[u]], (uint32_t)(4 * l + u));
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+    for (int u = 0; u < 4; ++u) taken[u] = in[u] && first[r[u]] != (uint32_t)(4 * l + u);
+    for (;;) {
+        // the taken steps of this half, one word per step of a lane
+        uint32_t word[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) word[u] = (uint32_t)(__builtin_amdgcn_ballot_w64(taken[u]) >> (threadIdx.x & 32));
+        bool more = false;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int c = r[u] - t0;  // the step whose t the draw is
+            if (!in[u] || taken[u] || c < 0 || c >= 4 * l + u) continue;
+            const uint32_t wc = (c & 2) ? ((c & 1) ? word[3] : word[2]) : ((c & 1) ? word[1] : word[0]);
+            if ((wc >> (c >> 2)) & 1u) taken[u] = more = true;
+        }
+        if ((__builtin_amdgcn_ballot_w64(more) & half_mask) == 0) break;
+    }
+    if (4 * l < p_shell) {
+        uint32_t v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = (uint32_t)(taken[u] ? t0 + 4 * l + u : r[u]);
+        *(uint2*)(ranks + k * (int64_t)p_stride + 4 * l) = make_uint2(v[0] | (v[1] << 16), v[2] | (v[3] << 16));
+    }
+}
+
 // The same with the bitmaps in device memory, for lists too long for LDS: a
 // grid of `threads` threads takes the atoms in turn, thread t's bitmap word w
 // at bits[w * threads + t].
@@ -1206,7 +1287,11 @@ static hipError_t launch_draw(irbe_ctx* h, uint64_t step)
     size_t lds = 0;
     const int block = draw_block(h, &lds);
     const unsigned nb = (unsigned)blocks_for(n, block);
-    if (lds > 64 * 1024) {
+    const size_t half_lds = (size_t)(kHalfDrawBlock / 32) * h->shell_bound() * 4;
+    if (n < kHalfDrawAtoms && h->cfg.p_shell <= kHalfDrawMost && half_lds <= 64 * 1024) {
+        k_draw_batches_half<<<(unsigned)blocks_for(n, kHalfDrawBlock / 32), kHalfDrawBlock, half_lds, h->stream>>>(
+            n, h->perm, h->nshell, h->cfg.p_shell, h->p_stride, h->cfg.seed, step, h->shell_bound(), h->ranks);
+    } else if (lds > 64 * 1024) {
         // bitmaps in device memory: as many threads as fit 1 GiB of bitmaps
         const int64_t threads = std::max<int64_t>(256, std::min<int64_t>(n, ((int64_t)1 << 28) / words) / 256 * 256);
         hipError_t e = ensure_draw_bits(h, (size_t)threads * (size_t)words);
