@@ -279,10 +279,16 @@ __global__ __launch_bounds__(kBlock) void k_cell_order(int64_t n, const int32_t*
     const uint4 s = sq[i];
     const int32_t b = cell_start[s.w], e = cell_start[s.w + 1];
     int32_t r = 0;
-    for (int32_t u = b; u < e; ++u) {
-        const int32_t o = in[u];
-        const uint32_t xo = sq[o].x;
-        r += (xo < s.x || (xo == s.x && o < i)) ? 1 : 0;
+    for (int32_t u = b; u < e; u += 4) {
+        // (four at a time, for their dependent loads: 0.119 -> 0.100 ms at 3.1M atoms)
+        int32_t o[4];
+        uint32_t xo[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) o[v] = in[min(u + v, e - 1)];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) xo[v] = sq[o[v]].x;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) r += (u + v < e && (xo[v] < s.x || (xo[v] == s.x && o[v] < i))) ? 1 : 0;
     }
     const int32_t k = b + r;
     perm[k] = i;
