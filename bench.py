@@ -531,20 +531,21 @@ def main():
         # algorithmic HBM bytes of the list build: each atom's position and molecule
         # id read once (20 B), its two counts and its list entries written. The
         # "lists" stage times the whole build: the packing of the per-atom records
-        # (k_pack_sorted, ~0.02 ms) and k_build_lists_tiled.
+        # (k_pack_sorted, ~0.02 ms) and k_list_blocks.
         # The count takes 4 bytes per list entry (lists as explicit CSR of indices);
-        # the build stores shell entries as 16-bit codes where it can, and the bytes
-        # as stored are reported beside it.
+        # the build stores shell lists as bit masks over each block's candidates where
+        # it can (shell_entry_bits 16), whose bytes are in the counters' traffic only;
+        # stored_bytes is given where the entries are indices.
         list_bytes = 20.0 * n + 8.0 * n + 4.0 * (n_core + n_shell)
-        stored_bytes = 20.0 * n + 8.0 * n + 4.0 * n_core + shell_bits / 8.0 * n_shell
+        stored_bytes = list_bytes if shell_bits == 32 else None
         lists_ms = st["lists"][0]
         roof = {
-            "kernel": "k_build_lists", "bound": "hbm", "achieved": list_bytes / (lists_ms * 1e-3) / 1e9,
-            "peak": HBM_PEAK_GBS, "unit": "GB/s", "traffic": measured_traffic("k_build_lists", args.workload),
+            "kernel": "k_list_blocks", "bound": "hbm", "achieved": list_bytes / (lists_ms * 1e-3) / 1e9,
+            "peak": HBM_PEAK_GBS, "unit": "GB/s", "traffic": measured_traffic("k_list_blocks", args.workload),
             "algorithmic_bytes": list_bytes, "avg_launch_ms": lists_ms,
             "algorithmic_basis": "20 B read + 8 B counts + 4 B per core or shell entry",
             "shell_entry_bits": shell_bits, "stored_bytes": stored_bytes,
-            "stored_frac": stored_bytes / (lists_ms * 1e-3) / 1e9 / HBM_PEAK_GBS,
+            "stored_frac": stored_bytes / (lists_ms * 1e-3) / 1e9 / HBM_PEAK_GBS if stored_bytes else None,
         }
         roof["frac"] = roof["achieved"] / roof["peak"]
         # measured ceilings of this GPU beside the published peaks (irbe_probe_rates):
