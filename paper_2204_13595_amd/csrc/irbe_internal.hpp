@@ -194,12 +194,12 @@ struct irbe_ctx {
     int32_t* blk_start = nullptr;     // [list_block_slots] first atom + 1 of the blocks of the list build
     int32_t* perm = nullptr;          // [N] sorted -> caller id
     int32_t* rank = nullptr;          // [N] caller id -> sorted
-    uint4* spos = nullptr;            // [N] sorted {sx, sy, sz, type}
+    uint4* spos = nullptr;            // [N] sorted {sx, sy, sz, type} (FP32: at the last build)
     uint4* spk = nullptr;             // [N] sorted packed records of the list build
     int32_t* brow = nullptr;          // [N] cell (z << 16 | y) at the build of each sorted atom (lists with a skin)
     uint4* spq = nullptr;             // [N] sorted {sx, sy, sz, FP32 charge with the type in its low 4 bits}
                                       //     (FP32 evaluations; the FP64 ones read spos and sq_r)
-    void* sq_r = nullptr;             // real[N] sorted charges
+    void* sq_r = nullptr;             // real[N] sorted charges (FP32: at the last build)
     int32_t* smol = nullptr;          // [N] sorted molecule ids
 
     int32_t* core = nullptr;          // [N * cap_core]

@@ -427,10 +427,14 @@ __global__ __launch_bounds__(kBlock) void k_requantize(int64_t n, const real* __
     const uint32_t sz = quantize1((double)pos[3 * i + 2], inv_l, bad);
     const int32_t k = rank[i];
     sq[i] = make_uint4(sx, sy, sz, sq[i].w);
-    spos[k] = make_uint4(sx, sy, sz, (uint32_t)type[i]);
-    sqr[k] = q[i];
-    if (std::is_same<real, float>::value)
-        spq[k] = pos_charge_record(make_uint4(sx, sy, sz, 0u), (float)q[i], type[i]);
+    // (FP32: the pair kernels read the one record; spos and sqr stay those of the build: scattered
+    // writes of 16 instead of 36 bytes per atom, 0.089 -> 0.051 ms at 3.1M atoms)
+    if constexpr (std::is_same<real, float>::value) {
+        spq[k] = pos_charge_record(make_uint4(sx, sy, sz, 0u), q[i], type[i]);
+    } else {
+        spos[k] = make_uint4(sx, sy, sz, (uint32_t)type[i]);
+        sqr[k] = q[i];
+    }
     if (bad) atomicOr(err, ERR_NONFINITE);
 }
 

@@ -1709,7 +1709,8 @@ __global__ __launch_bounds__(kCoopBlock) void k_pair_adjoint(
     if (BK) {
         const int64_t f = min(blk * NW * apw, n - 1);
         int z, y;
-        key_cell(bk, f, spos[f], z, y);
+        if constexpr (std::is_same<real, float>::value) key_cell(bk, f, spq[f], z, y);
+        else key_cell(bk, f, spos[f], z, y);
         row0 = z * bk.n_c + y;
     }
     real lane_max = 0;  // largest |component| of the records this lane staged
