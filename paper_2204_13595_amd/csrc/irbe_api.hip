@@ -766,6 +766,8 @@ irbe_status irbe_set_system(irbe_handle h, const int32_t* type, const void* char
     IRBE_TRY(h, launch_sum_q2(h), "sum q^2");
     const irbe_status st = upload_lj(h);
     if (st != IRBE_OK) return st;
+    // the copies above read the caller's arrays and this call's own tables
+    IRBE_TRY(h, hipStreamSynchronize(h->stream), "set_system");
     h->have_system = true;
     h->have_lists = false;
     return IRBE_OK;

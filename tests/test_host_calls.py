@@ -1,0 +1,50 @@
+"""What the library asks of the HIP runtime, in order (no GPU): hip_record.cpp defines
+the runtime functions, runs calls of the C ABI and prints each request."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+@pytest.fixture(scope="module")
+def record(tmp_path_factory):
+    """record(*commands): [(command, status, [request, ...]), ...]"""
+    from paper_2204_13595_amd import irbe
+    if not os.path.exists(irbe.LIB_PATH):
+        from paper_2204_13595_amd import build
+        build.build(verbose=False)
+    exe = str(tmp_path_factory.mktemp("hip_record") / "hip_record")
+    subprocess.run(["g++", "-std=c++17", "-O1", f"-I{os.path.join(ROOT, 'include')}",
+                    os.path.join(HERE, "hip_record.cpp"), "-rdynamic", "-ldl", "-o", exe], check=True)
+
+    def run(*commands):
+        r = subprocess.run([exe, irbe.LIB_PATH, *commands], capture_output=True, text=True, timeout=120)
+        assert r.returncode == 0, r.stdout + r.stderr
+        calls, requests = [], []
+        for line in r.stdout.splitlines():
+            if line.startswith("= "):
+                name, status = line[2:].rsplit(" ", 1)
+                calls.append((name, int(status), requests))
+                requests = []
+            else:
+                requests.append(line)
+        assert [c[0] for c in calls] == list(commands)
+        return calls
+
+    return run
+
+
+def _last(requests, *kinds):
+    return max((i for i, r in enumerate(requests) if r.split()[0] in kinds), default=-1)
+
+
+@pytest.mark.parametrize("types", [1, 4, 5])
+def test_set_system_waits_for_its_copies(record, types):
+    """The caller's arrays and the tables made on the host are free again on return."""
+    (_, st0, _), (_, st1, requests) = record(f"create:n=100,types={types},mol=3", "set")
+    assert st0 == st1 == 0
+    assert _last(requests, "copy", "launch") > 0
+    assert _last(requests, "wait") > _last(requests, "copy", "launch")
