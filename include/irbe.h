@@ -177,8 +177,12 @@ irbe_status irbe_set_system(irbe_handle h, const int32_t* type, const void* char
                             const double* lj_sigma_host, const double* lj_eps_host);
 
 /* Replace charges (device, N) and the LJ tables (host, n_types^2) without
- * touching the topology; NULL leaves that part unchanged. Waits only when LJ
- * tables are given. */
+ * touching the topology; NULL leaves that part unchanged. Both are taken in
+ * stream order: charge is read when the stream reaches the call and must stay
+ * as it is until then; the host tables are read before the call returns. Waits
+ * only for LJ tables of more than four types (up to four travel as kernel
+ * arguments). LJ tables into a stream under capture are IRBE_EUNSUPPORTED;
+ * nothing is queued and the capture stays valid. */
 irbe_status irbe_update_parameters(irbe_handle h, const void* charge, const double* lj_sigma_host,
                                    const double* lj_eps_host);
 

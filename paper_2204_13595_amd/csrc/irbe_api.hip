@@ -453,8 +453,8 @@ void lj_tables(const irbe_ctx* h, std::vector<LJ<real>>& tab, std::vector<real>&
 }
 
 // The tables to the device: as the arguments of a kernel where they fit (up to
-// kLjArgTypes types), in stream order and without a wait; otherwise, and into a
-// stream under capture, by copies and a wait for them.
+// kLjArgTypes types), in stream order and without a wait; otherwise by copies and
+// a wait for them.
 template <typename real>
 hipError_t upload_lj_t(irbe_ctx* h)
 {
@@ -462,12 +462,8 @@ hipError_t upload_lj_t(irbe_ctx* h)
     std::vector<LJ<real>> tab;
     std::vector<real> raw;
     lj_tables(h, tab, raw);
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    hipError_t e = hipStreamIsCapturing(h->stream, &cap);
-    if (e != hipSuccess) return e;
-    if (h->cfg.n_types <= kLjArgTypes && cap == hipStreamCaptureStatusNone)
-        return launch_store_lj<real>(h, tab.data(), raw.data());
-    e = hipMemcpyAsync(h->lj, tab.data(), sizeof(LJ<real>) * nt2, hipMemcpyHostToDevice, h->stream);
+    if (h->cfg.n_types <= kLjArgTypes) return launch_store_lj<real>(h, tab.data(), raw.data());
+    hipError_t e = hipMemcpyAsync(h->lj, tab.data(), sizeof(LJ<real>) * nt2, hipMemcpyHostToDevice, h->stream);
     if (e == hipSuccess)
         e = hipMemcpyAsync(h->lj_raw, raw.data(), sizeof(real) * 2 * nt2, hipMemcpyHostToDevice, h->stream);
     return e == hipSuccess ? hipStreamSynchronize(h->stream) : e;
@@ -781,6 +777,12 @@ irbe_status irbe_update_parameters(irbe_handle h, const void* charge, const doub
     if ((lj_sigma_host == nullptr) != (lj_eps_host == nullptr))
         return fail(h, IRBE_EINVAL, "give both LJ tables or neither");
     if (lj_sigma_host) {
+        // (a graph would store these values again at every replay, and the copies of
+        // larger tables wait, which ends the capture with an error)
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        IRBE_TRY(h, hipStreamIsCapturing(h->stream, &cap), "capture status");
+        if (cap != hipStreamCaptureStatusNone)
+            return fail(h, IRBE_EUNSUPPORTED, "irbe_update_parameters: LJ tables into a stream under capture");
         std::string why;
         if (!set_lj_host(h, lj_sigma_host, lj_eps_host, why)) return fail(h, IRBE_EINVAL, why);
         const irbe_status st = upload_lj(h);

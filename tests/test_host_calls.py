@@ -48,3 +48,12 @@ def test_set_system_waits_for_its_copies(record, types):
     assert st0 == st1 == 0
     assert _last(requests, "copy", "launch") > 0
     assert _last(requests, "wait") > _last(requests, "copy", "launch")
+
+
+@pytest.mark.parametrize("types", [1, 4, 5])
+def test_tables_are_refused_under_capture_before_anything_is_queued(record, types):
+    """A wait or a pageable copy would invalidate the caller's capture."""
+    calls = record(f"create:n=100,types={types}", "set", "capture=1", "lj", "capture=0", "lj")
+    name, status, requests = calls[3]
+    assert (status, requests) == (-6, [])
+    assert calls[5][1] == 0 and _last(calls[5][2], "copy", "launch") >= 0
