@@ -670,8 +670,10 @@ irbe_status irbe_create(const irbe_config* cfg, void* hip_stream, irbe_handle* o
         if (c.capacity_hint > 0.0) cap_s = round_up32(c.capacity_hint);
         if (h->full_list) cap_c = 1;
         if (h->stencil) cap_s = 1;  // no shell list
-        cap_c = (int32_t)std::min<int64_t>(cap_c, c.n_atoms + 32);
-        cap_s = (int32_t)std::min<int64_t>(cap_s, c.n_atoms + 32);
+        // (no more than the atoms; rows start at multiples of four entries, which are loaded and stored together)
+        const int32_t most = round_up32((double)c.n_atoms + 32.0);
+        cap_c = std::min(cap_c, most);
+        cap_s = std::min(cap_s, most);
         e = alloc_lists(h, cap_c, cap_s);
     }
     if (e == hipSuccess)

@@ -57,3 +57,15 @@ def test_tables_are_refused_under_capture_before_anything_is_queued(record, type
     name, status, requests = calls[3]
     assert (status, requests) == (-6, [])
     assert calls[5][1] == 0 and _last(calls[5][2], "copy", "launch") >= 0
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 7, 18, 30, 33, 95])
+@pytest.mark.parametrize("hint", [0, 50, 1000])
+def test_list_rows_are_whole_16_byte_units(record, n, hint):
+    """The pair kernel and the list build take four entries at a time from the start
+    of any row, so the capacities of small systems, which are bounded by the number
+    of atoms, are multiples of four as well."""
+    calls = record(f"create:n={n},box=9,hint={hint},entries=32", "set", "build", "counts")
+    assert [c[1] for c in calls] == [0, 0, 0, 0]
+    core, shell = (int(x) for x in calls[3][2][-1].split()[1:])
+    assert core % 4 == 0 and shell % 4 == 0 and min(core, shell) >= min(n, 32)
