@@ -150,8 +150,10 @@ typedef struct {
                               of dense cells (>= 4 atoms per cell on average)
                               runs, the shell stencil has at most 128 rows, a
                               block at most 8,192 candidates and a stencil row at
-                              most 1,024 (otherwise, and once a build finds more,
-                              32-bit indices); IRBE_ENTRIES_32: 32-bit sorted
+                              most 1,024 (2,048 in stencils of at most 32 rows,
+                              4,096 of at most 16); otherwise, and from the build
+                              on that follows one that finds more, 32-bit
+                              indices. IRBE_ENTRIES_32: 32-bit sorted
                               indices always. Lists, batches and results are the
                               same either way: the masks take a fifth of the
                               device memory of the indices, and of the bytes the

@@ -351,24 +351,21 @@ irbe_status check_device_error(irbe_ctx* h)
     int32_t chk[4] = {0, 0, 0, 0};
     IRBE_TRY(h, hipMemcpyAsync(chk, h->err, sizeof(chk), hipMemcpyDeviceToHost, h->stream), "read the list check");
     IRBE_TRY(h, hipStreamSynchronize(h->stream), "synchronize");
-    const uint32_t err = (uint32_t)chk[0];
+    uint32_t err = (uint32_t)chk[0];
     const int32_t* const mx = chk + 1;
     if (err) {
         IRBE_TRY(h, launch_fill_i32(h->stream, (int32_t*)h->err, 0, 1), "clear error word");
         if (err & ERR_NONFINITE) return fail(h, IRBE_ENONFINITE, "non-finite position");
-        // a stencil row's candidates too many for the masks: 32-bit entries from the
-        // next build on
+        // a crowded stencil row: 32-bit entries from the next build on (the lists of this one are whole)
         if (err & ERR_SHELL_ROW) h->masks_ok = false;
+        err &= ~(uint32_t)ERR_SHELL_ROW;
+    }
+    if (err) {
         // the rows of some build since the last check were too short: the forces
         // computed from those lists miss entries; grow the rows for the next build
         const hipError_t e = grow_lists(h, std::max(mx[0], h->max_core), std::max(mx[1], h->max_shell), mx[2]);
         if (e == hipErrorInvalidValue) return fail(h, IRBE_ECAPACITY, "more than 65535 list entries per atom");
         if (e != hipSuccess) return hip_fail(h, e, "grow lists");
-        if (err & ERR_SHELL_ROW)
-            return fail(h, IRBE_ECAPACITY,
-                        "a shell stencil row's candidates exceeded the shell masks in a build since the last "
-                        "check: forces computed from those lists are wrong; 32-bit entries from now on, build the "
-                        "lists again");
         return fail(h, IRBE_ECAPACITY,
                     "list capacity exceeded by a build since the last check: forces computed from those lists are "
                     "incomplete; the rows have been grown, build the lists again");
@@ -389,7 +386,7 @@ irbe_status poll_list_check(irbe_ctx* h)
     const uint32_t err = (uint32_t)h->chk_host[0];
     h->max_core = h->chk_host[1];
     h->max_shell = h->chk_host[2];
-    // (a row range too long for the masks: 32-bit entries from the next build on)
+    // (a crowded stencil row: 32-bit entries from the next build on)
     if (err & ERR_SHELL_ROW) h->masks_ok = false;
     if (err & (ERR_CORE_CAP | ERR_SHELL_CAP)) {
         const hipError_t e = grow_lists(h, h->max_core, h->max_shell, h->chk_host[3]);
@@ -839,8 +836,7 @@ irbe_status irbe_build_lists(irbe_handle h, const void* pos, uint64_t step)
             if (err & ERR_NONFINITE) return fail(h, IRBE_ENONFINITE, "non-finite position");
             // capacity bits of this build: the rows grow below and the lists are built again
             if (err & ERR_SHELL_ROW) {
-                // a stencil row's candidate range too long for the masks: 32-bit
-                // entries from now on, and the lists built again
+                // a crowded stencil row: 32-bit entries from now on, and the lists built again
                 h->masks_ok = false;
                 continue;
             }

@@ -12,7 +12,8 @@
 
 namespace irbe {
 
-// Error-word bits set by kernels and read back at the next waiting call.
+// Error-word bits set by kernels and read back at the next waiting call
+// (ERR_SHELL_ROW: no error, the next build is to take 32-bit shell entries).
 enum : uint32_t { ERR_NONFINITE = 1u, ERR_CORE_CAP = 2u, ERR_SHELL_CAP = 4u, ERR_SHELL_ROW = 8u };
 
 // Shell lists as masks. The list build takes blocks of up to 32 consecutive
@@ -122,6 +123,7 @@ struct ListBlockArgs {
     uint32_t* mask;
     int32_t *words, *nw, *slot_of;
     int cap_words;
+    int max_row;                     // candidates of a stencil row beyond which ERR_SHELL_ROW is set
 };
 
 // Stencil and segments of the block list build: segments of G cells of a cell
@@ -206,7 +208,7 @@ struct irbe_ctx {
     int32_t* ncore = nullptr;         // [N]
     int32_t* shell = nullptr;         // [N * cap_shell] sorted indices, or (masks) [N * cap_words] mask words
     bool masks = false;               // the shell rows are allocated as masks (ShellMasks)
-    bool masks_ok = true;             // cleared for good once a build found a row range too long for them
+    bool masks_ok = true;             // cleared for good once a build found a crowded stencil row or a block of too many words
     int32_t cap_words = 0;            // words per mask row
     int32_t* blk_words = nullptr;     // [2 * list_block_slots * cap_words] first candidate of the blocks' half words
     int32_t* blk_nw = nullptr;        // [list_block_slots] words of the blocks

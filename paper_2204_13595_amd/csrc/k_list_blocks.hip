@@ -51,7 +51,6 @@ namespace irbe {
 // compute units (2,703 atoms: 128 blocks, 54 us with four).
 constexpr int mask_threads(bool narrow) { return narrow ? 256 : 512; }
 constexpr int kMaskWords = 128;  // words per tile (two per lane when the masks are read back by atom)
-constexpr int kMaskMaxRow = 1024;  // candidates of one stencil row beyond which shell lists are not kept as masks
 constexpr int kMaskRows = 128;  // stencil rows per pass (two index ranges each)
 constexpr float kMaskUnit = 64.0f;  // the list radius in the units of the half-precision coordinates
 constexpr float kMaskNorm = 64.0f;  // the norms are carried divided by this
@@ -264,7 +263,7 @@ __global__ __launch_bounds__(mask_threads(NARROW), NARROW ? 4 : 2) void k_list_b
                 }
             }
         }
-        if (MASK) long_row |= sl + __shfl_xor(sl, 1, 64) > kMaskMaxRow;
+        if (MASK) long_row |= sl + __shfl_xor(sl, 1, 64) > p.max_row;
         // ---- first half word of every range
         const int wn = (sl + 15) >> 4;
         const int inc = wave_scan(wn);
@@ -538,8 +537,9 @@ __global__ __launch_bounds__(mask_threads(NARROW), NARROW ? 4 : 2) void k_list_b
         __syncthreads();
     }
     if (MASK) {
-        // a block with more words than a row holds (its masks are cut off there), or a
-        // stencil row with too many candidates for the masks: reported to the host
+        // reported to the host: a block with more words than a row holds (its masks are
+        // cut off there), and a crowded stencil row (its masks are whole: the handle only
+        // changes to 32-bit entries with the next build)
         if (ballot64(long_row) != 0 && lane == 0) atomicOr(p.err, ERR_SHELL_ROW);
         if (tid == 0) {
             p.nw[slot] = min(wbase, p.cap_words);
@@ -640,6 +640,18 @@ int mask_words_wanted(const irbe_ctx* h)
     return std::min(kMaskMaxWords, ((int)std::ceil(1.6 * words) + 8 + 3) / 4 * 4);
 }
 
+// Candidates of a stencil row up to which a handle keeps its shell lists as masks:
+// 1,024, and for stencils of at most 32 rows 65,536 over their rows (rounded up to
+// a power of two), so that row and place in it fit 16 bits. The masks need no such
+// bound; it is the crowding up to which the compact storage is promised, and beyond
+// which a few blocks' long mask rows would size the rows of all atoms.
+static int mask_row_most(int rows)
+{
+    int bits = 0;
+    while ((1 << bits) < rows) ++bits;
+    return std::max(1024, 65536 >> bits);
+}
+
 hipError_t launch_list_blocks(irbe_ctx* h)
 {
     const Geometry& g = h->geo;
@@ -660,6 +672,7 @@ hipError_t launch_list_blocks(irbe_ctx* h)
     const double unit = kMaskUnit / r_out;
     p.unit = (float)unit;
     p.inv_span = 1.0f / (float)s.span;
+    p.max_row = mask_row_most(s.span * s.span);
     auto tu = [unit](uint64_t t) { return (float)((double)t * unit * unit); };
     p.tu_out = tu(p.t_out);
     p.tu_in = tu(p.t_in);

@@ -9,7 +9,7 @@
 // call made meanwhile):
 //   create:key=value,...   a handle (n, box, rcore, rshell, p, types, hint, skin, fp64, stencil, entries)
 //   set | lj | charge      irbe_set_system; irbe_update_parameters with LJ tables, with charges
-//   build | forces | backward
+//   build | forces | backward | sync
 //   counts                 prints the row capacities of IRBE_DBG_COUNTS
 //   capture=0|1            the stream reports that it is being captured
 //   overflow=core,shell,words,err   what the list checks read back from now on
@@ -192,6 +192,7 @@ int main(int argc, char** argv)
     FN(irbe_compute_forces);
     FN(irbe_compute_forces_backward);
     FN(irbe_get_debug);
+    FN(irbe_sync);
     irbe_handle h = nullptr;
     int64_t n = 0;
     int types = 1;
@@ -255,6 +256,8 @@ int main(int argc, char** argv)
             st = f_irbe_compute_forces(h, pos.data(), 0, out.data(), 0, nullptr);
         } else if (name == "backward") {
             st = f_irbe_compute_forces_backward(h, pos.data(), 0, out.data(), out.data(), nullptr, nullptr);
+        } else if (name == "sync") {
+            st = f_irbe_sync(h);
         } else if (name == "counts") {
             int64_t v[4] = {0, 0, 0, 0}, w = 0;
             st = f_irbe_get_debug(h, IRBE_DBG_COUNTS, v, 4, &w);

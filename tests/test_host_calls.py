@@ -69,3 +69,13 @@ def test_list_rows_are_whole_16_byte_units(record, n, hint):
     assert [c[1] for c in calls] == [0, 0, 0, 0]
     core, shell = (int(x) for x in calls[3][2][-1].split()[1:])
     assert core % 4 == 0 and shell % 4 == 0 and min(core, shell) >= min(n, 32)
+
+
+def test_crowded_row_is_no_error(record):
+    """A stencil row of many candidates (bit 3 of the error word) leaves the masks of that
+    build whole: the handle takes 32-bit entries with the next build, and nothing fails."""
+    calls = record("create:n=4000,box=4", "set", "build", "overflow=0,0,0,8", "build", "sync", "overflow=0,0,0,0",
+                   "build", "sync")
+    assert [c[1] for c in calls] == [0] * len(calls)
+    masks = [any("k_list_blocks" in r and "Lb1EEE" in r for r in calls[i][2]) for i in (2, 4, 7)]
+    assert masks == [True, True, False]
