@@ -7,6 +7,7 @@ no fallback: if the library or a GPU is missing, the calls raise.
 """
 from __future__ import annotations
 
+import contextlib
 import ctypes
 import os
 
@@ -295,16 +296,38 @@ def _tables_on_host(lj_sigma: torch.Tensor, lj_eps: torch.Tensor):
     return s.cpu().numpy(), e.cpu().numpy()
 
 
+@contextlib.contextmanager
+def _handle_stream(h: Handle, *read: torch.Tensor):
+    """Work queued inside comes after the calling stream's, which made the tensors it
+    reads, and before what the calling stream does next; their memory stays theirs until
+    the handle's stream has read them. (The outputs are the calling stream's own.)"""
+    current = torch.cuda.current_stream(h.device)
+    if current == h.stream:
+        yield
+        return
+    h.stream.wait_stream(current)
+    try:
+        yield
+    finally:
+        for t in read:
+            if t.device == h.device:  # (else the call has raised)
+                t.record_stream(h.stream)
+        current.wait_stream(h.stream)
+
+
 class IRBEForce(torch.autograd.Function):
     """F = IRBE force(pos, charge, LJ tables) at the samples of ``step`` and the
     lists of the handle's last build; backward gives dL/dpos, dL/dcharge and
-    dL/dsigma, dL/deps of the LJ tables (n_types^2 each)."""
+    dL/dsigma, dL/deps of the LJ tables (n_types^2 each). The calling stream may be
+    another one than the handle's."""
 
     @staticmethod
     def forward(ctx, pos, charge, lj_sigma, lj_eps, handle: Handle, step: int):
         sigma, eps = _tables_on_host(lj_sigma, lj_eps)
-        handle.update_parameters(charge=charge.detach().contiguous(), lj_sigma=sigma, lj_eps=eps)
-        f = handle.compute_forces(pos.detach().contiguous(), step)
+        q, x = charge.detach().contiguous(), pos.detach().contiguous()
+        with _handle_stream(handle, q, x):
+            handle.update_parameters(charge=q, lj_sigma=sigma, lj_eps=eps)
+            f = handle.compute_forces(x, step)
         ctx.handle = handle
         ctx.step = step
         ctx.lj_host = (sigma, eps)  # the tables' values at the forward, which the backward takes again
@@ -315,13 +338,11 @@ class IRBEForce(torch.autograd.Function):
     def backward(ctx, grad_f):
         pos, charge, lj_sigma, lj_eps = ctx.saved_tensors
         h: Handle = ctx.handle
-        current = torch.cuda.current_stream(h.device)
-        if current != h.stream:
-            current.synchronize()  # the handle's stream reads the gradient that this one may still compute
         sigma, eps = ctx.lj_host
-        h.update_parameters(charge=charge.detach().contiguous(), lj_sigma=sigma, lj_eps=eps)
-        gp, gq, gl = h.compute_forces_backward(pos.detach().contiguous(), ctx.step, grad_f.contiguous(),
-                                               want_charge=True, want_lj=True)
+        q, x, g = charge.detach().contiguous(), pos.detach().contiguous(), grad_f.contiguous()
+        with _handle_stream(h, q, x, g):
+            h.update_parameters(charge=q, lj_sigma=sigma, lj_eps=eps)
+            gp, gq, gl = h.compute_forces_backward(x, ctx.step, g, want_charge=True, want_lj=True)
         nt2 = h.n_types ** 2
         g_sig = gl[:nt2].to(lj_sigma.dtype).reshape(lj_sigma.shape).to(lj_sigma.device)
         g_eps = gl[nt2:].to(lj_eps.dtype).reshape(lj_eps.shape).to(lj_eps.device)
