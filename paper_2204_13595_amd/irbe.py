@@ -288,12 +288,12 @@ class Handle:
 
 
 def _tables_on_host(lj_sigma: torch.Tensor, lj_eps: torch.Tensor):
-    """The values of both LJ tables, in one copy (and wait) where they are alike."""
+    """Copies of the values of both LJ tables, in one transfer (and wait) where they are alike."""
     s, e = lj_sigma.detach().reshape(-1), lj_eps.detach().reshape(-1)
     if s.device == e.device and s.dtype == e.dtype:
         both = torch.cat((s, e)).cpu().numpy()
         return both[:s.numel()], both[s.numel():]
-    return s.cpu().numpy(), e.cpu().numpy()
+    return s.cpu().numpy().copy(), e.cpu().numpy().copy()
 
 
 @contextlib.contextmanager

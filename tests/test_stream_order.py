@@ -101,3 +101,13 @@ def test_no_waits_on_the_handles_stream(monkeypatch):
     f = IRBEForce.apply(*x, FakeHandle(mine, log), 1)
     torch.autograd.grad(f, x, grad_outputs=torch.ones(N, 3))
     assert not [e for e in log if e[0] == "wait"]
+
+
+def test_host_values_are_the_forwards_own():
+    """Tables of two types on the host: the values kept for the backward are no view of them."""
+    from paper_2204_13595_amd.irbe import _tables_on_host
+    s, e = torch.ones(2, 2, dtype=torch.float64), torch.ones(2, 2, dtype=torch.float32)
+    a, b = _tables_on_host(s, e)
+    s.fill_(7.0)
+    e.fill_(7.0)
+    assert a.max() == 1.0 and b.max() == 1.0
