@@ -97,6 +97,12 @@ __device__ __forceinline__ bool in_annulus(uint4 a, uint4 b, uint64_t t_lo, uint
 // integrated from those forces, and the FP64 energies, virials and LJ gradients
 // summed from the FP32 terms, resolve a change of their last bits, and runs are
 // to be reproduced bit for bit.
+// The fused form's products with separations in quanta (up to 2^31) would overflow FP32
+// where the force itself is 10^30 and less (atoms within 0.002 nm of each other), so its
+// charges and LJ coefficients are scaled by 2^-32, which rounds nothing, and the sums
+// by the box length instead of the quantum: the same bits wherever both are finite.
+constexpr double kFusedScale = 2.3283064365386963e-10;  // 2^-32
+constexpr bool fused_form(bool full, bool ev, bool skin) { return !ev && (full || skin); }
 
 // Separation in quanta (minimum image).
 template <typename real>
@@ -177,7 +183,7 @@ __device__ __forceinline__ real pair_phi(real r2, real qq, const LJ<real>& lj, c
 }
 
 // Force, energy and virial sums of one list (core or shell batch). Fused form:
-// forces in quanta.
+// forces over the box length.
 template <typename real>
 struct PairSum {
     real fx = 0, fy = 0, fz = 0;
@@ -743,8 +749,17 @@ __global__ __launch_bounds__(kCoopBlock, ENC && !EV && sizeof(real) == 4 ? 5 : 1
     __shared__ double red[kPairPartials * (kCoopBlock / 64)];
     __shared__ StencilRows<STENCIL ? kDecodeRows : 1> srows[kCoopBlock / 64];  // stencil rows of one cell per wave
     __shared__ __align__(16) unsigned char mtab[ENC ? (kCoopBlock / 64) * sizeof(MaskTable) : 16];  // masks: one atom's row per wave
+    constexpr bool kPass = FULL && !EV;
+    constexpr bool kFused = fused_form(FULL, EV, SKIN);  // (ke and quantum come scaled)
     const int nt2 = n_types * n_types;
-    for (int t = threadIdx.x; t < nt2; t += kCoopBlock) lj[t] = lj_g[t];
+    for (int t = threadIdx.x; t < nt2; t += kCoopBlock) {
+        LJ<real> e = lj_g[t];
+        if (kFused) {
+            e.a12 *= (real)kFusedScale;
+            e.b6 *= (real)kFusedScale;
+        }
+        lj[t] = e;
+    }
     __syncthreads();
     const int lane = threadIdx.x & 63;
     const int64_t blk = xcd_block(blockIdx.x, gridDim.x);
@@ -844,8 +859,6 @@ __global__ __launch_bounds__(kCoopBlock, ENC && !EV && sizeof(real) == 4 ? 5 : 1
     // one in flight while a pass is evaluated. Bound by vector issue (13 passes of a
     // water atom's 728 entries at about 60 slots): 3,145,728 atoms 4.4 ms, 4.92 ms as
     // a loop of dependent loads with the excluded pairs in a pass of their own.
-    constexpr bool kPass = FULL && !EV;
-    constexpr bool kFused = !EV && (FULL || SKIN);
     if constexpr (kPass) {
         auto entry = [&](int64_t a, int t, int pass) -> int {
             const int ns = bcast(h_ns, t), nx = bcast(h_x.y, t);
@@ -1336,7 +1349,11 @@ template <typename real, bool FULL, bool EV, bool STENCIL, bool SKIN, bool ENC =
 static hipError_t launch_coop_t(irbe_ctx* h, uint64_t step)
 {
     const int64_t n = h->cfg.n_atoms;
-    const PairParams<real> pp = pair_params<real>(h);
+    PairParams<real> pp = pair_params<real>(h);
+    if (fused_form(FULL, EV, SKIN)) {
+        pp.ke *= (real)kFusedScale;
+        pp.quantum *= (real)(1.0 / kFusedScale);
+    }
     hipError_t e = launch_draw(h, step);
     if (e != hipSuccess) return e;
     // stencil sampling keeps one cell's stencil rows for consecutive atoms: longer
