@@ -120,7 +120,7 @@ struct RowLoad {
 // (six wavefronts per SIMD, what the stage leaves of LDS: the register bounds of seven and eight spill)
 template <int MODE>
 __global__ __launch_bounds__(kListWave, 6) void k_build_lists_lanes(
-    int n_c, int lo, int hi, int G, int parts, PackedBounds tb, uint64_t t_core, uint64_t t_lo, uint64_t t_shell, float r2_cells, bool excl,
+    int n_c, int lo, int hi, int G, int parts, int seg, PackedBounds tb, uint64_t t_core, uint64_t t_lo, uint64_t t_shell, float r2_cells, bool excl,
     const uint4* __restrict__ spos, const u32x4* __restrict__ spk, const int32_t* __restrict__ cell_start,
     int cap_core, int cap_shell, int32_t* __restrict__ core, int32_t* __restrict__ ncore,
     int32_t* __restrict__ shell, int32_t* __restrict__ nshell, int32_t* __restrict__ maxcnt,
@@ -146,9 +146,11 @@ __global__ __launch_bounds__(kListWave, 6) void k_build_lists_lanes(
     const int r0 = cell_start[home], r1 = cell_start[home + n_c];
     int32_t* const mine_st = stage + lane * kStage;
     const int nrows = span * span;  // at most 2 * kListWave (checked at the launch)
-    // the row's atoms in equal runs of at most 64; this wavefront takes run part, part + parts, ...
+    // the row's atoms in equal runs of at most 64 (seg = 0), this wavefront taking run part,
+    // part + parts, ..., or those of seg consecutive cells per wavefront
     const int runs = (r1 - r0 + kListWave - 1) / kListWave;
     const int run = runs > 0 ? (r1 - r0 + runs - 1) / runs : 0;
+    auto part_start = [&](int q) { return seg > 0 ? cell_start[home + min(q * seg, n_c)] : min(r0 + q * run, r1); };
     // (the last parts are often empty: they rotate with the row, because consecutive workgroups
     // go to the shader engines in turn, and four parts in a fixed order left one of them idle)
     int part = (g - rowid * parts + rowid) % parts;
@@ -156,10 +158,10 @@ __global__ __launch_bounds__(kListWave, 6) void k_build_lists_lanes(
         return (int)(((uint64_t)x * (uint32_t)n_c) >> 32);
     };
     int maxc = 0, maxs = 0;
-    for (int s = r0 + part * run, e = min(s + run, r1); s < e;) {
-        // the atoms from s on whose cells' union fits (all of the run but in sparse rows)
+    for (int s = part_start(part), e = part_start(part + 1); s < e;) {
+        // the atoms from s on, one per lane, whose cells' union fits (all of the run but in sparse rows)
         const int x0 = cell_of(spos[s].x);
-        const int a1 = min(e, cell_start[home + min(x0 + G, n_c)]);
+        const int a1 = min(min(e, s + kListWave), cell_start[home + min(x0 + G, n_c)]);
         const int span_u = cell_of(spos[a1 - 1].x) - x0 + span;  // cells of the union x range
         const int xu0 = wrap(x0 + lo, n_c);                      // first cell of the union
         const int lenA = min(span_u, n_c - xu0);                 // cells before the wrap
@@ -434,8 +436,8 @@ __global__ __launch_bounds__(kListWave, 6) void k_build_lists_lanes(
         s = a1;
         if (s == e) {
             part += parts;
-            s = r0 + part * run;
-            e = min(s + run, r1);
+            s = part_start(part);
+            e = part_start(part + 1);
         }
         __syncthreads();
     }
@@ -589,7 +591,20 @@ static hipError_t launch_list_lanes(irbe_ctx* h)
     // wavefronts per cell row: its runs of 64 atoms, with two standard deviations of a
     // random system's rows (fuller rows: their wavefronts take further runs)
     const double per_row = (double)h->cfg.n_atoms / ((double)n_c * n_c);
-    const int parts = (int)std::ceil((per_row + 2.0 * std::sqrt(per_row)) / kListWave);
+    int parts = (int)std::ceil((per_row + 2.0 * std::sqrt(per_row)) / kListWave);
+    // where those runs are longer than G cells (small or very dilute boxes), a wavefront takes
+    // its run in pieces, one after another; a chip that the rows leave idle (up to 2,048 of
+    // them, two wavefronts per SIMD) does better with a wavefront per segment of at most
+    // G cells (and 48 atoms, as segments differ in them). Build of all lists, runs against
+    // segments: 1.3 ions per cell, 600 ions (49 rows) 451 and 93 us, 10^5 (1,849 rows) 306
+    // and 215, 1.6 10^5 (2,500 rows) 322 and 324; 0.2 per cell, 12,000 (1,521 rows) 138 and
+    // 135, 30,000 (2,809 rows) 165 and 202
+    int seg = 0;
+    if (n_c * n_c <= 2 * 1024 && n_c > 0.8 * G * std::ceil(per_row / kListWave)) {
+        parts = std::max((n_c + G - 1) / G, (int)std::ceil(per_row / 48.0));
+        seg = (n_c + parts - 1) / parts;
+        parts = (n_c + seg - 1) / seg;
+    }
     const int64_t groups = (int64_t)n_c * n_c * parts;
     // the packed records as for one cell per group: only a lane's own candidates
     // (within the stencil of its cell) are tested, so 16-bit differences of the
@@ -601,7 +616,7 @@ static hipError_t launch_list_lanes(irbe_ctx* h)
     k_pack_sorted<<<(unsigned)blocks_for(h->cfg.n_atoms, kBlock), kBlock, 0, h->stream>>>(
         h->cfg.n_atoms, pl.sh, h->spos, h->smol, (u32x4*)h->spk);
 #define IRBE_LANES_ARGS                                                                                            \
-    n_c, g.lo, g.hi, G, parts, pl.tb, g.tl_core, g.tl_lo, g.tl_shell, r2_cells, h->n_excl > 0, h->spos, (const u32x4*)h->spk, h->cell_start, \
+    n_c, g.lo, g.hi, G, parts, seg, pl.tb, g.tl_core, g.tl_lo, g.tl_shell, r2_cells, h->n_excl > 0, h->spos, (const u32x4*)h->spk, h->cell_start, \
         h->cap_core, h->cap_shell, h->core, h->ncore, h->shell, h->nshell, h->maxcnt, h->err
     if (h->full_list)
         k_build_lists_lanes<kListsFull><<<(unsigned)groups, kListWave, 0, h->stream>>>(IRBE_LANES_ARGS);

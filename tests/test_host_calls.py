@@ -79,3 +79,12 @@ def test_crowded_row_is_no_error(record):
     assert [c[1] for c in calls] == [0] * len(calls)
     masks = [any("k_list_blocks" in r and "Lb1EEE" in r for r in calls[i][2]) for i in (2, 4, 7)]
     assert masks == [True, True, False]
+
+
+@pytest.mark.parametrize("n,box,rows,segments", [(600, 39.1, 49, 7), (1000, 46.4, 81, 3), (12000, 106.2, 441, 2)])
+def test_dilute_rows_are_cut_where_a_window_ends(record, n, box, rows, segments):
+    """The list build of few ions takes one wavefront per segment of a cell row that a
+    window of the box allows, not one per row that takes them in turn."""
+    calls = record(f"create:n={n},box={box},rcore=5,rshell=15", "set", "build")
+    launch = [r.split() for r in calls[2][2] if "k_build_lists_lanes" in r]
+    assert len(launch) == 1 and int(launch[0][2]) == rows * segments
