@@ -728,7 +728,9 @@ irbe_status irbe_set_system(irbe_handle h, const int32_t* type, const void* char
         a = b;
     }
     int64_t total = 0;
+    int32_t most = 0;
     for (size_t i = 0; i < n; ++i) {
+        most = std::max(most, off[i + 1]);
         total += off[i + 1];
         if (total > INT32_MAX) return fail(h, IRBE_EUNSUPPORTED, "too many excluded pairs");
         off[i + 1] = (int32_t)total;
@@ -752,6 +754,7 @@ irbe_status irbe_set_system(irbe_handle h, const int32_t* type, const void* char
     IRBE_TRY(h, dalloc(h, &h->xidx, idx.size()), "alloc exclusions");
     IRBE_TRY(h, dalloc(h, &h->sxidx, idx.size()), "alloc exclusions");
     h->n_excl = total;
+    h->max_excl = most;
     IRBE_TRY(h, hipMemcpyAsync(h->xoff, off.data(), (n + 1) * 4, hipMemcpyHostToDevice, h->stream), "upload");
     IRBE_TRY(h, hipMemcpyAsync(h->xidx, idx.data(), idx.size() * 4, hipMemcpyHostToDevice, h->stream), "upload");
     IRBE_TRY(h, hipMemcpyAsync(h->type_orig, type, n * 4, hipMemcpyDeviceToDevice, h->stream), "copy types");

@@ -116,7 +116,8 @@ struct ListBlockArgs {
     const int2* sxr;
     const int32_t* xidx;             // excluded partners (caller ids) and the caller ids' sorted indices
     const int32_t* rank;
-    int32_t* sxidx;                  // the partners' sorted indices, written by the build
+    const int32_t* smol;             // molecule ids
+    int32_t* sxidx;                  // the partners' sorted indices, written by the build (not with ids)
     int32_t *core, *ncore, *shell, *nshell, *maxcnt;
     uint32_t* err;
     // shell lists as masks (ShellMasks)
@@ -184,6 +185,7 @@ struct irbe_ctx {
     int32_t* sxidx = nullptr;         // [n_excl] xidx entries as sorted indices (rebuilt with the cells)
     int2* sxr = nullptr;              // [N] sorted atom's range (first, count) in sxidx
     int64_t n_excl = 0;
+    int32_t max_excl = 0;             // most excluded partners of an atom
     double* sumq2 = nullptr;          // [1]
     double* q2part = nullptr;
 
@@ -298,6 +300,13 @@ constexpr double kLaneMaxPerCell = 4.0;
 bool lists_by_lanes(const irbe_ctx* h);
 // The block form of the list build (k_list_blocks) and the block slots it takes.
 hipError_t launch_list_blocks(irbe_ctx* h);
+// Most excluded partners of an atom up to which the build clears them from its masks one
+// by one (and writes their sorted indices on the way); beyond, by molecule ids (and the
+// indices in a launch of their own). One by one against ids, build of 96,000 atoms in
+// molecules of 3: 138 and 189 us, of 100: 196 and 215, of 200: 269 and 254, of 400: 470
+// and 382, of 4,000: 3,932 and 1,678.
+constexpr int kPartnersMost = 200;
+bool exclusions_by_id(const irbe_ctx* h);
 ListBlockShape list_block_shape(const Geometry& geo, bool core_only);
 int64_t list_block_slots(const Geometry& geo, bool core_only, int64_t n);
 hipError_t launch_rho(irbe_ctx* h, const void* grad, bool with_adjoint);

@@ -354,8 +354,8 @@ hipError_t launch_bin(irbe_ctx* h, const void* pos)
                                                           (const float*)h->q_orig, h->mol_orig, h->xoff, h->spos,
                                                           (float*)h->sq_r, h->spq, h->smol, h->sxr, h->rank,
                                                           h->geo.n_c, h->brow, s.G, gpr, h->blk_start);
-    // (the block form of the list build writes the excluded partners' sorted indices itself)
-    if (!blocks && h->n_excl > 0)
+    // (the block form of the list build writes the excluded partners' sorted indices itself where they are few)
+    if ((!blocks || exclusions_by_id(h)) && h->n_excl > 0)
         k_excl_sorted<<<(unsigned)blocks_for(h->n_excl, kBlock), kBlock, 0, h->stream>>>(h->n_excl, h->xidx, h->rank,
                                                                                         h->sxidx);
     return hipGetLastError();

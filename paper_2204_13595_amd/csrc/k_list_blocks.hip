@@ -28,8 +28,9 @@
 // A wave converts 64 candidates at a time; its chunks whose candidates can come
 // within r_core of the block get a second pair of MFMAs for C(i) (same operands,
 // another constant), a third with a skin. Same-molecule pairs and the atom
-// itself are then cleared from the masks by position, and the masks are written
-// out as lists, chunk by chunk: a member's place is a bit count.
+// itself are then cleared from the masks by position (molecules of hundreds of
+// atoms: by comparing ids, chunk by chunk), and the masks are written out as
+// lists, chunk by chunk: a member's place is a bit count.
 //
 // What bounds it: vector issue (397 instructions per atom at 3.1 M atoms of
 // water, of which the 60 chunks of a block take about 100 each). Split lists of
@@ -126,7 +127,9 @@ struct MaskSeg {
     int base, len, half;
 };
 
-template <int MODE, bool NARROW, bool MASK>
+// IDS: same-molecule pairs leave the masks by the molecule ids of the candidates (and of
+// the atom itself, by its index) instead of by position, chunk by chunk.
+template <int MODE, bool NARROW, bool MASK, bool IDS>
 __global__ __launch_bounds__(mask_threads(NARROW), NARROW ? 4 : 2) void k_list_blocks(ListBlockArgs p)
 {
     constexpr int kMaskBlock = mask_threads(NARROW);
@@ -142,6 +145,7 @@ __global__ __launch_bounds__(mask_threads(NARROW), NARROW ? 4 : 2) void k_list_b
     __shared__ int cflag[kMaskWords / 2];                // chunks that hold core candidates
     __shared__ int fw[kMaskWords];                       // their words
     __shared__ uint16_t xpre[kMaskWaves][64];            // members before each of one atom's flagged words
+    __shared__ __align__(16) int32_t cid[IDS ? kMaskWaves : 1][IDS ? 64 : 1];  // ids of a chunk's candidates, in bit order
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int slot = (int)xcd_block(blockIdx.x, gridDim.x);
@@ -162,7 +166,7 @@ __global__ __launch_bounds__(mask_threads(NARROW), NARROW ? 4 : 2) void k_list_b
     const uint32_t xext = (uint32_t)__builtin_amdgcn_readlane((int)si.x, 31) - xlo;  // x extent of the block
     // the excluded partner this thread clears in the first round (its loads go out early)
     const int xa = tid & 31, xe = tid >> 5;
-    const int2 xr = p.sxr[k0 + min(xa, na - 1)];
+    const int2 xr = IDS ? make_int2(0, 0) : p.sxr[k0 + min(xa, na - 1)];
     auto partner = [&](int e) {
         // entry e of the atom itself and its excluded partners, whose sorted indices are
         // written for the pair kernels on the way
@@ -172,8 +176,20 @@ __global__ __launch_bounds__(mask_threads(NARROW), NARROW ? 4 : 2) void k_list_b
         p.sxidx[xr.x + e - 1] = j;
         return j;
     };
-    const int xj = partner(xe);
+    const int xj = IDS ? -1 : partner(xe);
     uint4 xs = p.spos[max(xj, 0)];
+    // an atom's id (without a molecule, its own), and the ids of the block's atoms by their low 6 bits
+    auto id_of = [&](int k) {
+        const int m = p.smol[k];
+        return m >= 0 ? m : -2 - k;
+    };
+    const int my_id = IDS ? id_of(k0 + al) : 0;
+    uint64_t ids = 0;
+    if constexpr (IDS) {
+        ids = 1ull << (my_id & 63);
+#pragma unroll
+        for (int off = 16; off > 0; off >>= 1) ids |= __shfl_xor((unsigned long long)ids, off, 64);
+    }
     // centre and half extents of the block's bounding box
     const uint32_t bx = xlo + xext / 2;
     const uint32_t yb = bound[cy], zb = bound[cz];
@@ -295,9 +311,11 @@ __global__ __launch_bounds__(mask_threads(NARROW), NARROW ? 4 : 2) void k_list_b
             const int ci = lane & 31;
             const int cw = NARROW ? 2 * ((ci >> 2) & 1) + (lane >> 5) : lane >> 4;  // half word of the chunk's four
             const int cb = NARROW ? ((ci >> 3) << 2) + (ci & 3) : lane & 15;
+            int id_n = 0;  // (its id)
             auto load_c = [&](int c, bool& ok) {
                 const int2 w = wt[4 * min(c, nch - 1) + cw];
                 ok = cb < w.y;
+                if constexpr (IDS) id_n = id_of(ok ? w.x + cb : k0);
                 return p.spos[ok ? w.x + cb : k0];
             };
             bool ok_n = false;
@@ -307,6 +325,7 @@ __global__ __launch_bounds__(mask_threads(NARROW), NARROW ? 4 : 2) void k_list_b
             for (int c = wave; c < nch; c += kMaskWaves) {
                 const uint4 sc = sn;
                 const bool ok = ok_n;
+                const int id = id_n;
                 sn = load_c(c + kMaskWaves, ok_n);  // the next chunk's candidates are in flight
                 const float x = rel(sc.x, bx), y = rel(sc.y, by), z = rel(sc.z, bz);
                 u32x4 f0, f1;
@@ -380,7 +399,23 @@ __global__ __launch_bounds__(mask_threads(NARROW), NARROW ? 4 : 2) void k_list_b
                     }
                     return word;
                 };
-                uint32_t wo = ball(p.t_out, p.tu_out);
+                // candidates with an id of the block (few chunks where molecules are small): the
+                // lane's word of those with its atom's id
+                uint32_t same = 0;
+                if constexpr (IDS) {
+                    if (ballot64(ok && ((ids >> (id & 63)) & 1ull)) != 0) {
+                        cid[wave][16 * cw + cb] = ok ? id : -1;
+                        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                        for (int b = 28; b >= 0; b -= 4) {
+                            const int4 q = *(const int4*)&cid[wave][(lane & 32) + b];
+                            same = (same << 4) | (q.w == my_id ? 8u : 0u) | (q.z == my_id ? 4u : 0u) |
+                                   (q.y == my_id ? 2u : 0u) | (q.x == my_id ? 1u : 0u);
+                        }
+                        __builtin_amdgcn_wave_barrier();
+                    }
+                }
+                uint32_t wo = ball(p.t_out, p.tu_out) & ~same;
                 if constexpr (kTwo) {
                     // candidates of this chunk near enough for C(i) (r_in: its radius, with a margin)
                     uint64_t near = ballot64(ok);
@@ -390,7 +425,7 @@ __global__ __launch_bounds__(mask_threads(NARROW), NARROW ? 4 : 2) void k_list_b
                     const bool any = near != 0;
                     if (lane == 0) cflag[c] = any ? 1 : 0;
                     if (any) {
-                        const uint32_t wi = ball(p.t_in, p.tu_in);
+                        const uint32_t wi = ball(p.t_in, p.tu_in) & ~same;
                         wo &= MODE == kListsSplitSkin ? ~ball(p.t_lo, p.tu_lo) : ~wi;
                         mc[myw][lane & 31] = wi;
                     }
@@ -401,7 +436,7 @@ __global__ __launch_bounds__(mask_threads(NARROW), NARROW ? 4 : 2) void k_list_b
             if (MASK) atomicAdd(&cnt_s[lane & 31], members);
             __syncthreads();
             // ---- the atom itself and its excluded partners leave the masks
-            for (int e = xe; e <= 4096; e += kMaskBlock / 32) {
+            for (int e = xe; !IDS && e <= 4096; e += kMaskBlock / 32) {
                 // (threads of one round: 8 partners of every atom; usually one round)
                 if (ballot64(e <= xr.y) == 0) break;
                 int j = xj;
@@ -611,6 +646,8 @@ int64_t list_block_slots(const Geometry& geo, bool core_only, int64_t n)
     return n / 32 + (int64_t)geo.n_c * geo.n_c * s.gpr + 1;
 }
 
+bool exclusions_by_id(const irbe_ctx* h) { return h->max_excl > kPartnersMost; }
+
 int mask_words_wanted(const irbe_ctx* h)
 {
     const Geometry& g = h->geo;
@@ -689,6 +726,7 @@ hipError_t launch_list_blocks(irbe_ctx* h)
     p.sxidx = h->sxidx;
     p.xidx = h->xidx;
     p.rank = h->rank;
+    p.smol = h->smol;
     p.core = h->core;
     p.ncore = h->ncore;
     p.shell = h->shell;
@@ -700,14 +738,20 @@ hipError_t launch_list_blocks(irbe_ctx* h)
     p.nw = h->blk_nw;
     p.slot_of = h->slot_of;
     p.cap_words = h->cap_words;
+    using std::false_type;
+    using std::true_type;
     auto run = [&](auto mode, auto mask) {
         constexpr int M = decltype(mode)::value;
         constexpr bool K = decltype(mask)::value;
-        if (s.narrow) k_list_blocks<M, true, K><<<(unsigned)slots, mask_threads(true), 0, h->stream>>>(p);
-        else k_list_blocks<M, false, K><<<(unsigned)slots, mask_threads(false), 0, h->stream>>>(p);
+        auto go = [&](auto narrow, auto ids) {
+            constexpr bool N = decltype(narrow)::value;
+            k_list_blocks<M, N, K, decltype(ids)::value><<<(unsigned)slots, mask_threads(N), 0, h->stream>>>(p);
+        };
+        if (s.narrow && exclusions_by_id(h)) go(true_type{}, true_type{});
+        else if (s.narrow) go(true_type{}, false_type{});
+        else if (exclusions_by_id(h)) go(false_type{}, true_type{});
+        else go(false_type{}, false_type{});
     };
-    using std::false_type;
-    using std::true_type;
     if (h->full_list) run(std::integral_constant<int, kListsFull>{}, false_type{});
     else if (h->stencil) run(std::integral_constant<int, kListsCoreOnly>{}, false_type{});
     else if (g.skin && h->masks) run(std::integral_constant<int, kListsSplitSkin>{}, true_type{});

@@ -77,7 +77,7 @@ def test_crowded_row_is_no_error(record):
     calls = record("create:n=4000,box=4", "set", "build", "overflow=0,0,0,8", "build", "sync", "overflow=0,0,0,0",
                    "build", "sync")
     assert [c[1] for c in calls] == [0] * len(calls)
-    masks = [any("k_list_blocks" in r and "Lb1EEE" in r for r in calls[i][2]) for i in (2, 4, 7)]
+    masks = [any("k_list_blocks" in r and "ELb1ELb0EEE" in r for r in calls[i][2]) for i in (2, 4, 7)]
     assert masks == [True, True, False]
 
 
@@ -88,3 +88,14 @@ def test_dilute_rows_are_cut_where_a_window_ends(record, n, box, rows, segments)
     calls = record(f"create:n={n},box={box},rcore=5,rshell=15", "set", "build")
     launch = [r.split() for r in calls[2][2] if "k_build_lists_lanes" in r]
     assert len(launch) == 1 and int(launch[0][2]) == rows * segments
+
+
+@pytest.mark.parametrize("per_mol,by_id", [(3, False), (201, False), (202, True), (1000, True)])
+def test_large_molecules_are_excluded_by_id(record, per_mol, by_id):
+    """Up to 200 excluded partners are cleared from the masks one by one; for more the list
+    build compares ids, and the partners' sorted indices take a launch of their own."""
+    calls = record(f"create:n=4000,box=3.42,mol={per_mol}", "set", "build")
+    names = [r.split()[1] for r in calls[2][2] if r.startswith("launch")]
+    assert any("k_excl_sorted" in n for n in names) == by_id
+    assert any("k_list_blocksILi0ELb0ELb1ELb%dEEE" % by_id in n or "k_list_blocksILi0ELb1ELb1ELb%dEEE" % by_id in n
+               for n in names)
