@@ -148,16 +148,22 @@ typedef struct {
                               IRBE_ENTRIES_AUTO: compact, one bit per candidate of
                               the atom's block of up to 32 atoms, where the build
                               of dense cells (>= 4 atoms per cell on average)
-                              runs, the shell stencil has at most 128 rows, a
-                              block at most 8,192 candidates and a stencil row at
-                              most 1,024 (2,048 in stencils of at most 32 rows,
-                              4,096 of at most 16); otherwise, and from the build
-                              on that follows one that finds more, 32-bit
-                              indices. IRBE_ENTRIES_32: 32-bit sorted
-                              indices always. Lists, batches and results are the
-                              same either way: the masks take a fifth of the
-                              device memory of the indices, and of the bytes the
-                              list build writes and the pair kernel reads.       */
+                              runs, the shell stencil has at most 128 rows and a
+                              stencil row at most 1,024 candidates (2,048 in
+                              stencils of at most 32 rows, 4,096 of at most 16).
+                              Blocks of more than 8,192 and up to 65,536
+                              candidates (r_shell from about 1.6 nm in water)
+                              take it where it is the faster storage of the
+                              forces (mixed precision, index lists of more than
+                              256 MiB, of which the draws would read much), and
+                              where indices would take more than 32 GiB.
+                              Otherwise, and from the build on that follows one
+                              that finds more, 32-bit indices. IRBE_ENTRIES_32:
+                              32-bit sorted indices always. Lists, batches and
+                              results are the same either way: the masks take a
+                              fifth of the device memory of the indices, and of
+                              the bytes the list build writes and the pair
+                              kernel reads.                                      */
 } irbe_config;
 
 /* Create a handle for one system size and parameter set; work is queued on

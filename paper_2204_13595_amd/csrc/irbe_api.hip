@@ -307,12 +307,13 @@ hipError_t ensure_shell_rows_32(irbe_ctx* h)
 }
 
 // Longer mask rows for blocks of max_words words: true when the rows must be
-// allocated again (beyond kMaskMaxWords the masks are given up).
+// allocated again (beyond kMaskTableWords the masks are given up unless long ones are preferred).
 bool grow_mask_rows(irbe_ctx* h, int32_t max_words)
 {
     if (!h->masks || max_words <= h->cap_words) return false;
-    if (max_words > kMaskMaxWords) h->masks_ok = false;
-    else h->cap_words = std::min(kMaskMaxWords, (max_words + max_words / 8 + 3) / 4 * 4);
+    if (max_words > kMaskMaxWords || (max_words > kMaskTableWords && !irbe::long_masks(h, max_words / 1.2))) h->masks_ok = false;
+    else h->cap_words = std::min(max_words <= kMaskTableWords ? kMaskTableWords : kMaskMaxWords,
+                                 (max_words + max_words / 8 + 3) / 4 * 4);
     return true;
 }
 

@@ -30,7 +30,8 @@ struct ShellMasks {
     const int32_t* slot_of;
     int cap;  // words per row, a multiple of 4, at most kMaskMaxWords
 };
-constexpr int kMaskMaxWords = 256;
+constexpr int kMaskMaxWords = 2048;
+constexpr int kMaskTableWords = 256;  // words per row up to which a wavefront keeps an atom's masks and bases in LDS
 
 constexpr int kBlock = 256;          // threads per block of the per-atom kernels
 constexpr int kReduceBlock = 256;    // threads of the deterministic final reductions
@@ -329,6 +330,8 @@ hipError_t ensure_batch_atoms(irbe_ctx* h);
 // Words per mask row that this handle's shell lists take (an estimate with a
 // margin), 0 when they are stored as 32-bit indices.
 int mask_words_wanted(const irbe_ctx* h);
+// Whether mask rows of `words` words, more than kMaskTableWords, are preferred to 32-bit indices.
+bool long_masks(const irbe_ctx* h, double words);
 // Device-memory Floyd bitmaps of at least `words` 32-bit words.
 hipError_t ensure_draw_bits(irbe_ctx* h, size_t words);
 hipError_t launch_stencil_decode(irbe_ctx* h);

@@ -648,6 +648,35 @@ int64_t list_block_slots(const Geometry& geo, bool core_only, int64_t n)
 
 bool exclusions_by_id(const irbe_ctx* h) { return h->max_excl > kPartnersMost; }
 
+// Rows of more than kMaskTableWords words: the pair kernel takes a table of them per atom,
+// and a word and its bases per draw from memory, where indices take one cache line per
+// draw. Indices are better while their lists stay in the last-level cache (256 MiB), with
+// few draws, with long core lists (the table's LDS and registers cost wavefronts) and in
+// FP64 (fewer wavefronts still). The line lies where the distinct lines of 32 indices that
+// the draws read pass 0.11 per word and 0.05 per core entry. Forces, indices against
+// masks, 400,000 atoms of 100 per nm^3 (r_core, r_shell; draws): 0.6, 1.8; 30: 447 and
+// 471 us, 50: 588 and 493, 100: 861 and 649; 0.7, 2.0; 30: 524 and 587, 100: 1,003 and
+// 789; 1.0, 1.6; 100: 978 and 1,057; 1.0, 2.0; 100: 1,180 and 1,112; 0.9, 1.6; 100, at
+// 45,000 atoms (255 MB): 137 and 145, at 65,000: 199 and 162; FP64, 98,304 atoms, 0.7,
+// 2.0; 100: 375 and 424. The build writes masks two to three times faster, but lists are
+// also kept. Indices of more than 32 GiB (a third of a card with the rest) are masks in any case.
+bool long_masks(const irbe_ctx* h, double words)
+{
+    if (1.2 * words > kMaskMaxWords) return false;
+    const Geometry& g = h->geo;
+    const double n = (double)h->cfg.n_atoms;
+    auto members = [&](uint64_t t) {  // expected atoms within sqrt(t) quanta
+        const double r = std::sqrt((double)t) / 4294967296.0;
+        return 4.0 / 3.0 * 3.14159265358979323846 * r * r * r * n;
+    };
+    const double core = members(g.tl_core), list = members(g.tl_shell) - members(g.tl_lo);
+    if (1.3 * 4.0 * list * n > 32.0 * 1073741824.0) return true;
+    if (h->fp64 || 4.0 * list * n <= 256.0 * 1048576.0) return false;
+    const double lines = std::max(1.0, list / 32.0);
+    const double read = lines * (1.0 - std::pow(1.0 - 1.0 / lines, (double)h->cfg.p_shell));
+    return read > 0.11 * words + 0.05 * core;
+}
+
 int mask_words_wanted(const irbe_ctx* h)
 {
     const Geometry& g = h->geo;
@@ -672,9 +701,11 @@ int mask_words_wanted(const irbe_ctx* h)
             words += w * per_row / 32.0 + 0.5;
         }
     // a margin of 1.6 for the blocks of thin cell rows (a build that needs more grows
-    // the rows); masks are given up where even a fifth more than the mean would not fit
-    if (1.2 * words > kMaskMaxWords) return 0;
-    return std::min(kMaskMaxWords, ((int)std::ceil(1.6 * words) + 8 + 3) / 4 * 4);
+    // the rows); rows are long where a fifth more than the mean would not fit short ones
+    const bool is_long = 1.2 * words > kMaskTableWords;
+    if (is_long && !long_masks(h, words)) return 0;
+    const int most = is_long ? kMaskMaxWords : kMaskTableWords;
+    return std::min(most, ((int)std::ceil(1.6 * words) + 8 + 3) / 4 * 4);
 }
 
 // Candidates of a stencil row up to which a handle keeps its shell lists as masks:

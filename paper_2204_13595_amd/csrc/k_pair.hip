@@ -519,54 +519,109 @@ __device__ __forceinline__ int stencil_rows_atom(const StencilRows<ROWS>& T, int
     return o < la ? T.a[lo_k] + o : T.b[lo_k] + (o - la);
 }
 
-// Shell lists as masks: a wavefront keeps one atom's mask row in LDS, with the
-// members before every word and the words' first candidates (those of the
-// atom's block), and finds a member by its rank: the word by binary search over
-// the members before it, the bit by halving the word.
-struct MaskTable {
-    uint32_t pre[kMaskMaxWords];   // members before word w
-    uint32_t word[kMaskMaxWords];
-    int32_t base[2 * kMaskMaxWords];  // sorted index of the first candidate of half q of word w at 2 w + q
+// Shell lists as masks: a wavefront finds a member of an atom's row by its rank, the
+// word by binary search over the members before each, the bit by halving the word.
+// Rows of up to kMaskTableWords words (SHORT) lie in LDS whole, with the words' first
+// candidates (those of the atom's block). Longer ones (LONG) keep only the members before
+// each word there, in 16 bits; a search's word and bases then come from memory, in one
+// round trip of two loads.
+enum { kIndices = 0, kMasksShort = 1, kMasksLong = 2 };
+
+template <int ENC>
+struct MaskTable {};
+
+template <>
+struct MaskTable<kMasksShort> {
+    uint32_t pre[kMaskTableWords];   // members before word w
+    uint32_t word[kMaskTableWords];
+    int32_t base[2 * kMaskTableWords];  // sorted index of the first candidate of half q of word w at 2 w + q
 };
 
-// This lane's four words of atom a's row (nw words).
-__device__ __forceinline__ uint4 mask_load(const ShellMasks& sm, int64_t a, int nw, int lane)
+template <>
+struct MaskTable<kMasksLong> {
+    uint16_t pre[kMaskMaxWords];  // members before word w
+};
+
+// The words of an atom's row that a lane loads ahead of the table: four of every 256.
+template <int ENC>
+struct MaskWords {
+    uint4 v[ENC == kMasksLong ? 2 : 1];
+};
+
+// This lane's four words of words q .. q + 255 of atom a's row (nw words).
+__device__ __forceinline__ uint4 mask_load(const ShellMasks& sm, int64_t a, int nw, int q, int lane)
 {
-    return 4 * lane < nw ? *(const uint4*)(sm.mask + a * (int64_t)sm.cap + 4 * lane) : make_uint4(0u, 0u, 0u, 0u);
+    return q + 4 * lane < nw ? *(const uint4*)(sm.mask + a * (int64_t)sm.cap + q + 4 * lane) : make_uint4(0u, 0u, 0u, 0u);
+}
+
+template <int ENC>
+__device__ __forceinline__ MaskWords<ENC> mask_ahead(const ShellMasks& sm, int64_t a, int nw, int lane)
+{
+    MaskWords<ENC> m;
+    m.v[0] = mask_load(sm, a, nw, 0, lane);
+    if constexpr (ENC == kMasksLong) m.v[1] = mask_load(sm, a, nw, 256, lane);
+    return m;
 }
 
 // The first candidates of the words of block `slot`.
-__device__ __forceinline__ void mask_bases(MaskTable& T, const ShellMasks& sm, int slot, int nw, int lane)
+__device__ __forceinline__ void mask_bases(MaskTable<kMasksShort>& T, const ShellMasks& sm, int slot, int nw, int lane)
 {
     const int32_t* const b = sm.words + 2 * (int64_t)slot * sm.cap;
 #pragma unroll
-    for (int q = 0; q < 2 * kMaskMaxWords; q += 256)
+    for (int q = 0; q < 2 * kMaskTableWords; q += 256)
         if (q + 4 * lane < 2 * nw) *(int4*)&T.base[q + 4 * lane] = *(const int4*)(b + q + 4 * lane);
     __builtin_amdgcn_wave_barrier();
 }
 
-// The lanes' words and the members before each into the table (the wavefront's
-// own: its later reads follow these writes in order).
-__device__ __forceinline__ void mask_rows(MaskTable& T, uint4 m, int lane)
+// The members before each of this lane's four words (among the 256 of the lanes); c[3]: in all four.
+__device__ __forceinline__ uint32_t mask_scan(uint4 m, uint32_t (&c)[4])
 {
-    const uint32_t c0 = __popc(m.x), c1 = c0 + __popc(m.y), c2 = c1 + __popc(m.z), c3 = c2 + __popc(m.w);
-    int x = (int)c3;
+    c[0] = __popc(m.x);
+    c[1] = c[0] + __popc(m.y);
+    c[2] = c[1] + __popc(m.z);
+    c[3] = c[2] + __popc(m.w);
+    int x = (int)c[3];
     x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);
     x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
     x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
     x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
     x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);
     x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);
-    const uint32_t p = (uint32_t)x - c3;
-    *(uint4*)&T.pre[4 * lane] = make_uint4(p, p + c0, p + c1, p + c2);
-    *(uint4*)&T.word[4 * lane] = m;
+    return (uint32_t)x - c[3];
+}
+
+// The lanes' words and the members before each into the table (the wavefront's
+// own: its later reads follow these writes in order).
+__device__ __forceinline__ void mask_rows(MaskTable<kMasksShort>& T, const ShellMasks&, int64_t, int,
+                                          const MaskWords<kMasksShort>& mk, int lane)
+{
+    uint32_t c[4];
+    const uint32_t p = mask_scan(mk.v[0], c);
+    *(uint4*)&T.pre[4 * lane] = make_uint4(p, p + c[0], p + c[1], p + c[2]);
+    *(uint4*)&T.word[4 * lane] = mk.v[0];
+    __builtin_amdgcn_wave_barrier();
+}
+
+// (the words past the first 512 are loaded here)
+__device__ __forceinline__ void mask_rows(MaskTable<kMasksLong>& T, const ShellMasks& sm, int64_t a, int nw,
+                                          const MaskWords<kMasksLong>& mk, int lane)
+{
+    uint32_t before = 0;
+    for (int q = 0; q < nw; q += 256) {
+        const uint4 m = q == 0 ? mk.v[0] : (q == 256 ? mk.v[1] : mask_load(sm, a, nw, q, lane));
+        uint32_t c[4];
+        const uint32_t p = before + mask_scan(m, c);
+        *(uint2*)&T.pre[q + 4 * lane] = make_uint2((p & 0xffffu) | ((p + c[0]) << 16), ((p + c[1]) & 0xffffu) | ((p + c[2]) << 16));
+        before = bcast(p + c[3], 63);
+    }
     __builtin_amdgcn_wave_barrier();
 }
 
 // Sorted index of member r (below the list's length) of a row of nw words
 // (clamped to the last atom: the rows of a build that reported too few words
 // per row still read in bounds).
-__device__ __forceinline__ int mask_member(const MaskTable& T, int nw, int r, int last)
+__device__ __forceinline__ int mask_member(const MaskTable<kMasksShort>& T, const ShellMasks&, int64_t, int, int nw, int r,
+                                           int last)
 {
     int w = 0;
     if (nw > 128 && T.pre[128] <= (uint32_t)r) w = 128;
@@ -574,6 +629,19 @@ __device__ __forceinline__ int mask_member(const MaskTable& T, int nw, int r, in
     for (int s = 64; s >= 1; s >>= 1) w += T.pre[w + s] <= (uint32_t)r ? s : 0;
     const int b = nth_set_bit(T.word[w], (uint32_t)r - T.pre[w]);
     return (int)min((uint32_t)(T.base[2 * w + (b >> 4)] + (b & 15)), (uint32_t)last);
+}
+
+// (a, slot: the atom and its block, whose rows in memory hold the word and its bases)
+__device__ __forceinline__ int mask_member(const MaskTable<kMasksLong>& T, const ShellMasks& sm, int64_t a, int slot, int nw,
+                                           int r, int last)
+{
+    int w = 0;
+    for (int s = 1 << (31 - __builtin_clz(nw | 1)); s >= 1; s >>= 1)
+        w += w + s < nw && (uint32_t)T.pre[w + s] <= (uint32_t)r ? s : 0;
+    const uint32_t m = sm.mask[a * (int64_t)sm.cap + w];
+    const int2 base = *(const int2*)&sm.words[2 * ((int64_t)slot * sm.cap + w)];
+    const int b = nth_set_bit(m, (uint32_t)r - T.pre[w]);
+    return (int)min((uint32_t)((b >> 4 ? base.y : base.x) + (b & 15)), (uint32_t)last);
 }
 
 // A drawn atom j of atom a (sorted indices) counts as a shell pair: not a
@@ -632,32 +700,34 @@ __global__ __launch_bounds__(kDecodeBlock) void k_stencil_decode(int64_t n, int 
 // Shell lists as masks: the drawn atoms of the current batch (the list members
 // at the drawn ranks) into batch_j, for the adjoint when no forward at this
 // step wrote them. One wavefront per apw consecutive atoms.
+template <int ENC>
 __global__ __launch_bounds__(kDecodeBlock) void k_list_decode(int64_t n, int apw, ShellMasks sm,
                                                               const int32_t* __restrict__ nshell, int p_shell,
                                                               int p_stride, const uint16_t* __restrict__ ranks,
                                                               int32_t* __restrict__ batch_j)
 {
-    __shared__ __align__(16) MaskTable tab[kDecodeBlock / 64];
+    __shared__ __align__(16) MaskTable<ENC> tab[kDecodeBlock / 64];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int64_t a0 = ((int64_t)blockIdx.x * (kDecodeBlock / 64) + wave) * apw;
     const int64_t a1 = min(n, a0 + apw);
-    MaskTable& T = tab[wave];
+    MaskTable<ENC>& T = tab[wave];
     int cur = -1, nw = 0;
     for (int64_t a = a0; a < a1; ++a) {
         const int slot = sm.slot_of[a];
         if (slot != cur) {
             nw = sm.nw[slot];
-            mask_bases(T, sm, slot, nw, lane);
+            if constexpr (ENC == kMasksShort) mask_bases(T, sm, slot, nw, lane);
             cur = slot;
         }
         const int m = nshell[a];
         const bool sample = m > p_shell;
         const int cnt = sample ? p_shell : m;
         const uint16_t* rrow = ranks + a * (int64_t)p_stride;
-        mask_rows(T, mask_load(sm, a, nw, lane), lane);
+        mask_rows(T, sm, a, nw, mask_ahead<ENC>(sm, a, nw, lane), lane);
         for (int c = lane; c < cnt; c += 64)
-            batch_j[a * (int64_t)p_stride + c] = mask_member(T, nw, sample ? (int)rrow[c] : c, (int)n - 1);
+            batch_j[a * (int64_t)p_stride + c] =
+                mask_member(T, sm, a, slot, nw, sample ? (int)rrow[c] : c, (int)n - 1);
     }
 }
 
@@ -735,7 +805,7 @@ __device__ __forceinline__ void add_excl(PairSum<real>& px, uint4 si, real qi, u
     }
 }
 
-template <typename real, bool FULL, bool EV, bool STENCIL, bool SKIN, bool ENC>
+template <typename real, bool FULL, bool EV, bool STENCIL, bool SKIN, int ENC>
 __global__ __launch_bounds__(kCoopBlock, ENC && !EV && sizeof(real) == 4 ? 5 : 1) void k_pair_coop(
     int64_t n, int apw, PairParams<real> pp, const uint4* __restrict__ spos, const real* __restrict__ sqr,
     const uint4* __restrict__ spq, const int2* __restrict__ sxr, const int32_t* __restrict__ sxidx,
@@ -748,7 +818,7 @@ __global__ __launch_bounds__(kCoopBlock, ENC && !EV && sizeof(real) == 4 ? 5 : 1
     __shared__ LJ<real> lj[256];
     __shared__ double red[kPairPartials * (kCoopBlock / 64)];
     __shared__ StencilRows<STENCIL ? kDecodeRows : 1> srows[kCoopBlock / 64];  // stencil rows of one cell per wave
-    __shared__ __align__(16) unsigned char mtab[ENC ? (kCoopBlock / 64) * sizeof(MaskTable) : 16];  // masks: one atom's row per wave
+    __shared__ __align__(16) unsigned char mtab[ENC ? (kCoopBlock / 64) * sizeof(MaskTable<ENC>) : 16];  // masks: one atom's row per wave
     constexpr bool kPass = FULL && !EV;
     constexpr bool kFused = fused_form(FULL, EV, SKIN);  // (ke and quantum come scaled)
     const int nt2 = n_types * n_types;
@@ -785,7 +855,7 @@ __global__ __launch_bounds__(kCoopBlock, ENC && !EV && sizeof(real) == 4 ? 5 : 1
     const int h_mol = STENCIL ? sa.smol[ah] : 0;
     const int h_slot = ENC ? sm.slot_of[ah] : 0;
     const int h_nw = ENC ? sm.nw[h_slot] : 0;
-    MaskTable& T = reinterpret_cast<MaskTable*>(mtab)[ENC ? wave : 0];
+    MaskTable<ENC>& T = reinterpret_cast<MaskTable<ENC>*>(mtab)[ENC ? wave : 0];
     // shell weight N_S / p~ (1 when every member is taken), one division per lane
     const real h_w = (!FULL && h_ns > p_shell) ? (real)((double)h_ns / (double)p_shell) : (real)1;
     const int nrows = sa.span * sa.span;
@@ -797,8 +867,8 @@ __global__ __launch_bounds__(kCoopBlock, ENC && !EV && sizeof(real) == 4 ? 5 : 1
     // (entries nc .. nc + nx - 1 of the combined list); with energies they keep
     // their own slot.
     constexpr bool kFold = !EV;
-    auto first_level = [&](int64_t a, int t, int& jc, int& r0, int& r1, int& jx, uint4& mk) {
-        if (ENC) mk = mask_load(sm, a, bcast(h_nw, t), lane);
+    auto first_level = [&](int64_t a, int t, int& jc, int& r0, int& r1, int& jx, MaskWords<ENC>& mk) {
+        if (ENC) mk = mask_ahead<ENC>(sm, a, bcast(h_nw, t), lane);
         const int nc = bcast(h_nc, t);
         const int ns = bcast(h_ns, t);
         const int2 xr = make_int2(bcast(h_x.x, t), bcast(h_x.y, t));
@@ -825,25 +895,31 @@ __global__ __launch_bounds__(kCoopBlock, ENC && !EV && sizeof(real) == 4 ? 5 : 1
         jx = (!kFold && lane < xr.y) ? sxidx[xr.x + lane] : -1;
     };
     // atom a's mask row (its lanes' words mk) into the wavefront's table
-    auto mask_table = [&](int t, uint4 mk) {
-        const int slot = bcast(h_slot, t);
-        if (slot != tslot) {
-            mask_bases(T, sm, slot, bcast(h_nw, t), lane);
-            tslot = slot;
+    auto mask_table = [&](int64_t a, int t, const MaskWords<ENC>& mk) {
+        if constexpr (ENC == kMasksShort) {
+            const int slot = bcast(h_slot, t);
+            if (slot != tslot) {
+                mask_bases(T, sm, slot, bcast(h_nw, t), lane);
+                tslot = slot;
+            }
         }
-        mask_rows(T, mk, lane);
+        if constexpr (ENC != kIndices) mask_rows(T, sm, a, bcast(h_nw, t), mk, lane);
+    };
+    // the shell member at position q of atom a's list as a mask in the table
+    auto masked = [&](int64_t a, int t, int q) -> int {
+        if constexpr (ENC != kIndices) return mask_member(T, sm, a, bcast(h_slot, t), bcast(h_nw, t), q, (int)n - 1);
+        return -1;
     };
     // second level of an atom's first pass: the shell members at its two ranks (the
     // atoms themselves with stencil sampling)
-    auto second_level = [&](int64_t a, int t, int r0, int r1, uint4 mk, int& e0, int& e1) {
+    auto second_level = [&](int64_t a, int t, int r0, int r1, const MaskWords<ENC>& mk, int& e0, int& e1) {
         if (STENCIL) {
             e0 = r0;
             e1 = r1;
         } else if (ENC) {
-            mask_table(t, mk);
-            const int nw = bcast(h_nw, t);
-            e0 = r0 >= 0 ? mask_member(T, nw, r0, (int)n - 1) : -1;
-            e1 = r1 >= 0 ? mask_member(T, nw, r1, (int)n - 1) : -1;
+            mask_table(a, t, mk);
+            e0 = r0 >= 0 ? masked(a, t, r0) : -1;
+            e1 = r1 >= 0 ? masked(a, t, r1) : -1;
         } else {
             const int32_t* s1 = shell + a * (int64_t)cap_shell;
             e0 = r0 >= 0 ? s1[r0] : -1;
@@ -908,7 +984,7 @@ __global__ __launch_bounds__(kCoopBlock, ENC && !EV && sizeof(real) == 4 ? 5 : 1
     }
     int n_jc = -1, n_e0 = -1, n_e1 = -1, n_jx = -1;  // atom a: first level and shell entries
     int m_jc = -1, m_r0 = -1, m_r1 = -1, m_jx = -1;  // atom a + 1: first level
-    uint4 m_mk = make_uint4(0u, 0u, 0u, 0u);         // ... and its mask words
+    MaskWords<ENC> m_mk{};                           // ... and its mask words
     if (!kPass && a0 < a1) {
         int r0, r1;
         first_level(a0, 0, n_jc, r0, r1, n_jx, m_mk);
@@ -930,7 +1006,7 @@ __global__ __launch_bounds__(kCoopBlock, ENC && !EV && sizeof(real) == 4 ? 5 : 1
         const int32_t* crow = core + a * (int64_t)cap_core;
         const int32_t* srow = shell + a * (int64_t)cap_shell;
         // shell member at position q of the atom's list (masks: the atom's row in T)
-        auto member = [&](int q) -> int { return ENC ? mask_member(T, bcast(h_nw, t), q, (int)n - 1) : srow[q]; };
+        auto member = [&](int q) -> int { return ENC ? masked(a, t, q) : srow[q]; };
         const uint16_t* rrow = ranks + a * (int64_t)p_stride;
         const bool sample = !FULL && ns > p_shell;
         const int cnt = sample ? p_shell : ns;
@@ -1017,7 +1093,7 @@ __global__ __launch_bounds__(kCoopBlock, ENC && !EV && sizeof(real) == 4 ? 5 : 1
             }
         }
         // (the table holds the next atom's row by now)
-        if (ENC && cnt > 128) mask_table(t, mask_load(sm, a, bcast(h_nw, t), lane));
+        if (ENC && cnt > 128) mask_table(a, t, mask_ahead<ENC>(sm, a, bcast(h_nw, t), lane));
         for (int c = lane + 128; c < cnt; c += 64) {
             if (STENCIL) {
                 const int j = stencil_rows_atom(srows[wave], nrows, sample ? (int)rrow[c] : c);
@@ -1267,8 +1343,12 @@ static hipError_t launch_list_decode(irbe_ctx* h)
     if (e != hipSuccess) return e;
     const int apw = 16;
     const int64_t waves = blocks_for(n, apw);
-    k_list_decode<<<(unsigned)blocks_for(waves, kDecodeBlock / 64), kDecodeBlock, 0, h->stream>>>(
-        n, apw, h->shell_masks(), h->nshell, h->cfg.p_shell, h->p_stride, h->ranks, h->batch_j);
+    auto run = [&](auto enc) {
+        k_list_decode<decltype(enc)::value><<<(unsigned)blocks_for(waves, kDecodeBlock / 64), kDecodeBlock, 0, h->stream>>>(
+            n, apw, h->shell_masks(), h->nshell, h->cfg.p_shell, h->p_stride, h->ranks, h->batch_j);
+    };
+    if (h->cap_words > kMaskTableWords) run(std::integral_constant<int, kMasksLong>{});
+    else run(std::integral_constant<int, kMasksShort>{});
     return hipGetLastError();
 }
 
@@ -1345,7 +1425,7 @@ static int spread_atoms(int64_t n, int apw)
     return apw;
 }
 
-template <typename real, bool FULL, bool EV, bool STENCIL, bool SKIN, bool ENC = false>
+template <typename real, bool FULL, bool EV, bool STENCIL, bool SKIN, int ENC = kIndices>
 static hipError_t launch_coop_t(irbe_ctx* h, uint64_t step)
 {
     const int64_t n = h->cfg.n_atoms;
@@ -1406,9 +1486,12 @@ static hipError_t launch_coop_s(irbe_ctx* h, uint64_t step, bool ev)
     if (h->stencil)
         return ev ? launch_coop_t<real, false, true, true, SKIN>(h, step)
                   : launch_coop_t<real, false, false, true, SKIN>(h, step);
+    if (h->masks && h->cap_words > kMaskTableWords)
+        return ev ? launch_coop_t<real, false, true, false, SKIN, kMasksLong>(h, step)
+                  : launch_coop_t<real, false, false, false, SKIN, kMasksLong>(h, step);
     if (h->masks)
-        return ev ? launch_coop_t<real, false, true, false, SKIN, true>(h, step)
-                  : launch_coop_t<real, false, false, false, SKIN, true>(h, step);
+        return ev ? launch_coop_t<real, false, true, false, SKIN, kMasksShort>(h, step)
+                  : launch_coop_t<real, false, false, false, SKIN, kMasksShort>(h, step);
     return ev ? launch_coop_t<real, false, true, false, SKIN>(h, step)
               : launch_coop_t<real, false, false, false, SKIN>(h, step);
 }
