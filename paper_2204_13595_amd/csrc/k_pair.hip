@@ -805,6 +805,13 @@ __device__ __forceinline__ void add_excl(PairSum<real>& px, uint4 si, real qi, u
     }
 }
 
+// Excluded partners of an atom up to which they share the passes of its full list; more
+// come 64 for each of the wavefront's atoms in turn, which mostly share them, as their
+// records are read from L2 for every atom otherwise. Forces, in the passes against in
+// turn, molecules of 400: 96,000 atoms 312 and 278 us, 12,000 atoms 46 and 49; of
+// 1,000: 584 and 470, 66 and 65; of 4,000: 2,068 and 1,622, 194 and 161.
+constexpr int kExclFolded = 512;
+
 template <typename real, bool FULL, bool EV, bool STENCIL, bool SKIN, int ENC>
 __global__ __launch_bounds__(kCoopBlock, ENC && !EV && sizeof(real) == 4 ? 5 : 1) void k_pair_coop(
     int64_t n, int apw, PairParams<real> pp, const uint4* __restrict__ spos, const real* __restrict__ sqr,
@@ -817,6 +824,7 @@ __global__ __launch_bounds__(kCoopBlock, ENC && !EV && sizeof(real) == 4 ? 5 : 1
 {
     __shared__ LJ<real> lj[256];
     __shared__ double red[kPairPartials * (kCoopBlock / 64)];
+    __shared__ real excl_f[FULL && !EV ? kCoopBlock / 64 : 1][4][3];  // full lists: excluded pairs of large molecules
     __shared__ StencilRows<STENCIL ? kDecodeRows : 1> srows[kCoopBlock / 64];  // stencil rows of one cell per wave
     __shared__ __align__(16) unsigned char mtab[ENC ? (kCoopBlock / 64) * sizeof(MaskTable<ENC>) : 16];  // masks: one atom's row per wave
     constexpr bool kPass = FULL && !EV;
@@ -930,14 +938,42 @@ __global__ __launch_bounds__(kCoopBlock, ENC && !EV && sizeof(real) == 4 ? 5 : 1
     // the shell entries of atom a + 1 and the first level of atom a + 2 are loaded
     // (issued after atom a's gathers, so that waiting for those does not wait for
     // them: the vector memory counter is in order)
-    // Full list without energies: the list and the excluded partners as one sequence
+    // Full list without energies: the list and the excluded partners (those of large
+    // molecules before it, kExclFolded) as one sequence
     // of 64-entry passes, the indices of the pass after next and the atoms of the next
     // one in flight while a pass is evaluated. Bound by vector issue (13 passes of a
     // water atom's 728 entries at about 60 slots): 3,145,728 atoms 4.4 ms, 4.92 ms as
     // a loop of dependent loads with the excluded pairs in a pass of their own.
     if constexpr (kPass) {
+        static_assert(kAtomsPerWaveList <= 4, "sums of excluded pairs per atom");
+        auto folded = [&](int t) { const int nx = bcast(h_x.y, t); return nx <= kExclFolded ? nx : 0; };
+        const bool large = __builtin_amdgcn_ballot_w64(h_x.y > kExclFolded) != 0;
+        if (large) {
+            PairSum<real> e[4];
+            for (int c0 = 0, more = 1; more; c0 += 64) {
+                more = 0;
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const int nx = a0 + t < a1 ? bcast(h_x.y, t) : 0;
+                    if (nx <= kExclFolded || c0 >= nx) continue;
+                    more |= c0 + 64 < nx;
+                    if (c0 + lane < nx) {
+                        const uint4 si = make_uint4(bcast(h_s.x, t), bcast(h_s.y, t), bcast(h_s.z, t), bcast(h_s.w, t));
+                        uint4 sj;
+                        real q;
+                        at.get(sxidx[bcast(h_x.x, t) + c0 + lane], sj, q);
+                        add_pair_or_excl<real, kFused>(e[t], e[t], si, bcast(h_q, t) * pp.ke, sj, q, lj[0], pp, true);
+                    }
+                }
+            }
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const real f = wave_sum4(e[t].fx, e[t].fy, e[t].fz, e[t].fz);
+                if (f_comp >= 0) excl_f[wave][t][f_comp] = f;
+            }
+        }
         auto entry = [&](int64_t a, int t, int pass) -> int {
-            const int ns = bcast(h_ns, t), nx = bcast(h_x.y, t);
+            const int ns = bcast(h_ns, t), nx = folded(t);
             const int e = pass * 64 + lane;
             const int32_t* const srow = shell + a * (int64_t)cap_shell;
             if (pass * 64 + 64 <= ns) return srow[e];  // (uniform: a pass of list entries only)
@@ -954,7 +990,7 @@ __global__ __launch_bounds__(kCoopBlock, ENC && !EV && sizeof(real) == 4 ? 5 : 1
             const real qi = bcast(h_q, t) * pp.ke;
             const LJ<real>* const lrow = lj + (int)si.w * n_types;
             const int ns = bcast(h_ns, t);
-            const int passes = (ns + bcast(h_x.y, t) + 63) >> 6;
+            const int passes = (ns + folded(t) + 63) >> 6;
             int j = n_j0, jn = n_j1;
             uint4 pj;
             real qj;
@@ -975,7 +1011,9 @@ __global__ __launch_bounds__(kCoopBlock, ENC && !EV && sizeof(real) == 4 ? 5 : 1
                 if (in && (ex || !SKIN || dist2_q(si, sj) <= t_shell))
                     add_pair_or_excl<real, kFused>(pc, px, si, qi, sj, q, lrow[sj.w], pp, ex);
             }
-            const real f = pp.quantum * wave_sum4(pc.fx, pc.fy, pc.fz, pc.fz);
+            real f = wave_sum4(pc.fx, pc.fy, pc.fz, pc.fz);
+            if (large && f_comp >= 0) f += excl_f[wave][t][f_comp];
+            f *= pp.quantum;
             if (f_comp >= 0) {
                 fsr[3 * a + f_comp] = f;
                 fc_sum += (double)f;

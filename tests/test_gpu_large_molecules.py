@@ -79,3 +79,40 @@ def test_excluded_pairs_reach_the_forces(orc, precision):
     err = np.sqrt(((f - ref.force) ** 2).sum() / (ref.force ** 2).sum())
     assert err < (1e-10 if precision == "fp64" else 1e-5)
     h.close()
+
+
+@pytest.mark.parametrize("skin", [0.0, 0.04])
+@pytest.mark.parametrize("per_mol", [513, 514, 900])
+def test_full_list_forces(orc, per_mol, skin):
+    """Full lists without energies: excluded partners in the list's passes (up to 512) and
+    before them, atoms of either kind and of no molecule in one wavefront."""
+    from paper_2204_13595_amd import irbe
+    n, box, r_core, r_shell = 1700, 2.6, 0.5, 1.2
+    rng = np.random.default_rng(per_mol)
+    g = (np.arange(12) + 0.5) * (box / 12)
+    sites = np.stack(np.meshgrid(g, g, g, indexing="ij"), -1).reshape(-1, 3)
+    pos_np = sites[rng.permutation(len(sites))[:n]] + rng.uniform(-0.02, 0.02, (n, 3))
+    order = np.lexsort((pos_np[:, 0], np.floor(pos_np[:, 1] / 0.7), np.floor(pos_np[:, 2] / 0.7)))
+    mol = np.full(n, -1, np.int32)  # every eighth atom along the order of none
+    member = order[np.arange(n) % 8 != 3]
+    mol[member[:per_mol]] = 7
+    rest = member[per_mol:]
+    mol[rest] = 20 + np.arange(len(rest)) // 300
+    q = rng.choice([-0.7, 0.7], n)
+    t, sig, eps = np.zeros(n, np.int32), np.array([0.15]), np.array([0.4])
+    dev = torch.device("cuda", 0)
+    for precision, dt, tol in (("fp64", torch.float64, 1e-11), ("mixed", torch.float32, 1e-5)):
+        h = irbe.Handle(n, box, r_core=r_core, r_shell=r_shell, p_shell=0, p_kspace=8, n_types=1, skin=skin,
+                        precision=precision, device=dev)
+        h.set_system(torch.tensor(t, device=dev), torch.tensor(q, dtype=dt, device=dev), torch.tensor(mol, device=dev),
+                     sig, eps)
+        pos = torch.tensor(pos_np, dtype=dt, device=dev)
+        h.build_lists(pos, 1)
+        s = orc.quantize(pos.double().cpu().numpy(), box)
+        lists = orc.build_lists(s, mol, box, r_core, r_shell, full=True, skin=skin)
+        f = h.compute_forces(pos, 1).double().cpu().numpy()
+        p = orc.Params(box=box, r_core=r_core, r_shell=r_shell, p_shell=0, p_kspace=8, n_types=1, skin=skin)
+        ref = orc.forward(None, torch.tensor(q, dtype=dt).double().numpy(), t, mol, sig, eps, p, step=1, mode="full",
+                          s=s, lists=lists)
+        assert np.sqrt(((f - ref.force) ** 2).sum() / (ref.force ** 2).sum()) < tol
+        h.close()
