@@ -809,6 +809,8 @@ irbe_status irbe_build_lists(irbe_handle h, const void* pos, uint64_t step)
     h->have_lists = false;
     h->ranks_valid = false;
     h->batch_j_valid = h->batch_j_fwd = false;
+    // (rows that a growth gave up and could not allocate again)
+    if (!h->core || !h->shell) IRBE_TRY(h, alloc_lists(h, h->cap_core, h->cap_shell), "allocating the lists");
     if (h->lists_sized && !h->stencil) {
         // steady state: queue the build and a copy of its error word and list
         // lengths, and take in an earlier copy if it has completed; no wait

@@ -99,3 +99,16 @@ def test_large_molecules_are_excluded_by_id(record, per_mol, by_id):
     assert any("k_excl_sorted" in n for n in names) == by_id
     assert any("k_list_blocksILi0ELb0ELb1ELb%dEEE" % by_id in n or "k_list_blocksILi0ELb1ELb1ELb%dEEE" % by_id in n
                for n in names)
+
+
+@pytest.mark.parametrize("k", [0, 1, 2])
+def test_a_build_after_a_failed_growth_allocates_first(record, k):
+    """Rows that a failed growth has given up are allocated before any kernel is queued."""
+    calls = record("create:n=4000,box=4", "set", "build", "overflow=5000,100,0,2", "build", f"fail={k}", "sync",
+                   "overflow=0,0,0,0", "forces", "fail=0", "build", "build", "forces")
+    status = [c[1] for c in calls]
+    assert status[:6] == [0] * 6 and status[6] == -2  # IRBE_ENOMEM
+    assert status[8] == -5                            # forces: IRBE_ESTATE
+    assert status[10] == -2 and not [r for r in calls[10][2] if r.startswith("launch")]
+    assert status[11] == status[12] == 0
+    assert [r for r in calls[11][2] if r.startswith("malloc")]
