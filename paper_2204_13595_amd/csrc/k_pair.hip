@@ -352,11 +352,21 @@ __global__ __launch_bounds__(BLOCK) void k_draw_batches(int64_t n, const int32_t
 // that meets the rejection test of the multiply-shift takes the one-step form.
 // What bounds the other form there is one thread's chain of 25 blocks and bitmap round
 // trips, about 14 us for 100 draws however few the atoms. One thread against half a
-// wavefront: 14.3 and 4.8 us at 2,703 atoms, 14.9 and 7.8 at 12,288, but 29.6 and 33.3
-// at 98,304, where this form's idle lanes (25 of 32 draw) cost more than the chain.
+// wavefront, 100 draws: 14.3 and 4.8 us at 2,703 atoms, 14.9 and 7.8 at 12,288, but 29.6
+// and 33.3 at 98,304, where this form's idle lanes (25 of 32 draw) cost more than the
+// chain. The fewer the draws, the shorter the chain and the more lanes idle: draw and
+// pairs with 10 draws, 24,000 ions: 14.0 and 16.7 us; 24,000 atoms of water, 20 draws:
+// 26.5 and 29.2, 50: 31.1 and 30.7; 8,000 atoms, 10: 14.8 and 14.8. The line is that of
+// equal times, about 500 (draws - 4) atoms; up to 8,192 atoms few draws take either alike.
 constexpr int kHalfDrawBlock = 256;
 constexpr int kHalfDrawMost = 128;         // steps
 constexpr int64_t kHalfDrawAtoms = 32768;
+
+static bool half_draw(int64_t n, int p_shell)
+{
+    return p_shell <= kHalfDrawMost &&
+           n < std::min<int64_t>(kHalfDrawAtoms, std::max<int64_t>(8192, 500 * (int64_t)(p_shell - 4)));
+}
 
 __global__ __launch_bounds__(kHalfDrawBlock) void k_draw_batches_half(int64_t n, const int32_t* __restrict__ perm,
                                                                       const int32_t* __restrict__ nshell, int p_shell,
@@ -1419,7 +1429,7 @@ static hipError_t launch_draw(irbe_ctx* h, uint64_t step)
     const int block = draw_block(h, &lds);
     const unsigned nb = (unsigned)blocks_for(n, block);
     const size_t half_lds = (size_t)(kHalfDrawBlock / 32) * h->shell_bound() * 4;
-    if (n < kHalfDrawAtoms && h->cfg.p_shell <= kHalfDrawMost && half_lds <= 64 * 1024) {
+    if (half_draw(n, h->cfg.p_shell) && half_lds <= 64 * 1024) {
         k_draw_batches_half<<<(unsigned)blocks_for(n, kHalfDrawBlock / 32), kHalfDrawBlock, half_lds, h->stream>>>(
             n, h->perm, h->nshell, h->cfg.p_shell, h->p_stride, h->cfg.seed, step, h->shell_bound(), h->ranks);
     } else if (lds > 64 * 1024) {

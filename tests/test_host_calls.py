@@ -112,3 +112,14 @@ def test_a_build_after_a_failed_growth_allocates_first(record, k):
     assert status[10] == -2 and not [r for r in calls[10][2] if r.startswith("launch")]
     assert status[11] == status[12] == 0
     assert [r for r in calls[11][2] if r.startswith("malloc")]
+
+
+@pytest.mark.parametrize("n,p,half", [(4000, 100, True), (8191, 5, True), (8192, 20, False), (8192, 21, True),
+                                      (24000, 10, False),
+                                      (24000, 52, False), (24000, 53, True), (32767, 128, True), (32768, 128, False),
+                                      (4000, 129, False)])
+def test_draw_form_by_atoms_and_draws(record, n, p, half):
+    """Few draws per atom leave most lanes of the half-wavefront form idle."""
+    calls = record(f"create:n={n},box={(n / 100) ** (1 / 3):.4f},p={p}", "set", "build", "forces")
+    names = [r.split()[1] for r in calls[3][2] if r.startswith("launch")]
+    assert any("k_draw_batches_half" in k for k in names) == half
