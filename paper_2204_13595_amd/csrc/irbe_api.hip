@@ -622,8 +622,6 @@ irbe_status irbe_create(const irbe_config* cfg, void* hip_stream, irbe_handle* o
     ALLOC(dalloc(h, &h->ev_pair, kPairPartials));
     ALLOC(dalloc(h, &h->kvec, P));
     ALLOC(dalloc(h, &h->kcoef, 4 * P));
-    h->p_stride = c.p_shell > 0 ? (c.p_shell + 3) / 4 * 4 : 0;
-    h->part_blocks = nb64;
     // (a small system's structure factors in many blocks take more partial sums: not
     // where they alone would exceed the no-allocation scratch)
     if (noalloc_bytes(h) > kNoAllocScratchBytes) {

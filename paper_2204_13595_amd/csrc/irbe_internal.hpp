@@ -295,7 +295,12 @@ hipError_t launch_bin(irbe_ctx* h, const void* pos);
 // Positions and charges of a force evaluation, and the k-vectors of `step`.
 hipError_t launch_requantize(irbe_ctx* h, const void* pos, uint64_t step);
 hipError_t launch_build_lists(irbe_ctx* h);
-// Mean atoms per cell below which the list build takes one lane per atom.
+// Mean atoms per cell below which the list build takes one lane per atom. Build + forces
+// (100 draws), lanes against blocks, 400,000 atoms: 1.3 per cell 314 + 182 and 336 + 296 us,
+// 2: 365 + 271 and 318 + 372, 3: 476 + 293 and 321 + 372, 4: 544 + 356 and 317 + 374, 8:
+// 724 + 463 and 325 + 378; full lists, 3: 436 + 198 and 488 + 198, 5: 579 + 291 and 530 + 283.
+// The lanes' lists of indices make the cheaper forces, which counts where lists are kept; the
+// blocks build small boxes faster at any density (30,000 atoms, 3: 235 + 37 and 54 + 46).
 constexpr double kLaneMaxPerCell = 4.0;
 // True when it does (k_build_lists_lanes); else the blocks below.
 bool lists_by_lanes(const irbe_ctx* h);

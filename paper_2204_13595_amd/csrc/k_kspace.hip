@@ -321,7 +321,10 @@ __global__ __launch_bounds__(kBlock) void k_kspace_forces_lanes(
 // (131,072 atoms: two waves on each of 1,024 SIMDs), four below, sixteen for the
 // smallest systems. One against several lanes, forces, p = 200: 45 -> 28 us at
 // 98,304 atoms (4), 43 -> 7.1 us at 2,703 atoms (16); FP64, p = 100, 98,304 atoms:
-// 48 -> 27 us. The several lanes repeat the additions, so a full chip loses by them.
+// 48 -> 27 us. The several lanes repeat the additions, so a full chip loses by them: p = 100,
+// 1, 4 and 16 lanes, 2,700 atoms 26.8, 7.3, 7.1 us; 8,000: 26.9, 7.4, 9.1; 16,384: 26.6, 7.6,
+// 13.0; 131,072: 25.0, 21.6, 65.9; 262,144: 26.5, 37.5, 125 (equal times of 4 and 16 at about
+// 4,000 atoms, of 1 and 4 at about 180,000, for any p from 50 to 600).
 static int kspace_lanes(const irbe_ctx* h)
 {
     const int64_t n = h->cfg.n_atoms;

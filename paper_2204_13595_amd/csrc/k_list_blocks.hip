@@ -32,7 +32,7 @@
 // atoms: by comparing ids, chunk by chunk), and the masks are written out as
 // lists, chunk by chunk: a member's place is a bit count.
 //
-// What bounds it: vector issue (397 instructions per atom at 3.1 M atoms of
+// What bounds it: vector issue (395 instructions per atom at 3.1 M atoms of
 // water, of which the 60 chunks of a block take about 100 each). Split lists of
 // that box: 2.75 ms (6.03 ms with the candidate tests on the vector units and
 // 16-bit list entries stored per member); of 98,304 atoms 0.14 ms (0.43 ms), of

@@ -92,7 +92,7 @@ __device__ __forceinline__ bool in_annulus(uint4 a, uint4 b, uint64_t t_lo, uint
 // The pair terms come in two forms. Full lists and lists kept with a skin (forces
 // only) and the gradients take the fused one: separations in quanta scaled once
 // per atom, erfc through exp(x^2) erfc(x), so that one exponential serves both
-// terms of Eq. (2.10) (53 issue slots of a pair against 65, errors no larger).
+// terms of Eq. (2.10) (errors no larger).
 // Lists rebuilt every step, and every energy, keep the plain form: the MD state
 // integrated from those forces, and the FP64 energies, virials and LJ gradients
 // summed from the FP32 terms, resolve a change of their last bits, and runs are
@@ -1874,9 +1874,9 @@ __global__ __launch_bounds__(kCoopBlock) void k_pair_adjoint(
     const int2 h_x = sxr[ah];
     // shell weight N_S / p~ (1 when every member is taken), one division per lane
     const real h_w = h_ns > p_shell ? (real)((double)h_ns / (double)p_shell) : (real)1;
-    // first-level indices of one atom's first pass: the lane's first symmetric-list
-    // entry, its two batch ranks (or shell positions) and its first excluded partner
-    auto first_level = [&](int64_t a, int t, int& jc, int& r0, int& r1, int& jx) {
+    // first-level indices of one atom's first pass: the lane's first symmetric-list entry
+    // or excluded partner and its two batch ranks (or shell positions)
+    auto first_level = [&](int64_t a, int t, int& jc, int& r0, int& r1) {
         const int nsym = bcast(h_nsym, t);
         const int ns = bcast(h_ns, t);
         const int2 xr = make_int2(bcast(h_x.x, t), bcast(h_x.y, t));
@@ -1896,15 +1896,14 @@ __global__ __launch_bounds__(kCoopBlock) void k_pair_adjoint(
             r0 = lane < cnt ? (sample ? (int)rrow[lane] : lane) : -1;
             r1 = lane + 64 < cnt ? (sample ? (int)rrow[lane + 64] : lane + 64) : -1;
         }
-        jx = -1;
     };
-    int n_jc = -1, n_r0 = -1, n_r1 = -1, n_jx = -1;
-    if (a0 < a1) first_level(a0, 0, n_jc, n_r0, n_r1, n_jx);
+    int n_jc = -1, n_r0 = -1, n_r1 = -1;
+    if (a0 < a1) first_level(a0, 0, n_jc, n_r0, n_r1);
     for (int64_t a = a0; a < a1; ++a) {
         const int t_a = (int)(a - a0);
-        const int jc = n_jc, r0 = n_r0, r1 = n_r1, jx = n_jx;
+        const int jc = n_jc, r0 = n_r0, r1 = n_r1;
         // the next atom's first-level loads go out before this atom's dependent ones
-        if (a + 1 < a1) first_level(a + 1, t_a + 1, n_jc, n_r0, n_r1, n_jx);
+        if (a + 1 < a1) first_level(a + 1, t_a + 1, n_jc, n_r0, n_r1);
         const uint4 si = make_uint4(bcast(h_s.x, t_a), bcast(h_s.y, t_a), bcast(h_s.z, t_a),
                                     bcast(h_s.w, t_a));
         const int ti = (int)si.w;
@@ -2024,15 +2023,13 @@ __global__ __launch_bounds__(kCoopBlock) void k_pair_adjoint(
         // slots load atom 0)
         const int js0 = (STENCIL || BATCH) ? r0 : ((!FULL && r0 >= 0) ? srow[r0] : -1);
         const int js1 = (STENCIL || BATCH) ? r1 : ((!FULL && r1 >= 0) ? srow[r1] : -1);
-        const int ic = max(jc, 0), i0 = max(js0, 0), i1 = max(js1, 0), ix = max(jx, 0);
+        const int ic = max(jc, 0), i0 = max(js0, 0), i1 = max(js1, 0);
         uint4 pjc, pj0, pj1;
         real qjc, qj0, qj1;
         at.get(ic, pjc, qjc);
         const real gcx = gs[3 * (int64_t)ic], gcy = gs[3 * (int64_t)ic + 1], gcz = gs[3 * (int64_t)ic + 2];
         at.get(i0, pj0, qj0);
         at.get(i1, pj1, qj1);
-        (void)jx;
-        (void)ix;
         // skin: a symmetric-list entry counts inside r_core (r_shell for the full
         // list), a list shell entry inside the annulus, at these positions
         const uint64_t t_sym = FULL ? t_shell : t_core;
