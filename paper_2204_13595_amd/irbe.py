@@ -7,7 +7,6 @@ no fallback: if the library or a GPU is missing, the calls raise.
 """
 from __future__ import annotations
 
-import contextlib
 import ctypes
 import os
 
@@ -164,6 +163,7 @@ class Handle:
                           float(skin), float(lj_cut), int(shell_entries))
         with torch.cuda.device(self.device):
             self.stream = torch.cuda.current_stream(self.device)
+            self.raw_stream = self.stream.cuda_stream
             h = ctypes.c_void_p()
             st = self.lib.irbe_create(ctypes.byref(self.cfg), ctypes.c_void_p(self.stream.cuda_stream), ctypes.byref(h))
         if st != 0:
@@ -296,23 +296,27 @@ def _tables_on_host(lj_sigma: torch.Tensor, lj_eps: torch.Tensor):
     return s.cpu().numpy().copy(), e.cpu().numpy().copy()
 
 
-@contextlib.contextmanager
-def _handle_stream(h: Handle, *read: torch.Tensor):
-    """Work queued inside comes after the calling stream's, which made the tensors it
-    reads, and before what the calling stream does next; their memory stays theirs until
-    the handle's stream has read them. (The outputs are the calling stream's own.)"""
+def _to_handle_stream(h: Handle):
+    """Work queued on the handle's stream from here on comes after the calling stream's;
+    returns the calling stream where it is another one."""
+    # (the raw pointer: a Stream object costs several us on a path that the GPU waits for)
+    if torch._C._cuda_getCurrentRawStream(h.stream.device_index) == h.raw_stream:
+        return None
     current = torch.cuda.current_stream(h.device)
-    if current == h.stream:
-        yield
-        return
     h.stream.wait_stream(current)
-    try:
-        yield
-    finally:
-        for t in read:
-            if t.device == h.device:  # (else the call has raised)
-                t.record_stream(h.stream)
-        current.wait_stream(h.stream)
+    return current
+
+
+def _from_handle_stream(h: Handle, current, *read: torch.Tensor):
+    """The calling stream goes on after the handle's, and the memory of the tensors that
+    the handle's stream reads stays theirs until it has. (The outputs are the calling
+    stream's own.)"""
+    if current is None:
+        return
+    for t in read:
+        if t.device == h.device:  # (else the call has raised)
+            t.record_stream(h.stream)
+    current.wait_stream(h.stream)
 
 
 class IRBEForce(torch.autograd.Function):
@@ -325,9 +329,12 @@ class IRBEForce(torch.autograd.Function):
     def forward(ctx, pos, charge, lj_sigma, lj_eps, handle: Handle, step: int):
         sigma, eps = _tables_on_host(lj_sigma, lj_eps)
         q, x = charge.detach().contiguous(), pos.detach().contiguous()
-        with _handle_stream(handle, q, x):
+        current = _to_handle_stream(handle)
+        try:
             handle.update_parameters(charge=q, lj_sigma=sigma, lj_eps=eps)
             f = handle.compute_forces(x, step)
+        finally:
+            _from_handle_stream(handle, current, q, x)
         ctx.handle = handle
         ctx.step = step
         ctx.lj_host = (sigma, eps)  # the tables' values at the forward, which the backward takes again
@@ -340,9 +347,12 @@ class IRBEForce(torch.autograd.Function):
         h: Handle = ctx.handle
         sigma, eps = ctx.lj_host
         q, x, g = charge.detach().contiguous(), pos.detach().contiguous(), grad_f.contiguous()
-        with _handle_stream(h, q, x, g):
+        current = _to_handle_stream(h)
+        try:
             h.update_parameters(charge=q, lj_sigma=sigma, lj_eps=eps)
             gp, gq, gl = h.compute_forces_backward(x, ctx.step, g, want_charge=True, want_lj=True)
+        finally:
+            _from_handle_stream(h, current, q, x, g)
         nt2 = h.n_types ** 2
         g_sig = gl[:nt2].to(lj_sigma.dtype).reshape(lj_sigma.shape).to(lj_sigma.device)
         g_eps = gl[nt2:].to(lj_eps.dtype).reshape(lj_eps.shape).to(lj_eps.device)

@@ -2,8 +2,6 @@
 their queued work only when another one waits for them). The handle's stream waits for
 the inputs, copies of non-contiguous ones included, and the calling stream waits for the
 handle's before it reads the outputs."""
-import contextlib
-
 import pytest
 
 torch = pytest.importorskip("torch")
@@ -13,6 +11,8 @@ N, NT2 = 5, 4
 
 class Stream:
     """Work of the handle is queued and done when another stream waits for it."""
+
+    device_index = 0
 
     def __init__(self, log):
         self.queue, self.log = [], log
@@ -29,6 +29,7 @@ class FakeHandle:
 
     def __init__(self, stream, log):
         self.stream, self.device, self.log = stream, torch.device("cpu"), log
+        self.raw_stream = id(stream)
 
     def update_parameters(self, charge=None, lj_sigma=None, lj_eps=None):
         self.log.append(("params", charge))
@@ -54,7 +55,7 @@ def test_order_across_streams(monkeypatch, table_dtype):
     log, kept = [], []
     mine, current = Stream(log), Stream(log)
     monkeypatch.setattr(torch.cuda, "current_stream", lambda *a, **k: current)
-    monkeypatch.setattr(torch.cuda, "stream", lambda s: contextlib.nullcontext())
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda i: id(current), raising=False)
     monkeypatch.setattr(torch.Tensor, "record_stream", lambda t, s: kept.append((t.data_ptr(), s)), raising=False)
     real = torch.Tensor.contiguous
 
@@ -95,7 +96,7 @@ def test_no_waits_on_the_handles_stream(monkeypatch):
     from paper_2204_13595_amd.irbe import IRBEForce
     log = []
     mine = Stream(log)
-    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a, **k: mine)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda i: id(mine), raising=False)
     x = [torch.zeros(N, 3, requires_grad=True), torch.zeros(N, requires_grad=True),
          torch.ones(2, 2, requires_grad=True), torch.ones(2, 2, requires_grad=True)]
     f = IRBEForce.apply(*x, FakeHandle(mine, log), 1)
