@@ -659,7 +659,7 @@ bool exclusions_by_id(const irbe_ctx* h) { return h->max_excl > kPartnersMost; }
 // 789; 1.0, 1.6; 100: 978 and 1,057; 1.0, 2.0; 100: 1,180 and 1,112; 0.9, 1.6; 100, at
 // 45,000 atoms (255 MB): 137 and 145, at 65,000: 199 and 162; FP64, 98,304 atoms, 0.7,
 // 2.0; 100: 375 and 424. The build writes masks two to three times faster, but lists are
-// also kept. Indices of more than 32 GiB (a third of a card with the rest) are masks in any case.
+// also kept. Lists whose indices would take more than 32 GiB, a ninth of the card, are masks in any case.
 bool long_masks(const irbe_ctx* h, double words)
 {
     if (1.2 * words > kMaskMaxWords) return false;
